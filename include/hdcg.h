@@ -105,7 +105,10 @@ int dwf_destroy(dwf_op_t op);
  * shape = {bx, by, bz, bt, remap, lds_kb, nt, morton, phases, rg}.
  *   bx..bt  site block of one workgroup in (x/2, y, z, t), powers of two
  *           (all 0: consecutive checkerboard sites); a block that does not
- *           divide the lattice or exceeds 256 threads falls back to 0;
+ *           divide the lattice falls back to 0; one of more than 256 / Ls sites
+ *           is marched along t where the library has that form (Shamir, Ls 8,
+ *           12 or 16, by and bz >= 2, at most 16 waves of bx by bz sites, 8 in
+ *           complex128), else falls back to 0;
  *   remap   1: workgroups reordered so each XCD takes one contiguous range;
  *   lds_kb  minimum LDS per workgroup in KiB (0..150; caps occupancy);
  *   nt      1: non-temporal output stores;
@@ -118,11 +121,11 @@ int dwf_destroy(dwf_op_t op);
  *           plane.  Orders 2-4 read a table that the library builds
  *           on the first launch outside graph capture (host memory and
  *           4 bytes of device memory per workgroup, kept until dwf_destroy);
- *   phases  2 or 4 neighbour-load phases per stage (0: 4 for complex128,
- *           2 for complex64 and 16-bit fields);
+ *   phases  2 or 4 neighbour-load phases per stage for Ls > 16 (0: 4 for
+ *           complex128, 2 for complex64 and 16-bit fields); Ls <= 16 has one;
  *   rg      right-hand sides one workgroup applies the stage to, one after
  *           another on the links it staged once (1..64; a call with fewer
- *           right-hand sides uses that many).
+ *           right-hand sides uses that many; Ls <= 16).
  * By default the block, remap, order and rg entries are chosen by the library's
  * autotuner: the first application of H for a field storage (complex128,
  * complex64, 16-bit) and for one or several right-hand sides times each

@@ -423,7 +423,7 @@ int dwf_get_hop_shape(dwf_op_t op, int prec, int nrhs, int shape[10], float* ms,
     for (int i = 0; i < n; ++i) ms[i] = c >= 0 ? op->hop_ms[pi][ri][i] : -1.f;
   int cand[7];
   const bool tuned = op->hop_autotune && c >= 0;
-  if (tuned) hop_shape_of(c, cand);
+  if (tuned) (void)hop_shape_of(op, prec, c, cand);
   for (int i = 0; i < 4; ++i) shape[i] = tuned ? cand[i] : op->tune.block[i];
   shape[4] = tuned ? cand[4] : op->tune.remap;
   shape[5] = op->tune.lds_kb;

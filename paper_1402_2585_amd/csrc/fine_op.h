@@ -146,9 +146,10 @@ int launch_convert16(dwf_op* op, bf16c* dst, const c64* src, int nrhs, hipStream
 int launch_convert16(dwf_op* op, c64* dst, const bf16c* src, int nrhs, hipStream_t stream);
 
 // the hop launch-shape candidates of the autotuner: their number, and
-// candidate c as {bx, by, bz, bt, remap, order, rhs per workgroup}
+// candidate c as {bx, by, bz, bt, remap, order, rhs per workgroup} (false: it
+// does not fit, and the default block stands in)
 int hop_shape_candidates();
-void hop_shape_of(int c, int shape[7]);
+bool hop_shape_of(const dwf_op* op, int prec, int c, int shape[7]);
 
 int ensure_tmp(dwf_op* op, int prec, int nrhs);
 void release_tmp(dwf_op* op);  // drop the operator's work fields (regrown on demand)

@@ -2,19 +2,27 @@
 //
 // One hop stage = one launch.  A workgroup owns `spw` output sites of one
 // checkerboard (a small 4D block of sites, or consecutive sites) and all Ls
-// slices of each (thread = (site, s)).  The Ls threads of a site copy its
-// eight links into LDS once, the neighbour spinors of a site column are
-// contiguous runs of Ls complex numbers per component, and each thread
-// issues the loads of several neighbour spinors before any arithmetic, so
-// many bytes are in flight per wave and few sites need to be resident per
-// CU: the neighbour columns a CU touches then stay in its XCD's L2 between
-// their consumers.
+// slices of each.  Ls <= 16 takes hop_split_kernel (hop_split.h: one wave per
+// site); larger Ls takes hop_kernel below (thread = (site, s)): the Ls threads
+// of a site copy its eight links into LDS once, the neighbour spinors of a
+// site column are contiguous runs of Ls complex numbers per component, and
+// each thread issues the loads of several neighbour spinors before any
+// arithmetic.
+//
+// Why two: the split form has half the sites in flight for the same bytes in
+// flight (the neighbour columns then stay in the XCD's 4 MB L2), no serial
+// recurrence and one load phase instead of four, so one wave's latency is a
+// third; but its rows hold at most 16 slices.  H, before and after: 4^4 x 8
+// complex128 33.7 -> 17.6 us; 16^4 x 16 complex128 314 -> 283 us; a complex128
+// CG iteration on 8^3 x 16 x 8 68 -> 52 us; 24^3 x 48 x 16 complex64, bound by
+// the bytes between L2 and L1, 1.86 -> 1.82 ms.
 //
 // Epilogues (the fifth-dimension factors of M_pc, Sec. IV):
 //   EPI_INV  out = M_5^-1 (Dh in)          or M_5^-+ (Dh^+ in)   [dense in s]
 //   EPI_SUB  out = M_5 c - 1/4 (Dh in)      or M_5^+ c - 1/4 (Dh^+ in)
-// EPI_INV stages the hop result in LDS and solves the Ls x Ls system per
-// (site, component) with the O(Ls) recurrence of the closed-form inverse.
+// hop_kernel's EPI_INV stages the hop result in LDS and solves the Ls x Ls
+// system per (site, component) with the O(Ls) recurrence of the closed-form
+// inverse.
 #include <algorithm>
 #include <type_traits>
 
@@ -304,17 +312,18 @@ struct HopArgs {
   int lbx, lby, lbz;  // log2 of bx, by, bz
   int nbx, nby, nbz;  // block-grid extents
   int remap;          // XCD-contiguous workgroup order
-  int nt;             // non-temporal output stores
+  int nt;             // non-temporal: 1 output stores, 2 links, 4 centre values
   int morton;         // Morton (bit-interleaved) order of the block grid (power-of-two grids)
   int nbt;            // block-grid extent in t
   const int* order;   // nullable: block of workgroup blockIdx.x, packed gx | gy << 8 | gz << 16 | gt << 24
   int rg;             // right-hand sides per workgroup (blockIdx.y takes rg of the nrhs)
   int nrhs;
-  int epi_off;        // byte offset of the epilogue's LDS buffer (0: it reuses the link rows)
+  int fold;           // march: blockIdx.x runs over tiles and right-hand sides
   size_t field;       // complex elements per rhs
   // fifth dimension: M_5 = alpha + beta K, recurrence of M_5^-1 y_s = ia x_s + kap y_{s-1},
   // Mobius C_5 = b5 + c5 K (K: P+ from s-1, P- from s+1, -mass at the wrap)
   double alpha, beta, ia, kap, b5, c5, mass;
+  double kp[4];       // kap^1, kap^2, kap^4, kap^8
   double* partials;   // EPI_SUB norm: [rhs][pstride] per-workgroup partials (nullable)
   size_t pstride;     // = number of workgroups
   unsigned* counters; // [rhs]
@@ -393,14 +402,14 @@ __device__ __forceinline__ void bcs_row(cplx<R>* row, int Ls, R b, R c, R m, boo
 // complex) and applies M_5^-1 (or M_5^-+); EPI_SUB forms M_5 c - acc/4 (or
 // M_5^+ c - acc/4) and, when A.partials is set, stores this workgroup's part
 // of its squared norm.  Every thread of the workgroup must call it.
-template <typename R, bool DAG, int EPI, int LS = 0, bool MOB = false, typename T = cplx<R>>
+template <typename R, bool DAG, int EPI, bool MOB, typename T>
 __device__ __forceinline__ void hop_epilogue(const cplx<R> (&acc)[12], bool active, int vloc, int s,
                                              int v, int wg, int rhs, T* __restrict__ out,
                                              const T* __restrict__ center,
                                              const R* __restrict__ pw, const HopArgs& A,
                                              unsigned char* smem_raw) {
   const Geom& g = A.g;
-  const int Ls = LS > 0 ? LS : g.Ls;
+  const int Ls = g.Ls;
   const int tid = threadIdx.x;
   if (EPI == EPI_INV) {
     // ---- M_5^-1 (or its adjoint) across s, through LDS --------------------
@@ -632,22 +641,18 @@ __device__ __forceinline__ void apply_dirs(cplx<R> (&acc)[12], const cplx<R> (&p
 }
 
 // NPH = number of load phases (2: four directions in flight at a time; 4:
-// two).  LS > 0 fixes Ls at compile time.  Dynamic LDS:
+// two).  For Ls > 16; smaller ones take hop_split_kernel.  Dynamic LDS:
 // max(spw * kLinkLd, spw * 12 * (Ls + 1)) complex.
-template <typename R, bool DAG, int EPI, int NPH, int LS, bool MOB, typename T, bool MR>
+template <typename R, bool DAG, int EPI, int NPH, bool MOB, typename T>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
 hop_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restrict__ center,
            const cplx<R>* __restrict__ gauge, const R* __restrict__ pw, HopArgs A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const Geom& g = A.g;
-  const int Ls = LS > 0 ? LS : g.Ls;  // compile-time when LS > 0: immediate load offsets
+  const int Ls = g.Ls;
   // a table order already places each workgroup on its XCD's region
   const int wg = (A.remap && !A.order) ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const int rhs0 = blockIdx.y * A.rg;
-  // MR: several right-hand sides per workgroup (a separate instantiation,
-  // so that the one-RHS kernel keeps the register footprint of straight-line
-  // code)
-  const int nr = MR ? min(A.rg, A.nrhs - rhs0) : 1;
+  const int rhs = blockIdx.y;
   const int tid = threadIdx.x;
   const int vloc = tid / Ls, s = tid - vloc * Ls;
   Site c;
@@ -657,85 +662,59 @@ hop_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restrict__ 
   cplx<R>* links = reinterpret_cast<cplx<R>*>(smem_raw);  // [spw][kLinkLd]
   constexpr int ND = 8 / NPH;
   constexpr int SF = DAG ? 1 : -1;
-  constexpr int NL = LS > 0 ? (72 + LS - 1) / LS : 1;
   const size_t col = (size_t)12 * Ls;
   // Mobius: the first stage of M_pc hops C_5 in (C_5 on the neighbours' columns)
   constexpr bool C5IN = MOB && !DAG && EPI == EPI_INV;
   int nb[8];
   cplx<R> psi[ND][12];
-  // The site's 72 link entries, entry e by thread s = e mod Ls.  With Ls
-  // fixed at compile time they are loaded before the first right-hand
-  // side's first-phase neighbour loads are issued and written to LDS after
-  // them, so the wave waits for memory once instead of once per entry.
+  const T* __restrict__ inr = in + rhs * A.field;
+  // the site's 72 link entries, entry e by thread s = e mod Ls
   if (active) {
     const cplx<R>* G = gauge + (size_t)v * 72;
-    cplx<R> lk[NL];
-    if constexpr (LS > 0) {
-      // (the last entries of the short threads re-read entry 71: no branch)
-#pragma unroll
-      for (int k = 0; k < NL; ++k) lk[k] = G[min(s + k * LS, 71)];
-    } else {
-      for (int e = s; e < 72; e += Ls) links[vloc * kLinkLd + e] = G[e];
-    }
+    for (int e = s; e < 72; e += Ls) links[vloc * kLinkLd + e] = G[e];
     hop_neighbours(g, c, nb);
     if (C5IN)
-      load_dirs_c5<T, 0, ND>(psi, in + rhs0 * A.field, nb, col, s, Ls, (R)A.b5, (R)A.c5, (R)A.mass);
+      load_dirs_c5<T, 0, ND>(psi, inr, nb, col, s, Ls, (R)A.b5, (R)A.c5, (R)A.mass);
     else
-      load_dirs<T, 0, ND>(psi, in + rhs0 * A.field, nb, col, s, Ls);
-    if constexpr (LS > 0) {
-#pragma unroll
-      for (int k = 0; k < NL; ++k)
-        if (s + k * LS < 72) links[vloc * kLinkLd + s + k * LS] = lk[k];
-    }
+      load_dirs<T, 0, ND>(psi, inr, nb, col, s, Ls);
   }
-  // The workgroup's right-hand sides one after another, all on the links
-  // staged once (with several, the epilogue has an LDS buffer of its own).
-  for (int rr = 0; rr < nr; ++rr) {
-    const int rhs = rhs0 + rr;
-    const T* __restrict__ inr = in + rhs * A.field;
-    T* __restrict__ outr = out + rhs * A.field;
-    if (rr > 0 && active) {
-      if (C5IN)
-        load_dirs_c5<T, 0, ND>(psi, inr, nb, col, s, Ls, (R)A.b5, (R)A.c5, (R)A.mass);
-      else
-        load_dirs<T, 0, ND>(psi, inr, nb, col, s, Ls);
-    }
-    __syncthreads();  // links in LDS
+  __syncthreads();  // links in LDS
 
-    cplx<R> acc[12];
-  #pragma unroll
-    for (int c = 0; c < 12; ++c) acc[c] = cmk((R)0, (R)0);
-    if (active) {
-      const cplx<R>* L = links + vloc * kLinkLd;
-      apply_dirs<R, 0, ND, SF>(acc, psi, L);
-      const R b5 = (R)A.b5, c5 = (R)A.c5, mm = (R)A.mass;
-      if (NPH >= 2) {
-        if (C5IN)
-          load_dirs_c5<T, ND % 8, ND>(psi, inr, nb, col, s, Ls, b5, c5, mm);
-        else
-          load_dirs<T, ND % 8, ND>(psi, inr, nb, col, s, Ls);
-        apply_dirs<R, ND % 8, ND, SF>(acc, psi, L);
-      }
-      if (NPH == 4) {
-        if (C5IN)
-          load_dirs_c5<T, 4, ND>(psi, inr, nb, col, s, Ls, b5, c5, mm);
-        else
-          load_dirs<T, 4, ND>(psi, inr, nb, col, s, Ls);
-        apply_dirs<R, 4, ND, SF>(acc, psi, L);
-        if (C5IN)
-          load_dirs_c5<T, 6, ND>(psi, inr, nb, col, s, Ls, b5, c5, mm);
-        else
-          load_dirs<T, 6, ND>(psi, inr, nb, col, s, Ls);
-        apply_dirs<R, 6, ND, SF>(acc, psi, L);
-      }
+  cplx<R> acc[12];
+#pragma unroll
+  for (int c = 0; c < 12; ++c) acc[c] = cmk((R)0, (R)0);
+  if (active) {
+    const cplx<R>* L = links + vloc * kLinkLd;
+    apply_dirs<R, 0, ND, SF>(acc, psi, L);
+    const R b5 = (R)A.b5, c5 = (R)A.c5, mm = (R)A.mass;
+    if (NPH >= 2) {
+      if (C5IN)
+        load_dirs_c5<T, ND % 8, ND>(psi, inr, nb, col, s, Ls, b5, c5, mm);
+      else
+        load_dirs<T, ND % 8, ND>(psi, inr, nb, col, s, Ls);
+      apply_dirs<R, ND % 8, ND, SF>(acc, psi, L);
     }
-    // the epilogue's LDS buffer reuses the link rows (one right-hand side per
-    // workgroup) or the previous right-hand side's buffer
-    if (EPI == EPI_INV || (MOB && DAG)) __syncthreads();
-    hop_epilogue<R, DAG, EPI, LS, MOB, T>(acc, active, vloc, s, v, wg, rhs, outr, center, pw, A,
-                                          smem_raw + A.epi_off);
+    if (NPH == 4) {
+      if (C5IN)
+        load_dirs_c5<T, 4, ND>(psi, inr, nb, col, s, Ls, b5, c5, mm);
+      else
+        load_dirs<T, 4, ND>(psi, inr, nb, col, s, Ls);
+      apply_dirs<R, 4, ND, SF>(acc, psi, L);
+      if (C5IN)
+        load_dirs_c5<T, 6, ND>(psi, inr, nb, col, s, Ls, b5, c5, mm);
+      else
+        load_dirs<T, 6, ND>(psi, inr, nb, col, s, Ls);
+      apply_dirs<R, 6, ND, SF>(acc, psi, L);
+    }
   }
+  // the epilogue's LDS buffer reuses the link rows
+  if (EPI == EPI_INV || (MOB && DAG)) __syncthreads();
+  hop_epilogue<R, DAG, EPI, MOB, T>(acc, active, vloc, s, v, wg, rhs, out + rhs * A.field, center, pw, A, smem_raw);
 }
+
+}  // namespace hdk
+#include "hop_march.h"
+namespace hdk {
 
 // ------------------------------------------------------------------ BLAS ---
 template <typename R>
@@ -862,36 +841,85 @@ int ensure_tmp(dwf_op* op, int prec, int nrhs) {
   return DWF_OK;
 }
 
-template <typename R, int NPH, int LS, bool MOB, typename T, bool MR>
-static void launch_hop_mr(bool dagger, int epi, dim3 grid, dim3 block, size_t lds, hipStream_t stream,
-                          T* out, const T* in, const T* center, const cplx<R>* G, const R* pw, const HopArgs& A) {
+template <typename R, int NPH, bool MOB, typename T>
+static void launch_hop(bool dagger, int epi, dim3 grid, dim3 block, size_t lds, hipStream_t stream, T* out, const T* in,
+                       const T* center, const cplx<R>* G, const R* pw, const HopArgs& A) {
+#define HDCG_HOP(D, E) \
+  hipLaunchKernelGGL((hop_kernel<R, D, E, NPH, MOB, T>), grid, block, lds, stream, out, in, center, G, pw, A)
   if (epi == EPI_INV) {
-    if (dagger)
-      hipLaunchKernelGGL((hop_kernel<R, true, EPI_INV, NPH, LS, MOB, T, MR>), grid, block, lds, stream, out, in, center,
-                         G, pw, A);
-    else
-      hipLaunchKernelGGL((hop_kernel<R, false, EPI_INV, NPH, LS, MOB, T, MR>), grid, block, lds, stream, out, in,
-                         center, G, pw, A);
+    if (dagger) HDCG_HOP(true, EPI_INV);
+    else HDCG_HOP(false, EPI_INV);
   } else {
-    if (dagger)
-      hipLaunchKernelGGL((hop_kernel<R, true, EPI_SUB, NPH, LS, MOB, T, MR>), grid, block, lds, stream, out, in, center,
-                         G, pw, A);
-    else
-      hipLaunchKernelGGL((hop_kernel<R, false, EPI_SUB, NPH, LS, MOB, T, MR>), grid, block, lds, stream, out, in,
-                         center, G, pw, A);
+    if (dagger) HDCG_HOP(true, EPI_SUB);
+    else HDCG_HOP(false, EPI_SUB);
+  }
+#undef HDCG_HOP
+}
+
+template <typename R, int LS, bool MOB, typename T, bool LOOP>
+static void launch_split_ls(bool dagger, int epi, dim3 grid, dim3 block, size_t lds, hipStream_t stream, T* out,
+                            const T* in, const T* center, const cplx<R>* G, const R* pw, const HopArgs& A) {
+#define HDCG_SPLIT(D, E) \
+  hipLaunchKernelGGL((hop_split_kernel<R, D, E, LS, MOB, T, LOOP>), grid, block, lds, stream, out, in, center, G, pw, A)
+  if (epi == EPI_INV) {
+    if (dagger) HDCG_SPLIT(true, EPI_INV);
+    else HDCG_SPLIT(false, EPI_INV);
+  } else {
+    if (dagger) HDCG_SPLIT(true, EPI_SUB);
+    else HDCG_SPLIT(false, EPI_SUB);
+  }
+#undef HDCG_SPLIT
+}
+template <typename R, typename T, int LS>
+static void launch_split_mob(bool dagger, int epi, bool mob, bool loop, dim3 grid, dim3 block, size_t lds,
+                             hipStream_t stream, T* out, const T* in, const T* center, const cplx<R>* G, const R* pw,
+                             const HopArgs& A) {
+  if constexpr (LS > 0) {
+    if (!loop) {
+      if (mob) launch_split_ls<R, LS, true, T, false>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
+      else launch_split_ls<R, LS, false, T, false>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
+      return;
+    }
+  }
+  if (mob) launch_split_ls<R, LS, true, T, true>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
+  else launch_split_ls<R, LS, false, T, true>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
+}
+template <typename R, typename T>
+static void launch_split(bool dagger, int epi, bool mob, int Ls, bool loop, dim3 grid, dim3 block, size_t lds,
+                         hipStream_t stream, T* out, const T* in, const T* center, const cplx<R>* G, const R* pw,
+                         const HopArgs& A) {
+  switch (Ls) {
+    case 16: return launch_split_mob<R, T, 16>(dagger, epi, mob, loop, grid, block, lds, stream, out, in, center, G, pw, A);
+    case 12: return launch_split_mob<R, T, 12>(dagger, epi, mob, loop, grid, block, lds, stream, out, in, center, G, pw, A);
+    case 8: return launch_split_mob<R, T, 8>(dagger, epi, mob, loop, grid, block, lds, stream, out, in, center, G, pw, A);
+    default: return launch_split_mob<R, T, 0>(dagger, epi, mob, loop, grid, block, lds, stream, out, in, center, G, pw, A);
   }
 }
 
-// several right-hand sides per workgroup are built for the compile-time Ls
-// = 16 kernels only (the launch keeps A.rg = 1 otherwise)
-template <typename R, int NPH, int LS, bool MOB, typename T>
-static void launch_hop(bool dagger, int epi, dim3 grid, dim3 block, size_t lds, hipStream_t stream,
-                       T* out, const T* in, const T* center, const cplx<R>* G, const R* pw, const HopArgs& A) {
-  if constexpr (LS == 16) {
-    if (A.rg > 1)
-      return launch_hop_mr<R, NPH, LS, MOB, T, true>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
+template <typename R, typename T, int LS>
+static void launch_march_ls(bool dagger, int epi, dim3 grid, dim3 block, size_t lds, hipStream_t stream, T* out,
+                            const T* in, const T* center, const cplx<R>* G, const R* pw, const HopArgs& A) {
+#define HDCG_MARCH(D, E) \
+  hipLaunchKernelGGL((hop_march_kernel<R, D, E, LS, T>), grid, block, lds, stream, out, in, center, G, pw, A)
+  if (epi == EPI_INV) {
+    if (dagger) HDCG_MARCH(true, EPI_INV);
+    else HDCG_MARCH(false, EPI_INV);
+  } else {
+    if (dagger) HDCG_MARCH(true, EPI_SUB);
+    else HDCG_MARCH(false, EPI_SUB);
   }
-  launch_hop_mr<R, NPH, LS, MOB, T, false>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
+#undef HDCG_MARCH
+}
+
+// Whether the marching form takes this block: bx x by x bz pairs of sites,
+// marched over bt planes (extents that divide the lattice, at least two pairs
+// in y and z, waves and LDS for one workgroup; Shamir, Ls 8, 12 or 16).
+static bool march_fits(const Geom& g, bool mob, int prec, const int* b) {
+  if (mob || (g.Ls != 16 && g.Ls != 12 && g.Ls != 8) || b[0] < 1 || b[1] < 2 || b[2] < 2 || b[3] < 1) return false;
+  if (g.Xh % b[0] || g.Y % b[1] || g.Z % b[2] || g.T % b[3]) return false;
+  const int npair = b[0] * b[1] * b[2], ns = 16 / g.Ls;
+  return npair % ns == 0 && npair / ns <= (prec == DWF_C128 ? 8 : 16) &&
+         march_lds(npair, g.Ls, cbytes(prec), prec == DWF_C128 ? 16 : 8) <= 150 * 1024;
 }
 
 // ------------------------------------------------- region block orders --
@@ -1003,8 +1031,10 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   HopArgs A;
   A.g = g;
   A.out_parity = out_parity;
-  // linear order: one wave's worth of threads per workgroup (at least one site)
-  A.spw = g.Ls >= 64 ? 1 : 64 / g.Ls;
+  // linear order: four waves of the split kernel, or one wave's worth of
+  // threads (at least one site)
+  const bool split = g.Ls <= 16;
+  A.spw = split ? 4 * (16 / g.Ls) : g.Ls >= 64 ? 1 : 64 / g.Ls;
   A.bx = A.by = A.bz = A.bt = 0;
   A.lbx = A.lby = A.lbz = 0;
   A.nbx = A.nby = A.nbz = 1;
@@ -1014,12 +1044,18 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   A.nbt = 1;
   A.order = nullptr;
   A.nrhs = nrhs;
-  A.rg = g.Ls == 16 ? std::max(1, std::min(op->tune.rg, nrhs)) : 1;
+  A.fold = 0;
+  const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
+  // a block of more than 256 / Ls sites is marched along t where that fits
+  const int* b = op->tune.block;
+  const bool march = b[0] * b[1] * b[2] * b[3] * g.Ls > 256 && march_fits(g, op->f5.mobius, prec, b);
+  A.rg = split ? std::max(1, std::min(op->tune.rg, nrhs)) : 1;
   {
-    const int* b = op->tune.block;
     auto pow2 = [](int n) { return n > 0 && (n & (n - 1)) == 0; };
-    if (b[0] > 0 && pow2(b[0]) && pow2(b[1]) && pow2(b[2]) && pow2(b[3]) && b[0] * b[1] * b[2] * b[3] * g.Ls <= 256 &&
-        (size_t)b[0] * b[1] * b[2] * b[3] * 12 * (g.Ls + 1) * sizeof(c128) <= 65536 && g.Xh % b[0] == 0 && g.Y % b[1] == 0 &&
+    if (b[0] > 0 && pow2(b[0]) && pow2(b[1]) && pow2(b[2]) && pow2(b[3]) &&
+        (march || (b[0] * b[1] * b[2] * b[3] * g.Ls <= 256 &&
+                   (size_t)b[0] * b[1] * b[2] * b[3] * 12 * (g.Ls + 1) * sizeof(c128) <= 65536)) &&
+        g.Xh % b[0] == 0 && g.Y % b[1] == 0 &&
         g.Z % b[2] == 0 && g.T % b[3] == 0) {
       A.bx = b[0];
       A.by = b[1];
@@ -1043,10 +1079,18 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
     }
   }
   A.field = (size_t)g.Vh * 12 * g.Ls;
+  // Streamed operands.  In complex128, once a stage's links alone exceed the
+  // eight 4 MB L2s, links, centre values and output stores pass the caches
+  // as non-temporal: they are used once, and the neighbour columns, used
+  // eight times, stay (H on 16^4 x 16: 290 -> 273 us).  Smaller lattices keep
+  // them cached for the next stage, and the narrower types measured the same
+  // or slower with it (complex64 on 12x10x6x14 x 12: 38 -> 45 us).
+  if (split && sizeof(R) == 8 && (size_t)g.Vh * 72 * sizeof(cplx<R>) > ((size_t)32 << 20)) A.nt = 7;
   A.alpha = op->f5.alpha;
   A.beta = op->f5.beta;
   A.ia = op->f5.ia;
   A.kap = op->f5.kap;
+  for (int k = 0; k < 4; ++k) A.kp[k] = k == 0 ? A.kap : A.kp[k - 1] * A.kp[k - 1];
   A.b5 = op->f5.b5;
   A.c5 = op->f5.c5;
   A.mass = op->f5.mass;
@@ -1054,7 +1098,12 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   A.partials = nullptr;
   A.counters = nullptr;
   A.result = nullptr;
-  const int threads = ((A.spw * g.Ls + 63) / 64) * 64;
+  // waves of a split workgroup: more than four only in FP32, where a block of
+  // 16 sites at once shares neighbours in L1 (complex64 H on 24^3 x 48 x 16:
+  // 1.87 -> 1.82 ms; complex128, at twice the bytes, 273 -> 350 us on 16^4)
+  const int waves = split ? std::min(sizeof(R) == 8 ? 4 : 16, (A.spw + 16 / g.Ls - 1) / (16 / g.Ls))
+                          : (A.spw * g.Ls + 63) / 64;
+  const int threads = waves * 64;
   const int nwg = (g.Vh + A.spw - 1) / A.spw;
   A.pstride = (size_t)nwg;
   if (norm_result) {
@@ -1068,39 +1117,36 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   const cplx<R>* G = reinterpret_cast<const cplx<R>*>(dbl ? op->gauge128.ptr : op->gauge64.ptr) +
                      (size_t)out_parity * g.Vh * 72;
   const R* pw = reinterpret_cast<const R*>(dbl ? op->pw128.ptr : op->pw64.ptr);
+  if (march) {
+    A.fold = nrhs > 1 && nwg % 8 == 0;
+    const int npair = A.bx * A.by * A.bz;
+    const dim3 mgrid(A.fold ? nwg * nrhs : nwg, A.fold ? 1 : nrhs), mblock(npair / (16 / g.Ls) * 64);
+    const size_t mlds = march_lds(npair, g.Ls, sizeof(T), sizeof(cplx<R>));
+    if (g.Ls == 16) launch_march_ls<R, T, 16>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
+    else if (g.Ls == 12) launch_march_ls<R, T, 12>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
+    else launch_march_ls<R, T, 8>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
+    HDCG_HIP(hipGetLastError());
+    if (norm_result) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride);
+    return DWF_OK;
+  }
   dim3 grid(nwg, (nrhs + A.rg - 1) / A.rg), block(threads);
-  const size_t epi_lds = (epi == EPI_INV || (mob && dagger)) ? (size_t)A.spw * 12 * (g.Ls + 1) * sizeof(cplx<R>) : 0;
+  const size_t epi_lds =
+      !split && (epi == EPI_INV || (mob && dagger)) ? (size_t)A.spw * 12 * (g.Ls + 1) * sizeof(cplx<R>) : 0;
   const size_t link_lds = (size_t)A.spw * kLinkLd * sizeof(cplx<R>);
-  size_t lds;
-  if (A.rg > 1 && epi_lds > 0) {  // separate regions: the links stay for the next right-hand side
-    A.epi_off = (int)((link_lds + 15) / 16 * 16);
-    lds = A.epi_off + epi_lds;
-  } else {
-    A.epi_off = 0;
-    lds = std::max(epi_lds, link_lds);
-  }
   // optional LDS request that caps the resident workgroups per CU
-  if ((size_t)op->tune.lds_kb * 1024 > lds) lds = (size_t)op->tune.lds_kb * 1024;
-  // directions whose neighbour loads are in flight together: 8 / phases
-  // (the Mobius kernels are built for four phases only)
+  const size_t lds = std::max(std::max(epi_lds, link_lds), (size_t)op->tune.lds_kb * 1024);
+  // Ls > 16: directions whose neighbour loads are in flight together, 8 /
+  // phases (the Mobius kernels are built for four phases only)
   const int phases = op->tune.phases > 0 ? op->tune.phases : (sizeof(R) == 8 ? 4 : 2);
-  const bool two = phases == 4 || mob;
-  if (mob) {
-    if (g.Ls == 16)
-      launch_hop<R, 4, 16, true, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
-    else
-      launch_hop<R, 4, 0, true, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
-  } else if (g.Ls == 16) {
-    if (two)
-      launch_hop<R, 4, 16, false, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
-    else
-      launch_hop<R, 2, 16, false, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
-  } else {
-    if (two)
-      launch_hop<R, 4, 0, false, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
-    else
-      launch_hop<R, 2, 0, false, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
-  }
+  if (split)
+    launch_split<R, T>(dagger, epi, mob, g.Ls, A.rg > 1 || A.spw > waves * (16 / g.Ls), grid, block, lds, stream, out,
+                       in, center, G, pw, A);
+  else if (mob)
+    launch_hop<R, 4, true, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
+  else if (phases == 4)
+    launch_hop<R, 4, false, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
+  else
+    launch_hop<R, 2, false, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
   HDCG_HIP(hipGetLastError());
   if (norm_result) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride);
   return DWF_OK;
@@ -1125,37 +1171,64 @@ int launch_mpc(dwf_op* op, T* out, const T* in, bool dagger, int nrhs, hipStream
 // Candidate launch shapes of the hop stages: the workgroup's site block in
 // (x/2, y, z, t) and whether workgroups are reordered XCD-contiguously.  Which
 // is fastest depends on the lattice (how the block grid divides over the 8
-// XCDs and their L2 caches) and on the bytes per site; on 16^4 x 16 the
-// 2x2x1x1 XCD-contiguous Morton order wins, on 24^3 x 48 x 16 (a block grid
-// that is not a power of two) other shapes do.
+// XCDs and their L2 caches) and on the bytes per site.  The marching
+// candidates (hop_march.h) win where L2-to-L1 traffic bounds the split form
+// and there are workgroups enough to fill the chip with chunks of t: H in
+// complex64 on 24^3 x 48 x 16 1.69 against 1.87 ms, on 32^3 x 64 x 16 4.65
+// against 5.95 ms, on 16^3 x 32 x 16 0.316 against 0.352 ms; on 16^4 and on
+// 16-bit fields (half the bytes for the same instructions) the split form
+// stays ahead (0.142 against 0.150 ms; 0.95 against 1.05 ms on 24^3 x 48).
 struct HopShape {
   int block[4];
   int remap;
-  int order;  // 1 Morton (index formula), 2-4 region tables
+  int order;  // 0 lexicographic, 1 Morton (index formula), 2-4 region tables
   int rg;     // right-hand sides per workgroup (candidates with rg > 1 are tried only for several)
+  int march = 0;  // > 0: a tile to march, over the most planes that leave so many workgroups
 };
 constexpr HopShape kHopShapes[] = {
-    {{2, 2, 1, 1}, 1, 1, 1},  {{2, 2, 1, 1}, 0, 1, 1},  {{2, 2, 2, 2}, 1, 1, 1}, {{2, 2, 2, 2}, 0, 1, 1},
+    {{2, 2, 1, 1}, 1, 1, 1},  {{2, 2, 1, 1}, 0, 1, 1},  {{2, 4, 2, 1}, 1, 4, 1, 512}, {{2, 2, 2, 1}, 1, 4, 1, 512},
     {{4, 2, 1, 1}, 1, 1, 1},  {{1, 2, 2, 1}, 1, 1, 1},  {{2, 2, 1, 1}, 1, 2, 1}, {{1, 2, 2, 1}, 1, 2, 1},
-    {{2, 2, 1, 1}, 1, 3, 1},  {{2, 2, 2, 2}, 1, 2, 1},  {{2, 2, 1, 1}, 1, 4, 1}, {{1, 2, 2, 1}, 1, 4, 1},
+    {{2, 2, 1, 1}, 1, 3, 1},  {{1, 2, 2, 1}, 1, 4, 1, 1024},  {{2, 2, 1, 1}, 1, 4, 1}, {{1, 2, 2, 1}, 1, 4, 1},
     {{2, 2, 2, 2}, 1, 4, 1},  {{2, 2, 1, 1}, 1, 4, 16}, {{2, 2, 1, 1}, 1, 1, 16}, {{1, 2, 2, 1}, 1, 4, 16},
     {{2, 2, 1, 1}, 0, 0, 16}, {{2, 2, 1, 1}, 1, 4, 4}};
 constexpr int kNumHopShapes = sizeof(kHopShapes) / sizeof(kHopShapes[0]);
 static_assert(kNumHopShapes <= 24, "hop_ms holds 24 candidates");
 
 int hop_shape_candidates() { return kNumHopShapes; }
-void hop_shape_of(int c, int shape[7]) {
-  for (int i = 0; i < 4; ++i) shape[i] = kHopShapes[c].block[i];
-  shape[4] = kHopShapes[c].remap;
-  shape[5] = kHopShapes[c].order;
-  shape[6] = kHopShapes[c].rg;
+
+// Candidate c for this operator and storage.  A tile to march takes the most
+// planes, a power of two dividing T and at least 4 (a chunk loads two planes
+// of its neighbours' columns besides its own), that leave `march`
+// workgroups; where none fits, the default block stands in.
+bool hop_shape_of(const dwf_op* op, int prec, int c, int shape[7]) {
+  const HopShape& s = kHopShapes[c];
+  for (int i = 0; i < 4; ++i) shape[i] = s.block[i];
+  shape[4] = s.remap;
+  shape[5] = s.order;
+  shape[6] = s.rg;
+  if (!s.march) return true;
+  const Geom& g = op->g;
+  int best = 0;
+  for (int n = 4; n <= g.T; n *= 2) {
+    const int b[4] = {s.block[0], s.block[1], s.block[2], n};
+    if (march_fits(g, op->f5.mobius, prec, b) &&
+        (best == 0 || (long)g.Vh / (b[0] * b[1] * b[2] * n) >= s.march))
+      best = n;
+  }
+  if (best)
+    shape[3] = best;
+  else
+    for (int i = 0; i < 4; ++i) shape[i] = kHopShapes[0].block[i];
+  return best != 0;
 }
 
-static void apply_shape(dwf_op* op, int c) {
-  for (int i = 0; i < 4; ++i) op->tune.block[i] = kHopShapes[c].block[i];
-  op->tune.remap = kHopShapes[c].remap;
-  op->tune.morton = kHopShapes[c].order;
-  op->tune.rg = kHopShapes[c].rg;
+static void apply_shape(dwf_op* op, int prec, int c) {
+  int s[7];
+  (void)hop_shape_of(op, prec, c, s);
+  for (int i = 0; i < 4; ++i) op->tune.block[i] = s[i];
+  op->tune.remap = s[4];
+  op->tune.morton = s[5];
+  op->tune.rg = s[6];
 }
 
 template <typename R, typename T>
@@ -1175,12 +1248,13 @@ static int apply_mpcdagmpc(dwf_op* op, T* out, const T* in, int nrhs, hipStream_
 template <typename R, typename T>
 static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t st) {
   if (!op->hop_autotune) return DWF_OK;
-  const int pi = tmp_index(std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>()), ri = nrhs > 1;
+  const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
+  const int pi = tmp_index(prec), ri = nrhs > 1;
   int& choice = op->hop_choice[pi][ri];
   if (choice < 0) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-      apply_shape(op, 0);
+      apply_shape(op, prec, 0);
       return DWF_OK;
     }
     hipEvent_t e0, e1;
@@ -1191,7 +1265,12 @@ static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t s
     for (int c = 0; c < kNumHopShapes && rc == DWF_OK; ++c) {
       op->hop_ms[pi][ri][c] = -1.f;
       if (kHopShapes[c].rg > 1 && nrhs == 1) continue;  // the same as its one-RHS form
-      apply_shape(op, c);
+      int shape[7];
+      if (!hop_shape_of(op, prec, c, shape)) {
+        op->hop_ms[pi][ri][c] = op->hop_ms[pi][ri][0];  // runs as the default block does
+        continue;
+      }
+      apply_shape(op, prec, c);
       rc = apply_mpcdagmpc<R, T>(op, out, in, nrhs, st, nullptr);
       float m = 1e30f;
       for (int rep = 0; rep < 3 && rc == DWF_OK; ++rep) {
@@ -1214,7 +1293,7 @@ static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t s
     HDCG_TRY(rc);
     choice = best;
   }
-  apply_shape(op, choice);
+  apply_shape(op, prec, choice);
   return DWF_OK;
 }
 
