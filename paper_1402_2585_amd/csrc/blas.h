@@ -11,7 +11,7 @@ namespace hdk {
 
 struct Red {
   double* partials;   // [64][kMaxPartials]
-  unsigned* counters; // [64]
+  unsigned* counters; // kTicketWords, zero between launches
 };
 
 // res[rhs] = |x_rhs|^2

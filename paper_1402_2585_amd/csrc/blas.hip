@@ -1,16 +1,27 @@
 // BLAS-1 kernels with device-resident coefficients and FP64 reductions.
 #include "blas.h"
 
+#include <algorithm>
+
 namespace hdk {
 
 namespace {
 
 constexpr int kT = 256;
+constexpr int kMaxGrid = 1024;  // workgroups of a launch over all right-hand sides
 
-inline int nblocks(size_t n) {
+// Workgroups per right-hand side: at least eight elements a thread, and at
+// most four workgroups per CU over all right-hand sides.  These kernels are
+// bound by HBM (or the Infinity Cache), which 1024 workgroups with several
+// loads in flight a thread saturate; with 1024 per right-hand side (up to
+// 16384) the tickets of the reductions cost more than the data: on 4 x
+// 12^3 x 24 x 8 16-bit fields, 3888 tickets of about 10 ns each kept k_xpay
+// at 54.6 us for 96 MB.
+inline int nblocks(size_t n, int nrhs = 1) {
   size_t b = (n + kT * 8 - 1) / (kT * 8);
+  const size_t most = std::max(16, kMaxGrid / std::max(1, nrhs));
   if (b < 1) b = 1;
-  if (b > 1024) b = 1024;
+  if (b > most) b = most;
   return (int)b;
 }
 
@@ -42,8 +53,18 @@ __device__ __forceinline__ void coef(const double* num, bool cnum, const double*
 // coherent device-scope stores, waits for them to complete and takes a
 // ticket; the workgroup that takes the last ticket sums every partial in a
 // fixed order (the result does not depend on which one it is), writes
-// res[NQ * rhs + q] and resets the ticket counter.  No workgroup waits for
-// another, and no cache maintenance is needed.
+// res[NQ * rhs + q] and resets the ticket counters.  Tickets come in two
+// levels, kTicketSubs counters of a right-hand side and one for the last of
+// each, every counter on a cache line of its own: atomics on one address run
+// one after another (about 10 ns each), so a single counter would hold 1024
+// workgroups up for 10 us.  No workgroup waits for another, and no cache
+// maintenance is needed.
+__device__ __forceinline__ unsigned take_ticket(unsigned* c) {
+  return __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void reset_ticket(unsigned* c) {
+  __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 template <int NQ>
 __device__ __forceinline__ void reduce_out(double (&v)[NQ], Red red, int rhs, double* res) {
   __shared__ double lds[NQ * 16];
@@ -56,8 +77,16 @@ __device__ __forceinline__ void reduce_out(double (&v)[NQ], Red red, int rhs, do
     for (int q = 0; q < NQ; ++q)
       __hip_atomic_store(part + q * nslots + blockIdx.x, v[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_s_waitcnt(0);
-    const unsigned t = __hip_atomic_fetch_add(red.counters + rhs, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    last = t == gridDim.x - 1;
+    unsigned* line = red.counters + (size_t)rhs * (kTicketSubs + 1) * kTicketLine;
+    const unsigned G = gridDim.x, i = blockIdx.x % kTicketSubs;
+    unsigned* sub = line + (i + 1) * kTicketLine;
+    bool mine = take_ticket(sub) == (G - i - 1) / kTicketSubs;  // the last of this counter's workgroups
+    if (mine) {
+      reset_ticket(sub);
+      mine = take_ticket(line) == (G < kTicketSubs ? G : kTicketSubs) - 1;
+      if (mine) reset_ticket(line);
+    }
+    last = mine;
   }
   __syncthreads();
   if (!last) return;
@@ -83,7 +112,6 @@ __device__ __forceinline__ void reduce_out(double (&v)[NQ], Red red, int rhs, do
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) res[NQ * rhs + q] = s[q];
-    __hip_atomic_store(red.counters + rhs, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -151,6 +179,23 @@ struct Vec<bf16c> {
     reinterpret_cast<bf16c4*>(p)[g] = q;
   }
 };
+// f(g) for this thread's groups g = tid, tid + S, ... < m (S threads in the
+// grid), two at a time while both exist: f issues the loads of both before
+// its arithmetic.
+template <typename F>
+__device__ __forceinline__ void stream2(size_t m, F f) {
+  const size_t S = (size_t)gridDim.x * kT;
+  size_t g = (size_t)blockIdx.x * kT + threadIdx.x;
+  for (; g + S < m; g += 2 * S) {
+    const size_t at[2] = {g, g + S};
+    f(at);
+  }
+  if (g < m) {
+    const size_t at[1] = {g};
+    f(at);
+  }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(kT) k_norm2(const T* __restrict__ x, size_t n, Red red,
                                               double* res) {
@@ -159,12 +204,16 @@ __global__ void __launch_bounds__(kT) k_norm2(const T* __restrict__ x, size_t n,
   x += rhs * n;
   constexpr int V = Vec<T>::V;
   double acc = 0.0;
-  for (size_t g = (size_t)blockIdx.x * kT + threadIdx.x; g < n / V; g += (size_t)gridDim.x * kT) {
-    cplx<R> v[V];
-    Vec<T>::ld(x, g, v);
+  stream2(n / V, [&](const auto& at) {
+    constexpr int U = sizeof(at) / sizeof(at[0]);
+    cplx<R> v[U][V];
 #pragma unroll
-    for (int k = 0; k < V; ++k) acc += nrm(v[k]);
-  }
+    for (int u = 0; u < U; ++u) Vec<T>::ld(x, at[u], v[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < V; ++k) acc += nrm(v[u][k]);
+  });
   double v[1] = {acc};
   reduce_out<1>(v, red, rhs, res);
 }
@@ -176,11 +225,17 @@ __global__ void __launch_bounds__(kT) k_dot(const T* __restrict__ a, const T* __
   a += rhs * n;
   b += rhs * n;
   double re = 0.0, im = 0.0;
-  for (size_t i = (size_t)blockIdx.x * kT + threadIdx.x; i < n; i += (size_t)gridDim.x * kT) {
-    const auto x = St<T>::ld(a + i), y = St<T>::ld(b + i);
-    re += (double)x.re * y.re + (double)x.im * y.im;
-    im += (double)x.re * y.im - (double)x.im * y.re;
-  }
+  stream2(n, [&](const auto& at) {
+    constexpr int U = sizeof(at) / sizeof(at[0]);
+    cplx<typename St<T>::R> x[U], y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = St<T>::ld(a + at[u]), y[u] = St<T>::ld(b + at[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      re += (double)x[u].re * y[u].re + (double)x[u].im * y[u].im;
+      im += (double)x[u].re * y[u].im - (double)x[u].im * y[u].re;
+    }
+  });
   double v[2] = {re, im};
   reduce_out<2>(v, red, rhs, res);
 }
@@ -204,31 +259,34 @@ k_update(T* __restrict__ x, T* __restrict__ r, const T* __restrict__ p, const T*
   p += off;
   w += off;
   double acc = 0.0;
-  for (size_t g = (size_t)blockIdx.x * kT + threadIdx.x; g < n / V; g += (size_t)gridDim.x * kT) {
-    cplx<R> pv[V], wv[V], xv[V], rv[V];
-    Vec<T>::ld(p, g, pv);
-    if constexpr (!XONLY) {
-      Vec<T>::ld(w, g, wv);
-      Vec<T>::ld(r, g, rv);
-    }
-    if constexpr (X0) {
+  stream2(n / V, [&](const auto& at) {
+    constexpr int U = sizeof(at) / sizeof(at[0]);
+    cplx<R> pv[U][V], wv[U][V], xv[U][V], rv[U][V];
 #pragma unroll
-      for (int k = 0; k < V; ++k) xv[k] = cmk((R)0, (R)0);
-    } else {
-      Vec<T>::ld(x, g, xv);
-    }
-#pragma unroll
-    for (int k = 0; k < V; ++k) {
-      xv[k] = xv[k] + a * pv[k];
+    for (int u = 0; u < U; ++u) {
+      Vec<T>::ld(p, at[u], pv[u]);
       if constexpr (!XONLY) {
-        if (den2) wv[k] = wv[k] + l * pv[k];
-        rv[k] = rv[k] - a * wv[k];
-        acc += nrm(rv[k]);
+        Vec<T>::ld(w, at[u], wv[u]);
+        Vec<T>::ld(r, at[u], rv[u]);
       }
+      if constexpr (!X0) Vec<T>::ld(x, at[u], xv[u]);
     }
-    Vec<T>::st(x, g, xv);
-    if constexpr (!XONLY) Vec<T>::st(r, g, rv);
-  }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        if constexpr (X0) xv[u][k] = cmk((R)0, (R)0);
+        xv[u][k] = xv[u][k] + a * pv[u][k];
+        if constexpr (!XONLY) {
+          if (den2) wv[u][k] = wv[u][k] + l * pv[u][k];
+          rv[u][k] = rv[u][k] - a * wv[u][k];
+          acc += nrm(rv[u][k]);
+        }
+      }
+      Vec<T>::st(x, at[u], xv[u]);
+      if constexpr (!XONLY) Vec<T>::st(r, at[u], rv[u]);
+    }
+  });
   if (!XONLY && rr) {
     double v[1] = {acc};
     reduce_out<1>(v, red, rhs, rr);
@@ -249,17 +307,24 @@ k_xpay(T* __restrict__ p, const T* __restrict__ y, size_t n, const double* num, 
   p += off;
   y += off;
   double acc = 0.0;
-  for (size_t g = (size_t)blockIdx.x * kT + threadIdx.x; g < n / V; g += (size_t)gridDim.x * kT) {
-    cplx<R> yv[V], pv[V];
-    Vec<T>::ld(y, g, yv);
-    Vec<T>::ld(p, g, pv);
+  stream2(n / V, [&](const auto& at) {
+    constexpr int U = sizeof(at) / sizeof(at[0]);
+    cplx<R> yv[U][V], pv[U][V];
 #pragma unroll
-    for (int k = 0; k < V; ++k) {
-      pv[k] = yv[k] + b * pv[k];
-      acc += nrm(pv[k]);
+    for (int u = 0; u < U; ++u) {
+      Vec<T>::ld(y, at[u], yv[u]);
+      Vec<T>::ld(p, at[u], pv[u]);
     }
-    Vec<T>::st(p, g, pv);
-  }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        pv[u][k] = yv[u][k] + b * pv[u][k];
+        acc += nrm(pv[u][k]);
+      }
+      Vec<T>::st(p, at[u], pv[u]);
+    }
+  });
   if (pp) {
     double v[1] = {acc};
     reduce_out<1>(v, red, rhs, pp);
@@ -391,14 +456,14 @@ template <typename T>
 int norm2_t(Red red, const T* x, size_t n, int nrhs, double* res, hipStream_t st) {
   if (n % Vec<T>::V) return fail(DWF_ERR_ARG, "16-bit fields need a multiple of 4 complex values");
   if (nrhs > 64) return fail(DWF_ERR_ARG, "nrhs > 64");
-  hipLaunchKernelGGL((k_norm2<T>), dim3(nblocks(n), nrhs), dim3(kT), 0, st, x, n, red, res);
+  hipLaunchKernelGGL((k_norm2<T>), dim3(nblocks(n, nrhs), nrhs), dim3(kT), 0, st, x, n, red, res);
   LAUNCH_CHECK();
   return DWF_OK;
 }
 template <typename T>
 int dot_t(Red red, const T* a, const T* b, size_t n, int nrhs, double* res, hipStream_t st) {
   if (nrhs > 64) return fail(DWF_ERR_ARG, "nrhs > 64");
-  hipLaunchKernelGGL((k_dot<T>), dim3(nblocks(n), nrhs), dim3(kT), 0, st, a, b, n, red, res);
+  hipLaunchKernelGGL((k_dot<T>), dim3(nblocks(n, nrhs), nrhs), dim3(kT), 0, st, a, b, n, red, res);
   LAUNCH_CHECK();
   return DWF_OK;
 }
@@ -409,7 +474,7 @@ int update_t(Red red, T* x, T* r, const T* p, const T* w, size_t n, int nrhs, co
   if (n % Vec<T>::V) return fail(DWF_ERR_ARG, "16-bit fields need a multiple of 4 complex values");
   if (nrhs > 64) return fail(DWF_ERR_ARG, "nrhs > 64");
   if (mode < 0 || mode > (kUpdX0 | kUpdXOnly)) return fail(DWF_ERR_ARG, "update: bad mode");
-  const dim3 grid(nblocks(n), nrhs);
+  const dim3 grid(nblocks(n, nrhs), nrhs);
 #define HDCG_UPDATE(M)                                                                                      \
   hipLaunchKernelGGL((k_update<T, M>), grid, dim3(kT), 0, st, x, r, p, w, n, num, cnum, den, den2, lam, red, \
                      rr, dstr)
@@ -428,7 +493,7 @@ int xpay_t(Red red, T* p, const T* y, size_t n, int nrhs, const double* num, boo
            const double* den, double sign, double* pp, hipStream_t st, int dstr) {
   if (n % Vec<T>::V) return fail(DWF_ERR_ARG, "16-bit fields need a multiple of 4 complex values");
   if (nrhs > 64) return fail(DWF_ERR_ARG, "nrhs > 64");
-  hipLaunchKernelGGL((k_xpay<T>), dim3(nblocks(n), nrhs), dim3(kT), 0, st, p, y, n, num, cnum, den,
+  hipLaunchKernelGGL((k_xpay<T>), dim3(nblocks(n, nrhs), nrhs), dim3(kT), 0, st, p, y, n, num, cnum, den,
                      sign, red, pp, dstr);
   LAUNCH_CHECK();
   return DWF_OK;
@@ -473,14 +538,14 @@ int b_mirs16_init(Red red, bf16c* r, bf16c* p, const c64* b, size_t n, int nrhs,
                   hipStream_t st) {
   if (n % 12 || (n / 12) % Ls) return fail(DWF_ERR_ARG, "M_IRS: field size not a whole number of site rows");
   if (nrhs > 64) return fail(DWF_ERR_ARG, "nrhs > 64");
-  hipLaunchKernelGGL(k_mirs16_init, dim3(nblocks(n), nrhs), dim3(kT), 0, st, r, p, b, n / 12, Ls, red, rr);
+  hipLaunchKernelGGL(k_mirs16_init, dim3(nblocks(n, nrhs), nrhs), dim3(kT), 0, st, r, p, b, n / 12, Ls, red, rr);
   LAUNCH_CHECK();
   return DWF_OK;
 }
 int b_mirs16_last(c64* x_out, const bf16c* x, const bf16c* p, size_t n, int nrhs, int Ls, const double* num,
                   const double* den, const double* den2, double lam, hipStream_t st) {
   if (n % 12 || (n / 12) % Ls) return fail(DWF_ERR_ARG, "M_IRS: field size not a whole number of site rows");
-  hipLaunchKernelGGL(k_mirs16_last, dim3(nblocks(n), nrhs), dim3(kT), 0, st, x_out, x, p, n / 12, Ls, num, den,
+  hipLaunchKernelGGL(k_mirs16_last, dim3(nblocks(n, nrhs), nrhs), dim3(kT), 0, st, x_out, x, p, n / 12, Ls, num, den,
                      den2, lam);
   LAUNCH_CHECK();
   return DWF_OK;
@@ -499,14 +564,14 @@ int b_axpby(cplx<R>* y, const cplx<R>* x, double a, double b, size_t total, hipS
 template <typename Ry, typename Rx>
 int b_axpy_mixed(cplx<Ry>* y, const cplx<Rx>* x, const double* s, size_t n, int nrhs,
                  hipStream_t st, bool sqrt_s) {
-  hipLaunchKernelGGL((k_axpy_mixed<Ry, Rx>), dim3(nblocks(n), nrhs), dim3(kT), 0, st, y, x, s, n, sqrt_s);
+  hipLaunchKernelGGL((k_axpy_mixed<Ry, Rx>), dim3(nblocks(n, nrhs), nrhs), dim3(kT), 0, st, y, x, s, n, sqrt_s);
   LAUNCH_CHECK();
   return DWF_OK;
 }
 template <typename Ry, typename Rx>
 int b_scale_copy(cplx<Ry>* y, const cplx<Rx>* x, const double* v, bool invsqrt, size_t n, int nrhs,
                  hipStream_t st) {
-  hipLaunchKernelGGL((k_scale_copy<Ry, Rx>), dim3(nblocks(n), nrhs), dim3(kT), 0, st, y, x, v,
+  hipLaunchKernelGGL((k_scale_copy<Ry, Rx>), dim3(nblocks(n, nrhs), nrhs), dim3(kT), 0, st, y, x, v,
                      invsqrt, n);
   LAUNCH_CHECK();
   return DWF_OK;

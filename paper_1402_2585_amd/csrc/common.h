@@ -213,11 +213,13 @@ struct DevBuf {
 // a fixed order and resets the counter.
 constexpr int kMaxPartials = 1 << 16;  // partial slots per reduced quantity
 constexpr int kPinnedDoubles = 1024;   // host pinned scalars of an operator handle
-constexpr int kRedThreads = 256;
+constexpr int kTicketSubs = 32;        // first-level ticket counters of a right-hand side
+constexpr int kTicketLine = 32;        // words from one counter to the next (128 bytes)
+constexpr int kTicketWords = 64 * (kTicketSubs + 1) * kTicketLine;
 
 struct Reducer {
   DevBuf partials;  // double [nq][kMaxPartials]
-  DevBuf counters;  // unsigned [64]
+  DevBuf counters;  // tickets: [64][kTicketSubs + 1] counters, one a cache line
   DevBuf results;   // double [nq]
   int ensure(int nq);
 };

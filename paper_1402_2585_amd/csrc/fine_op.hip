@@ -820,8 +820,8 @@ static inline int red_blocks(size_t n) {
 int ensure_reducer(dwf_op* op) {
   HDCG_TRY(op->red.partials.ensure(sizeof(double) * (size_t)kMaxPartials * 64));
   if (op->red.counters.bytes == 0) {
-    HDCG_TRY(op->red.counters.ensure(sizeof(unsigned) * 64));
-    HDCG_HIP(hipMemset(op->red.counters.ptr, 0, sizeof(unsigned) * 64));
+    HDCG_TRY(op->red.counters.ensure(sizeof(unsigned) * kTicketWords));
+    HDCG_HIP(hipMemset(op->red.counters.ptr, 0, sizeof(unsigned) * kTicketWords));
   }
   HDCG_TRY(op->red.results.ensure(sizeof(double) * 256));
   return DWF_OK;
