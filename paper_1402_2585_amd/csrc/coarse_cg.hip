@@ -405,7 +405,8 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
 
   // ---- x = 0, r = b, p_0 = b; |b|^2
   double acc0 = 0.0, acc1 = 0.0;
-  for (int a = wg; a < Nc; a += G) {
+  for (int ia = wg; ia < Nc; ia += G) {
+    const int a = xcd_remap(ia, Nc);  // each XCD owns a contiguous slab (xcd_site)
     const size_t so = (size_t)a * nvec;
     if (has0) {
       const c64 bv = A.b[o0 + so];
@@ -462,7 +463,8 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
     // XCD's stale lines, so that its 81-fold reuse across the sites hits L2)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     acc0 = acc1 = 0.0;
-    for (int a = wg; a < Nc; a += G) {
+    for (int ia = wg; ia < Nc; ia += G) {
+      const int a = xcd_remap(ia, Nc);  // each XCD owns a contiguous slab (xcd_site)
       if constexpr (MODE == 0) {
         for (int r0 = 0; r0 < nr; r0 += NR0)
           capply_site<float, NR0, U0, false, kStencil, false>(A.AT, A.nbr, pk, A.w, a, Nc, nvec, nr, r0,
@@ -495,7 +497,8 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
     acc0 = acc1 = 0.0;
     {
       const float al0 = (float)s_alpha[q0], al1 = (float)s_alpha[q1];
-      for (int a = wg; a < Nc; a += G) {
+      for (int ia = wg; ia < Nc; ia += G) {
+      const int a = xcd_remap(ia, Nc);  // each XCD owns a contiguous slab (xcd_site)
         const size_t so = (size_t)a * nvec;
         if (has0) {
           const size_t i = o0 + so;
@@ -533,7 +536,8 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
     // ---- phase P: p_{k+1} = r_{k+1} + beta_k p_k on own sites
     {
       const float be0 = s_beta[q0], be1 = s_beta[q1];
-      for (int a = wg; a < Nc; a += G) {
+      for (int ia = wg; ia < Nc; ia += G) {
+      const int a = xcd_remap(ia, Nc);  // each XCD owns a contiguous slab (xcd_site)
         const size_t so = (size_t)a * nvec;
         if (has0) {
           const size_t i = o0 + so;
@@ -695,7 +699,7 @@ int launch_solve(hdcg* h, const PcgWork& wk, int mode, int mt, int G, int mprec,
   a.nr = nr;
   a.maxiter = maxiter;
   a.accumulate = accumulate;
-  a.ksteps = (2 * kStencil * nv + 15) / 16;
+  a.ksteps = mfma_ksteps(kStencil * nv);
   a.gmax = G;
   a.tol2 = tol * tol;
   a.spin_limit = 1u << 21;  // >= 50 ms of waiting at 64+ cycles per poll

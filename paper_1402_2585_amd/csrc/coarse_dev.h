@@ -26,6 +26,12 @@ __host__ __device__ inline int one_hop_l(int m) {
   return (m & 1) ? 40 - p3 : 40 + p3;
 }
 
+// The coarse site of this workgroup (grid Nc in x): each XCD takes one
+// contiguous range of sites, a slab of t-slices, so that its L2 holds the
+// operand of its slab and one slice either side (16 RHS on 6^4, Nvec 48: 3.7
+// of 8 MB) instead of every XCD's the whole grid's.
+__device__ __forceinline__ int xcd_site(int Nc) { return xcd_remap(blockIdx.x, Nc); }
+
 // Loads and stores of complex64 values that other workgroups of a running
 // persistent kernel write or read: relaxed device-scope atomics, coherent
 // across the XCDs' L2 caches without whole-cache write-back or invalidation.
@@ -137,7 +143,7 @@ __device__ __forceinline__ void capply_site(const cplx<R>* __restrict__ AT, cons
 // ------------------------------------------------------ 16-bit MFMA form --
 // For one coarse site the 81-point stencil is one real GEMM
 //   out[j][n] = sum_kappa Ahat[j][kappa] B[kappa][n]
-// with kappa = (part, l, k) over K = 2 * 81 * Nvec:
+// with kappa over (part, l, k), K = 2 * 81 * Nvec:
 //   Ahat[j][(0,l,k)] = Re A[a][l][j][k] / s_al,  Ahat[j][(1,l,k)] = Im A[a][l][j][k] / s_al
 //   B[(0,l,k)][r]          = rho_al Re c_r[a+dl][k],   B[(1,l,k)][r]          = -rho_al Im c_r[a+dl][k]
 //   B[(0,l,k)][nrhs + r]   = rho_al Im c_r[a+dl][k],   B[(1,l,k)][nrhs + r]   =  rho_al Re c_r[a+dl][k]
@@ -146,12 +152,21 @@ __device__ __forceinline__ void capply_site(const cplx<R>* __restrict__ AT, cons
 // scale), smax_a = max_l s_al and rho_al = s_al / smax_a <= 1, which keeps
 // both operands within the fp16 range.
 //
+// The complex columns q = (l, k) go in groups of 16, a group's real parts
+// (part 0) in one 16-wide K step and its imaginary parts (part 1) in the
+// next: the two need the same 16 operand values, so the 16x16x32 form reads
+// each once per site and RHS (its lanes kg and kg + 2 share a cache line), a
+// wave's consecutive 16x16x16 steps hit L1.  With all of part 0 before all of
+// part 1 every operand line went from L2 to L1 twice, 1 MB a site for 16 RHS
+// at Nvec 48 beside 0.75 MB of matrix.
+//
 // Ahat is stored per coarse site and K step as [row m < nvec][kgroup 0..3][4]
 // (the 16 K values of one step and row are contiguous), so the A fragment of
 // an M tile is one contiguous run that a wave reads with 8-byte lanes, and no
 // bytes are stored or read for the rows that pad nvec to a multiple of 16.
 // The NW waves take U consecutive K steps at a time, with all their loads
 // issued before the MFMAs, and reduce through LDS.
+__host__ __device__ inline int mfma_ksteps(int columns) { return 2 * ((columns + 15) / 16); }
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -192,12 +207,10 @@ __device__ __forceinline__ void capply_site_mfma(const unsigned short* __restric
   using frag = std::conditional_t<K32, s16x8, s16x4>;
   static_assert(!STAGED || NT == 1, "the LDS-staged operand serves one right-hand side");
   constexpr int KL = K32 ? 8 : 4;  // K values per lane and step
-  constexpr int KS = 4 * KL;       // K values per step
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int ktot = 2 * NS * nvec;
   const int kn = NS * nvec;
   const int r16 = lane & 15, kg = lane >> 4;
-  const int nsteps = K32 ? (ksteps + 1) / 2 : ksteps;
+  const int nsteps = K32 ? ksteps / 2 : ksteps;
   f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -236,11 +249,10 @@ __device__ __forceinline__ void capply_site_mfma(const unsigned short* __restric
       // one right-hand side, operand in LDS: each step's run converted as read
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int k0 = KS * (s0 + u) + KL * kg;
+        const int rem = K32 ? 16 * (s0 + u) + 8 * (kg & 1) : 16 * ((s0 + u) >> 1) + 4 * kg;
+        const int part = K32 ? kg >> 1 : (s0 + u) & 1;
         bf[u][0] = frag{};
-        if (cok && s0 + u < nsteps && k0 < ktot) {
-          const int part = k0 / kn;
-          const int rem = k0 - part * kn;
+        if (cok && s0 + u < nsteps && rem < kn) {
           const float r = rh[rem / nvec];
           frag b;
 #pragma unroll
@@ -261,11 +273,10 @@ __device__ __forceinline__ void capply_site_mfma(const unsigned short* __restric
       bool okv[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int k0 = KS * (s0 + u) + KL * kg;
-        const bool ok = cok && s0 + u < nsteps && k0 < ktot;
-        const int kk = ok ? k0 : 0;
-        const int part = kk / kn;
-        const int rem = kk - part * kn;
+        const int q0 = K32 ? 16 * (s0 + u) + 8 * (kg & 1) : 16 * ((s0 + u) >> 1) + 4 * kg;
+        const int part = K32 ? kg >> 1 : (s0 + u) & 1;
+        const bool ok = cok && s0 + u < nsteps && q0 < kn;
+        const int rem = ok ? q0 : 0;
         const int l = rem / nvec, k = rem - l * nvec;
         okv[u] = ok;
         prt[u] = part;

@@ -62,15 +62,13 @@ __global__ void k_frag(const c128* __restrict__ A, const float* __restrict__ rho
   const size_t as = e / (4 * (size_t)nvec);
   const int s = (int)(as % ksteps);
   const int a = (int)(as / ksteps);
-  const int ktot = 2 * NS * nvec;
+  const int part = s & 1;
   unsigned short v4[4];
   for (int i = 0; i < 4; ++i) {
-    const int kap = 16 * s + 4 * kg + i;
+    const int q = 16 * (s >> 1) + 4 * kg + i;
     float v = 0.f;
-    if (kap < ktot) {
-      const int part = kap / (NS * nvec);
-      const int rem = kap - part * NS * nvec;
-      const int l = rem / nvec, k = rem - (rem / nvec) * nvec;
+    if (q < NS * nvec) {
+      const int l = q / nvec, k = q - l * nvec;
       const float sal = rho[a * NS + l] * smax[a];
       const c128 x = A[(((size_t)a * NS + l) * nvec + m) * nvec + k];
       v = sal > 0.f ? (float)((part == 0 ? x.re : x.im) / sal) : 0.f;
@@ -87,7 +85,7 @@ k_capply_mfma(const unsigned short* __restrict__ F, const float* __restrict__ rh
               const float* __restrict__ smax, const int* __restrict__ nbr, const c64* __restrict__ in,
               c64* __restrict__ out, int Nc, int nvec, int nrhs, int ksteps) {
   __shared__ f32x4 red[NW * MT * NT * 64];
-  capply_site_mfma<BF16, MT, NT, NW, U, false, false, K32, NS>(F, rho, smax, nbr, in, out, blockIdx.x, Nc, nvec,
+  capply_site_mfma<BF16, MT, NT, NW, U, false, false, K32, NS>(F, rho, smax, nbr, in, out, xcd_site(Nc), Nc, nvec,
                                                                nrhs, ksteps, red);
 }
 
@@ -100,7 +98,7 @@ k_capply_mfma_staged(const unsigned short* __restrict__ F, const float* __restri
                      c64* __restrict__ out, int Nc, int nvec, int ksteps) {
   __shared__ f32x4 red[8 * MT * 64];
   __shared__ c64 xin[NS * 64];
-  const int a = blockIdx.x;
+  const int a = xcd_site(Nc);
   const int* nb = nbr + (size_t)a * NS;
   for (int e = threadIdx.x; e < NS * nvec; e += 8 * 64) {
     const int l = e / nvec;
@@ -292,7 +290,7 @@ int crs_build_mfma(hdcg* h, int prec, hipStream_t st) {
   const int nv = h->nvec;
   if (nv % 4 != 0 || nv > 64)
     return fail(DWF_ERR_ARG, "16-bit coarse storage needs nvec a multiple of 4 and <= 64");
-  const int ksteps = (2 * kStencil * nv + 15) / 16;
+  const int ksteps = mfma_ksteps(kStencil * nv);
   if (h->mf_smax.bytes == 0) {
     HDCG_TRY(h->mf_rho.ensure(sizeof(float) * h->Nc * kStencil));
     HDCG_TRY(h->mf_smax.ensure(sizeof(float) * h->Nc));
@@ -325,7 +323,7 @@ int crs_build_mfma(hdcg* h, int prec, hipStream_t st) {
 int crs_apply_mfma(hdcg* h, int prec, const c64* in, c64* out, int nr, hipStream_t st) {
   if ((prec == DWF_BF16 && !h->mf_have_bf16) || (prec == DWF_F16 && !h->mf_have_f16))
     HDCG_TRY(crs_build_mfma(h, prec, st));
-  const int ksteps = (2 * kStencil * h->nvec + 15) / 16;
+  const int ksteps = mfma_ksteps(kStencil * h->nvec);
   const unsigned short* F = (prec == DWF_BF16 ? h->mf_bf16 : h->mf_f16).as<unsigned short>();
   // one tile for the full 16-column launches, one for the last, smaller one
   const int nfull = nr / 16, rest = nr % 16;
@@ -419,7 +417,7 @@ int trunc16_chunk(hdcg* h, const unsigned short* F, const c64* in, c64* out, int
 
 template <bool BF16>
 int trunc16_all(hdcg* h, const unsigned short* F, const c64* in, c64* out, int nr, hipStream_t st) {
-  const int ksteps = (2 * kTS9 * h->nvec + 15) / 16;
+  const int ksteps = mfma_ksteps(kTS9 * h->nvec);
   const int mt = (h->nvec + 15) / 16;
   for (int r0 = 0; r0 < nr; r0 += 16) {
     const int n = nr - r0 < 16 ? nr - r0 : 16;
@@ -456,7 +454,7 @@ int trunc16_build(hdcg* h, int prec, double shift, hipStream_t st) {
   hipLaunchKernelGGL(k_rho<kTS9>, dim3((h->Nc + 127) / 128), dim3(128), 0, st, h->tq_rho.as<float>(),
                      h->tq_smax.as<float>(), h->Nc);
   HDCG_HIP(hipGetLastError());
-  const int ksteps = (2 * kTS9 * nv + 15) / 16;
+  const int ksteps = mfma_ksteps(kTS9 * nv);
   const size_t total = (size_t)h->Nc * ksteps * nv * 4;
   DevBuf& F = prec == DWF_BF16 ? h->tq_bf16 : h->tq_f16;
   HDCG_TRY(F.ensure(total * 4 * sizeof(unsigned short)));
@@ -503,7 +501,7 @@ int crs_mfma_tile(hdcg* h, int prec, int n, int out[3], float* ms, int* ntiles, 
     HDCG_HIP(hipMemsetAsync(a.ptr, 0, bytes, st));
     int t = 0;
     const int rc = tile_for(h, prec, (prec == DWF_BF16 ? h->mf_bf16 : h->mf_f16).as<unsigned short>(), a.as<c64>(),
-                            b.as<c64>(), n, (2 * kStencil * h->nvec + 15) / 16, st, &t);
+                            b.as<c64>(), n, mfma_ksteps(kStencil * h->nvec), st, &t);
     HDCG_HIP(hipStreamSynchronize(st));
     a.release();
     b.release();

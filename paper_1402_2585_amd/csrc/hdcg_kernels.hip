@@ -439,7 +439,7 @@ __global__ void __launch_bounds__(kCT)
 k_capply(const cplx<R>* __restrict__ AT, const int* __restrict__ nbr, const cplx<R>* __restrict__ in,
          cplx<R>* __restrict__ out, int Nc, int nvec, int nr) {
   __shared__ cplx<R> red[kCT * NR];
-  capply_site<R, NR, U>(AT, nbr, in, out, blockIdx.x, Nc, nvec, nr, blockIdx.y * NR, red);
+  capply_site<R, NR, U>(AT, nbr, in, out, xcd_site(Nc), Nc, nvec, nr, blockIdx.y * NR, red);
 }
 
 // One right-hand side in complex64: the site's operand at its 81 neighbours
@@ -452,7 +452,7 @@ k_capply_staged(const c64* __restrict__ AT, const int* __restrict__ nbr, const c
                 c64* __restrict__ out, int Nc, int nvec) {
   __shared__ c64 red[kCT];
   __shared__ c64 xin[kStencil * kStageNvec];
-  const int a = blockIdx.x;
+  const int a = xcd_site(Nc);
   const int* nb = nbr + (size_t)a * kStencil;
   for (int e = threadIdx.x; e < kStencil * nvec; e += kCT) {
     const int l = e / nvec;
@@ -472,7 +472,7 @@ k_capply_cmfma(const cplx<R>* __restrict__ AT, const int* __restrict__ nbr, cons
   __shared__ macc_t<R> red[NW * MT * NT * 64];
   const int r0 = 16 * blockIdx.y;
   const size_t off = (size_t)r0 * Nc * nvec;
-  capply_site_cmfma<R, MT, NT, NW, U>(AT, nbr, in + off, out + off, blockIdx.x, Nc, nvec, min(16, nr - r0), red);
+  capply_site_cmfma<R, MT, NT, NW, U>(AT, nbr, in + off, out + off, xcd_site(Nc), Nc, nvec, min(16, nr - r0), red);
 }
 
 template <typename R, int MT, int NT>
