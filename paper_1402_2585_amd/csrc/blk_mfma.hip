@@ -11,6 +11,8 @@
 // x = hi + mid + lo with |x - hi - mid - lo| <= 2^-24 |x|: every product is
 // exact in FP32 and equal to the one the FP32 kernels form with x, so the
 // results differ from theirs only in the order of the sums.
+#include <algorithm>
+
 #include "coarse_dev.h"
 
 namespace hdk {
@@ -48,10 +50,13 @@ __device__ __forceinline__ f32x4 mfma(w32x4 a, w32x4 b, f32x4 c) {
 
 // out[r*sr + a*sa + k*sk] = sum_i conj(P[a][k][i]) Q_r(site(a, i)) for the
 // right-hand sides r0 .. r0 + 15 (r < nr) of this workgroup (blockIdx.y).
-// One workgroup per block a (blockIdx.x); its NW waves split the nb entries
-// in K steps of 16 (U consecutive steps per wave at a time, their loads
-// issued before the MFMAs) and reduce through LDS (`red`, dynamic:
-// NW * MT * 2 * 64 f32x4).  Real GEMM: rows (k, Re) carry the K pairs
+// gridDim.z workgroups per block a (blockIdx.x) take equal slices of the nb
+// entries; a workgroup's NW waves split its slice in K steps of 16 (U
+// consecutive steps per wave at a time, their loads issued before the MFMAs)
+// and reduce through LDS (`red`, dynamic: NW * MT * 2 * 64 f32x4).  With
+// several slices each stores its sums (part, device-scope) and takes a
+// ticket (cnt[a, y]); the last adds the slices in their order, whichever
+// came last, and resets the ticket.  Real GEMM: rows (k, Re) carry the K pairs
 // (Re P, Im P), rows (k, Im) (-Im P, Re P), columns r (Re Q, Im Q) per
 // entry i.  Lane layout of the 16x16x32 form: A row lane % 16 and B column
 // lane % 16, each with K values 8 (lane / 16) .. + 7 (the entries
@@ -62,8 +67,9 @@ template <int NW, int U, int MT>
 __global__ void __launch_bounds__(NW * 64)
 k_project_mfma(const unsigned* __restrict__ P, const c64* __restrict__ Q, size_t fstride,
                const int* __restrict__ site_of, int nsb, int col, int nb, int nvec, int nr,
-               c64* __restrict__ out, size_t sr, size_t sa, size_t sk) {
+               c64* __restrict__ out, size_t sr, size_t sa, size_t sk, c64* part, unsigned* cnt) {
   extern __shared__ f32x4 red[];
+  __shared__ int last;
   const int a = blockIdx.x, r0 = blockIdx.y * 16;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r16 = lane & 15, kg = lane >> 4;
@@ -75,8 +81,9 @@ k_project_mfma(const unsigned* __restrict__ P, const c64* __restrict__ Q, size_t
   f32x4 acc[MT][2];
 #pragma unroll
   for (int m = 0; m < MT; ++m) acc[m][0] = acc[m][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int nsteps = (nb + 15) / 16;
-  for (int s0 = wave * U; s0 < nsteps; s0 += NW * U) {
+  const int S = gridDim.z, all = (nb + 15) / 16, per = ((all + S - 1) / S + U - 1) / U * U;
+  const int begin = blockIdx.z * per, nsteps = min(all, begin + per);
+  for (int s0 = begin + wave * U; s0 < nsteps; s0 += NW * U) {
     w32x4 pa[U][MT];
     f32x4 qa[U][2];
 #pragma unroll
@@ -130,12 +137,37 @@ k_project_mfma(const unsigned* __restrict__ P, const c64* __restrict__ Q, size_t
       vim += red[((w * MT + m) * 2 + 1) * 64 + ln];
     }
     const int r = r0 + (ln & 15);
+    if (S > 1) {
+      c64* mine = part + ((((size_t)blockIdx.y * gridDim.x + a) * S + blockIdx.z) * MT * 64 + q) * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) st_coherent(mine + e, cmk(vre[e], vim[e]));
+      continue;
+    }
     if (r >= nr) continue;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int k = m * 16 + 4 * (ln >> 4) + e;
       if (k < nvec) out[r * sr + a * sa + k * sk] = cmk(vre[e], vim[e]);
     }
+  }
+  if (S == 1) return;
+  __builtin_amdgcn_s_waitcnt(0);  // this wave's partial sums are stored
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned* c = cnt + (size_t)blockIdx.y * gridDim.x + a;
+    last = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)S - 1;
+    if (last) __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!last) return;
+  const c64* slices = part + ((size_t)blockIdx.y * gridDim.x + a) * S * MT * 256;
+  for (int q = threadIdx.x; q < MT * 256; q += NW * 64) {
+    const int m = q >> 8, ln = (q >> 2) & 63, e = q & 3;
+    const int r = r0 + (ln & 15), k = m * 16 + 4 * (ln >> 4) + e;
+    if (r >= nr || k >= nvec) continue;
+    c64 v = cmk(0.f, 0.f);
+    for (int z = 0; z < S; ++z) v = v + ld_coherent(slices + (size_t)z * MT * 256 + q);
+    out[r * sr + a * sa + k * sk] = v;
   }
 }
 
@@ -248,12 +280,31 @@ int blk_project_mfma(hdcg* h, const bf16c* P, const c64* fine, size_t fstride, i
   const int col = 12 * h->op->g.Ls;
   const int nb = h->nsb * col;
   const int mt = (h->nvec + 15) / 16;
-  const dim3 grid(h->Nc, (nr + 15) / 16);
+  // Slices of a block: workgroups for every CU to hold four (one a block
+  // left most of the chip idle on small coarse grids: 162 blocks, 24576
+  // entries, Nvec 48, 16 RHS 516 us; Nvec 8, 12288 entries, 4 RHS 154 us),
+  // each with at least four rounds of its waves.  Where the partial sums have
+  // no room yet and the stream is being captured, one slice.
+  const int groups = h->Nc * ((nr + 15) / 16);
+  int S = std::max(1, std::min(std::min(16, 1024 / groups), (nb + 15) / 16 / (4 * NW * U)));
+  if (S > 1 && h->pj_cnt.bytes == 0) {
+    // S * groups <= 1024: one allocation serves every later call
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+      S = 1;
+    } else {
+      HDCG_TRY(h->pj_part.ensure((size_t)1024 * mt * 256 * sizeof(c64)));
+      HDCG_TRY(h->pj_cnt.ensure(1024 * sizeof(unsigned)));
+      HDCG_HIP(hipMemsetAsync(h->pj_cnt.ptr, 0, h->pj_cnt.bytes, st));
+    }
+  }
+  const dim3 grid(h->Nc, (nr + 15) / 16, S);
   const size_t lds = (size_t)NW * mt * 2 * 64 * sizeof(f32x4);
   const unsigned* Pw = reinterpret_cast<const unsigned*>(P);
 #define HDCG_PROJ_MFMA(M)                                                                                      \
   hipLaunchKernelGGL((k_project_mfma<NW, U, M>), grid, dim3(NW * 64), lds, st, Pw, fine, fstride,              \
-                     h->site_of.as<int>(), h->nsb, col, nb, h->nvec, nr, out, sr, sa, sk)
+                     h->site_of.as<int>(), h->nsb, col, nb, h->nvec, nr, out, sr, sa, sk, h->pj_part.as<c64>(), \
+                     h->pj_cnt.as<unsigned>())
   switch (mt) {
     case 1: HDCG_PROJ_MFMA(1); break;
     case 2: HDCG_PROJ_MFMA(2); break;

@@ -67,6 +67,7 @@ struct hdcg {
   hdk::DevBuf mf_rho, mf_smax;      // per-matrix scales of the 16-bit coarse storage
   hdk::DevBuf mf_bf16, mf_f16;      // MFMA fragment-ordered 16-bit coarse matrices
   int mf_have_bf16 = 0, mf_have_f16 = 0;
+  hdk::DevBuf pj_part, pj_cnt;      // sliced project: partial sums of the slices, tickets (zero between launches)
   hdk::DevBuf pcg_part;             // persistent coarse CG: per-workgroup partial sums
   hdk::DevBuf pcg_state;            // persistent coarse CG: grid barrier, status, iterations
   int persistent_coarse = 1;        // run the coarse CG as one persistent kernel when it applies

@@ -778,6 +778,8 @@ int hdcg_destroy(hdcg_t h) {
   h->mf_smax.release();
   h->mf_bf16.release();
   h->mf_f16.release();
+  h->pj_part.release();
+  h->pj_cnt.release();
   h->pcg_part.release();
   h->pcg_state.release();
   h->ldZ128.release();
