@@ -30,14 +30,11 @@
 //   phase P   p_{k+1} = r_{k+1} + beta_k p_k on own sites
 //   barrier
 //
-// Reductions are deterministic: each workgroup stores one partial per
-// right-hand side, and every workgroup sums all partials in the same fixed
-// order, so every workgroup takes the same branch.  Partials alternate
-// between two buffers (a buffer is rewritten only after the barrier that
-// follows its last read).  The barrier uses per-workgroup arrival flags that
-// workgroup 0 polls and a release flag the others poll, with bounded waits:
-// a wait that exceeds its spin limit sets an error flag and every workgroup
-// leaves.
+// Reductions are deterministic and are barriers themselves (barrier_sum):
+// workgroup 0 adds the workgroups' sums in a fixed order and publishes the
+// result, so every workgroup takes the same branch.  Waits are bounded: one
+// that exceeds its spin limit sets an error flag and the workgroup leaves,
+// and the others leave when theirs do.
 //
 // Coherence without cache maintenance: every value one workgroup writes and
 // another reads (r in the single form, p, the partial sums) is stored and
@@ -60,16 +57,18 @@ namespace {
 
 constexpr int kMaxR = 16;  // right-hand sides per persistent solve
 
-// Grid barrier state.  Barrier number e (e = 1, 2, ...): every workgroup
-// stores e into its own arrival slot; workgroup 0 polls all slots (one per
-// thread) until every one holds e, then stores e into the release flag,
-// which the other workgroups poll.  Plain coherent stores and loads, no
-// read-modify-write on a shared address; the values only grow, so nothing
+// Grid barrier state.  Barrier number e (e = 1, 2, ...) of grid_barrier: every
+// workgroup stores e into its own arrival slot; workgroup 0 polls all slots
+// (one per thread) until every one holds e, then stores e into the release
+// flags, which the other workgroups poll.  Plain coherent stores and loads,
+// no read-modify-write on a shared address; the values only grow, so nothing
 // is reset between barriers of one solve.
 constexpr int kMaxGrid = 4096;
+constexpr int kCopies = 8;  // of what every workgroup polls: one per XCD (workgroups go to XCDs round-robin)
 struct PcgState {
   unsigned arrive[kMaxGrid];  // last barrier each workgroup reached
-  alignas(128) unsigned release;
+  alignas(128) unsigned release[kCopies][32];
+  alignas(128) unsigned long long sums[2][kCopies][2 * kMaxR];  // records of barrier_sum's results
   alignas(128) struct Result {
     unsigned err;              // 1: barrier wait exceeded, 2: non-finite residual
     unsigned iters;            // iterations run
@@ -96,21 +95,25 @@ struct PcgArgs {
   const int* nbr;
   const c64* b;
   c64 *x, *r, *p0, *p1, *w;  // p0, p1 (and r in the single form): coherent accesses only
-  double* part;               // [2][kMaxR][gmax]
+  unsigned long long* rec;    // records of the workgroups' sums: [2][kMaxR][gmax][2] words
   PcgState* st;
 };
 
-// Per-solve state (barrier flags, results); G workgroups.
-__global__ void k_pcg_reset(PcgState* st, int G) {
-  for (int g = threadIdx.x; g < G; g += blockDim.x) st->arrive[g] = 0;
-  if (threadIdx.x == 0) {
-    st->release = 0;
+// Per-solve state (barrier flags, records, results); G workgroups, nrec
+// words of records.
+__global__ void k_pcg_reset(PcgState* st, unsigned long long* rec, int G, int nrec) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < nrec) rec[i] = 0;
+  if (i < G) st->arrive[i] = 0;
+  if (i < 2 * kCopies * 2 * kMaxR) st->sums[0][0][i] = 0;
+  if (i < kCopies) st->release[i][0] = 0;
+  if (i == 0) {
     st->res.err = 0;
     st->res.iters = 0;
   }
-  if (threadIdx.x < kMaxR) {
-    st->res.iters_rhs[threadIdx.x] = 0;
-    st->res.rr[threadIdx.x] = 0.0;
+  if (i < kMaxR) {
+    st->res.iters_rhs[i] = 0;
+    st->res.rr[i] = 0.0;
   }
 }
 
@@ -132,100 +135,158 @@ __device__ __forceinline__ void st_flag(unsigned* p, unsigned v) {
 }
 
 // Grid-wide barrier number `epoch`; false if a wait exceeded its limit (then
-// st->res.err is set) or another workgroup reported an error.
+// st->res.err is set).
 __device__ __forceinline__ bool grid_barrier(PcgState* st, unsigned nblocks, unsigned epoch, unsigned spin_limit) {
-  __shared__ int ok;
   __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have completed
   __syncthreads();
   int good = 1;
+  unsigned it = 0;
+  auto wait_for = [&](const unsigned* p) {
+    while (good && ld_flag(p) < epoch) {
+      __builtin_amdgcn_s_sleep(1);
+      if (++it > spin_limit) good = 0;
+    }
+  };
   if (blockIdx.x == 0) {
-    // master: wait until every workgroup has arrived, then release
-    unsigned it = 0;
-    for (;;) {
-      int mine = 1;
-      for (unsigned g = 1 + threadIdx.x; g < nblocks; g += kCT) mine &= ld_flag(&st->arrive[g]) >= epoch;
-      if (__syncthreads_and(mine)) break;
-      __builtin_amdgcn_s_sleep(1);
-      if (++it > spin_limit) {
-        good = 0;
-        break;
-      }
-    }
+    for (unsigned g = 1 + threadIdx.x; g < nblocks; g += kCT) wait_for(&st->arrive[g]);
+    good = __syncthreads_and(good);
+    if (good && threadIdx.x < kCopies) st_flag(&st->release[threadIdx.x][0], epoch);
+  } else {
     if (threadIdx.x == 0) {
-      __builtin_amdgcn_s_waitcnt(0);
-      st_flag(&st->release, epoch);
+      st_flag(&st->arrive[blockIdx.x], epoch);
+      wait_for(&st->release[blockIdx.x % kCopies][0]);
     }
-  } else if (threadIdx.x == 0) {
-    st_flag(&st->arrive[blockIdx.x], epoch);
-    unsigned it = 0;
-    while (ld_flag(&st->release) < epoch) {
-      __builtin_amdgcn_s_sleep(1);
-      if (++it > spin_limit) {
-        good = 0;
-        break;
-      }
-    }
+    good = __syncthreads_and(good);
   }
-  if (threadIdx.x == 0) {
-    if (!good) st_flag(&st->res.err, 1u);
-    ok = good && ld_flag(&st->res.err) == 0;
-  }
-  __syncthreads();
-  return ok != 0;
+  if (!good && threadIdx.x == 0) st_flag(&st->res.err, 1u);
+  return good != 0;
 }
 
-// This workgroup's partial of right-hand side r (r < nr) into buffer `buf`.
-// v[q] is the thread's sum for right-hand side q (single form: kMaxR
-// registers), or, in the batched form, acc0 / acc1 are the thread's sums for
-// its two element slots e = tid and tid + kCT of every site (right-hand
-// sides e / nvec), summed through LDS in a fixed order.
-__device__ __forceinline__ void store_partials_slots(double acc0, double acc1, int nr, int nvec, double* part, int buf,
-                                                     int gmax, double* lds /* 2 kCT */) {
+// A double and the epoch it belongs to in two 64-bit words, each half of the
+// value beside the epoch: a reader that finds the epoch in both has the
+// value, whatever order the words became visible in.
+__device__ __forceinline__ void put_record(unsigned long long* p, double v, unsigned epoch) {
+  const unsigned long long bits = __builtin_bit_cast(unsigned long long, v);
+  __hip_atomic_store(p, (bits << 32) | epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p + 1, (bits & 0xffffffff00000000ull) | epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Whether the words hold the value of `epoch`.
+__device__ __forceinline__ bool record_value(unsigned long long lo, unsigned long long hi, unsigned epoch, double* v) {
+  *v = __builtin_bit_cast(double, (hi & 0xffffffff00000000ull) | (lo >> 32));
+  return (unsigned)lo == epoch && (unsigned)hi == epoch;
+}
+__device__ __forceinline__ unsigned long long ld_word(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The sum of records g = lane, lane + 64, ... < n of the array p, eight loads
+// at a time in flight (false after spin_limit polls; `it` counts them).
+__device__ __forceinline__ bool sum_records(const unsigned long long* p, int n, int lane, unsigned epoch, double* sum,
+                                            unsigned& it, unsigned spin_limit) {
+  constexpr int U = 8;
+  double s = 0.0;
+  for (int g0 = lane; g0 < n; g0 += 64 * U) {
+    for (;;) {
+      unsigned long long lo[U], hi[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const size_t g = min(g0 + 64 * u, n - 1);
+        lo[u] = ld_word(p + 2 * g);
+        hi[u] = ld_word(p + 2 * g + 1);
+      }
+      bool all = true;
+      double t = 0.0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        double x;
+        all = record_value(lo[u], hi[u], epoch, &x) && all;
+        t += g0 + 64 * u < n ? x : 0.0;
+      }
+      if (all) {
+        s += t;
+        break;
+      }
+      if (++it > spin_limit) return false;
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  *sum = s;
+  return true;
+}
+
+// The barrier of the reductions: thread r < nr of every workgroup brings its
+// workgroup's sum v for right-hand side r, and out[r] (LDS) holds the grid's
+// sums afterwards.  A workgroup's sum is its arrival: workgroup 0 reads every
+// workgroup's records (wave w the right-hand sides w, w + 8, ..., in a fixed
+// order, so the result is the same in every run) and publishes each sum as
+// another record, in one copy per XCD, for which thread r of the others
+// waits.  Two round trips through memory; with arrival flags, a release flag
+// and every workgroup then summing all partials itself it took four, and the
+// partials' loads grew with the square of the grid.  Records alternate
+// between two buffers: one of epoch e + 2 is written only after its writer
+// has seen a sum of e + 1, hence after workgroup 0 has read e, and a sum of
+// e + 2 only after every workgroup's record of e + 2, hence after all have
+// read the sum of e.
+__device__ __forceinline__ bool barrier_sum(PcgState* st, unsigned long long* rec, int gmax, int nr, unsigned epoch,
+                                            unsigned spin_limit, double v, double* out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have completed
+  __syncthreads();
+  unsigned long long* buf = rec + (size_t)(epoch & 1) * kMaxR * gmax * 2;
+  unsigned long long* sums = st->sums[epoch & 1][0];
+  if ((int)threadIdx.x < nr) put_record(buf + ((size_t)threadIdx.x * gmax + blockIdx.x) * 2, v, epoch);
+  int good = 1;
+  unsigned it = 0;
+  if (blockIdx.x == 0) {
+    for (int r = wave; r < nr && good; r += kCT / 64) {
+      double s = 0.0;
+      good = sum_records(buf + (size_t)r * gmax * 2, gridDim.x, lane, epoch, &s, it, spin_limit);
+      s = wave_sum(s);
+      if (__all(good)) {
+        if (lane < kCopies) put_record(sums + (size_t)lane * 2 * kMaxR + 2 * r, s, epoch);
+        if (lane == 0) out[r] = s;
+      }
+    }
+  } else if ((int)threadIdx.x < nr) {
+    double s = 0.0;
+    const unsigned long long* p = sums + (size_t)(blockIdx.x % kCopies) * 2 * kMaxR + 2 * threadIdx.x;
+    while (!record_value(ld_word(p), ld_word(p + 1), epoch, &s)) {
+      if (++it > spin_limit) {
+        good = 0;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    out[threadIdx.x] = s;
+  }
+  good = __syncthreads_and(good);
+  if (!good && threadIdx.x == 0) st_flag(&st->res.err, 1u);
+  return good != 0;
+}
+
+// This workgroup's sum for right-hand side r in thread r (r < nr), from the
+// threads' sums acc0 / acc1 for their two element slots e = tid and tid + kCT
+// of every site (right-hand sides e / nvec), through LDS in a fixed order.
+__device__ __forceinline__ double slot_sum(double acc0, double acc1, int nr, int nvec, double* lds /* 2 kCT */) {
   lds[threadIdx.x] = acc0;
   lds[kCT + threadIdx.x] = acc1;
   __syncthreads();
-  if (threadIdx.x < nr) {
-    double s = 0.0;
+  double s = 0.0;
+  if ((int)threadIdx.x < nr) {
     const int e0 = threadIdx.x * nvec;
     for (int e = e0; e < e0 + nvec; ++e) s += lds[e];
-    __hip_atomic_store(part + ((size_t)buf * kMaxR + threadIdx.x) * gmax + blockIdx.x, s, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
   }
-  __syncthreads();
+  return s;
 }
 
-__device__ __forceinline__ void store_partials_one(double v, double* part, int buf, int gmax, double* lds /* 8 */) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// The workgroup's sum of v in thread 0.
+__device__ __forceinline__ double one_sum(double v, double* lds /* 8 */) {
   const double s = wave_sum(v);
-  if (lane == 0) lds[wave] = s;
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
+  double t = 0.0;
+  if (threadIdx.x == 0)
     for (int w = 0; w < kCT / 64; ++w) t += lds[w];
-    __hip_atomic_store(part + (size_t)buf * kMaxR * gmax + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __syncthreads();
-}
-
-// out[r] = sum over all workgroups' partials of buffer `buf` (the same
-// fixed order in every workgroup), r < nr.
-__device__ __forceinline__ void sum_partials(double* part, int buf, int nr, int gmax, double* out,
-                                             double* lds /* kMaxR * 8 */) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int r = 0; r < nr; ++r) {
-    double s = 0.0;
-    for (int g = threadIdx.x; g < (int)gridDim.x; g += kCT)
-      s += __hip_atomic_load(part + ((size_t)buf * kMaxR + r) * gmax + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s = wave_sum(s);
-    if (lane == 0) lds[r * 8 + wave] = s;
-  }
-  __syncthreads();
-  if (threadIdx.x < nr) {
-    double s = 0.0;
-    for (int w = 0; w < kCT / 64; ++w) s += lds[threadIdx.x * 8 + w];
-    out[threadIdx.x] = s;
-  }
-  __syncthreads();
+  return t;
 }
 
 // Results of one solve, written by workgroup 0, thread 0 (after the last
@@ -262,10 +323,7 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
   __shared__ __align__(16) unsigned char red_raw[kRedBytes];
   __shared__ c64 s_in[kStencil * kMaxNvec];  // the site's operand at its neighbours
   __shared__ double s_tmp[8];
-  __shared__ double s_rr[kMaxR], s_bb[kMaxR], s_pap[kMaxR];
-  __shared__ unsigned s_it[kMaxR];
-  __shared__ float s_beta;
-  __shared__ double s_alpha;
+  __shared__ double s_rr, s_pap;
   const int G = gridDim.x, wg = blockIdx.x, tid = threadIdx.x;
   const int Nc = A.Nc, nvec = A.nvec;
 
@@ -280,33 +338,26 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
       st_coherent(A.p1 + idx, cmk(0.f, 0.f));
       acc += (double)bv.re * bv.re + (double)bv.im * bv.im;
     }
-  int buf = 0;
   unsigned epoch = 0;
-  store_partials_one(acc, A.part, buf, A.gmax, s_tmp);
-  if (!grid_barrier(A.st, G, ++epoch, A.spin_limit)) return flag_error(A.st, A.accumulate);
-  sum_partials(A.part, buf, 1, A.gmax, s_rr, s_tmp);
-  buf ^= 1;
-  if (tid == 0) {
-    s_bb[0] = s_rr[0];
-    s_beta = 0.f;
-    s_it[0] = 0;
-  }
-  __syncthreads();
+  if (!barrier_sum(A.st, A.rec, A.gmax, 1, ++epoch, A.spin_limit, one_sum(acc, s_tmp), &s_rr))
+    return flag_error(A.st, A.accumulate);
+  double rr = s_rr;  // the same in every thread
+  const double bb = rr;
+  float be = 0.f;
 
   int k = 0;
   for (;; ++k) {
     // uniform stopping test (every workgroup holds the same sums)
-    if (!isfinite(s_rr[0])) {
+    if (!isfinite(rr)) {
       if (tid == 0) __hip_atomic_store(&A.st->res.err, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       break;
     }
-    if (s_rr[0] <= A.tol2 * s_bb[0] || k >= A.maxiter) break;
+    if (rr <= A.tol2 * bb || k >= A.maxiter) break;
     c64* pk = (k & 1) ? A.p1 : A.p0;
     const c64* pprev = (k & 1) ? A.p0 : A.p1;
 
     // ---- phase A: p_k on own sites, w = A p_k, partial <p_k, w>
     acc = 0.0;
-    const float be = s_beta;
     for (int a = wg; a < Nc; a += G) {
       for (int e = tid; e < nvec; e += kCT) {
         const size_t idx = (size_t)a * nvec + e;
@@ -337,16 +388,13 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
         acc += (double)pv.re * wv.re + (double)pv.im * wv.im;
       }
     }
-    store_partials_one(acc, A.part, buf, A.gmax, s_tmp);
-    if (!grid_barrier(A.st, G, ++epoch, A.spin_limit)) return flag_error(A.st, A.accumulate);
-    sum_partials(A.part, buf, 1, A.gmax, s_pap, s_tmp);
-    buf ^= 1;
-    if (tid == 0) s_alpha = s_pap[0] != 0.0 ? s_rr[0] / s_pap[0] : 0.0;
-    __syncthreads();
+    if (!barrier_sum(A.st, A.rec, A.gmax, 1, ++epoch, A.spin_limit, one_sum(acc, s_tmp), &s_pap))
+      return flag_error(A.st, A.accumulate);
+    const double pap = s_pap;
 
     // ---- phase B: x += alpha p_k, r -= alpha w; partial |r|^2
     acc = 0.0;
-    const float al = (float)s_alpha;
+    const float al = (float)(pap != 0.0 ? rr / pap : 0.0);
     for (int a = wg; a < Nc; a += G)
       for (int e = tid; e < nvec; e += kCT) {
         const size_t idx = (size_t)a * nvec + e;
@@ -358,20 +406,15 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
         st_coherent(A.r + idx, rv);
         acc += (double)rv.re * rv.re + (double)rv.im * rv.im;
       }
-    store_partials_one(acc, A.part, buf, A.gmax, s_tmp);
-    if (!grid_barrier(A.st, G, ++epoch, A.spin_limit)) return flag_error(A.st, A.accumulate);
-    sum_partials(A.part, buf, 1, A.gmax, s_pap, s_tmp);  // s_pap reused for |r_{k+1}|^2
-    buf ^= 1;
-    if (tid == 0) {
-      const double old = s_rr[0], nw = s_pap[0];
-      s_beta = old > 0.0 ? (float)(nw / old) : 0.f;
-      s_rr[0] = nw;
-      s_it[0] = (unsigned)(k + 1);
-    }
-    __syncthreads();
+    const double old = rr;
+    if (!barrier_sum(A.st, A.rec, A.gmax, 1, ++epoch, A.spin_limit, one_sum(acc, s_tmp), &s_rr))
+      return flag_error(A.st, A.accumulate);
+    rr = s_rr;
+    be = old > 0.0 ? (float)(rr / old) : 0.f;
   }
+  const unsigned it = (unsigned)k;
   if (wg == 0 && tid == 0 && A.accumulate) A.st->tot.err |= ld_flag(&A.st->res.err);
-  finish(A.st, k, 1, s_rr, s_it, A.accumulate);
+  finish(A.st, k, 1, &rr, &it, A.accumulate);
 }
 
 // Several right-hand sides (2 <= nr <= 16; NT = 1 for nr <= 8, 2 above).
@@ -423,12 +466,10 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
       acc1 += (double)bv.re * bv.re + (double)bv.im * bv.im;
     }
   }
-  int buf = 0;
-  unsigned epoch = 0;
-  store_partials_slots(acc0, acc1, nr, nvec, A.part, buf, A.gmax, s_tmp);
-  if (!grid_barrier(A.st, G, ++epoch, A.spin_limit)) return flag_error(A.st, A.accumulate);
-  sum_partials(A.part, buf, nr, A.gmax, s_rr, s_tmp);
-  buf ^= 1;
+  unsigned epoch = 0;   // of grid_barrier
+  unsigned repoch = 0;  // of barrier_sum
+  if (!barrier_sum(A.st, A.rec, A.gmax, nr, ++repoch, A.spin_limit, slot_sum(acc0, acc1, nr, nvec, s_tmp), s_rr))
+    return flag_error(A.st, A.accumulate);
   if (tid < nr) {
     s_bb[tid] = s_rr[tid];
     s_act[tid] = 1;
@@ -486,10 +527,8 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
         acc1 += (double)pv.re * wv.re + (double)pv.im * wv.im;
       }
     }
-    store_partials_slots(acc0, acc1, nr, nvec, A.part, buf, A.gmax, s_tmp);
-    if (!grid_barrier(A.st, G, ++epoch, A.spin_limit)) return flag_error(A.st, A.accumulate);
-    sum_partials(A.part, buf, nr, A.gmax, s_sum, s_tmp);
-    buf ^= 1;
+    if (!barrier_sum(A.st, A.rec, A.gmax, nr, ++repoch, A.spin_limit, slot_sum(acc0, acc1, nr, nvec, s_tmp), s_sum))
+      return flag_error(A.st, A.accumulate);
     if (tid < nr) s_alpha[tid] = (s_act[tid] && s_sum[tid] != 0.0) ? s_rr[tid] / s_sum[tid] : 0.0;
     __syncthreads();
 
@@ -522,10 +561,8 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
         }
       }
     }
-    store_partials_slots(acc0, acc1, nr, nvec, A.part, buf, A.gmax, s_tmp);
-    if (!grid_barrier(A.st, G, ++epoch, A.spin_limit)) return flag_error(A.st, A.accumulate);
-    sum_partials(A.part, buf, nr, A.gmax, s_sum, s_tmp);
-    buf ^= 1;
+    if (!barrier_sum(A.st, A.rec, A.gmax, nr, ++repoch, A.spin_limit, slot_sum(acc0, acc1, nr, nvec, s_tmp), s_sum))
+      return flag_error(A.st, A.accumulate);
     if (tid < nr) {
       const double old = s_rr[tid], nw = s_sum[tid];
       s_beta[tid] = (s_act[tid] && old > 0.0) ? (float)(nw / old) : 0.f;
@@ -642,14 +679,15 @@ int pcg_dispatch(int mode, int mt, bool k32, int nr, bool query, const PcgArgs* 
 // complex64 each), the partial sums and the barrier / result state.
 struct PcgWork {
   c64 *r, *p0, *p1, *w;
-  double* part;
+  unsigned long long* rec;
   PcgState* st;
 };
 
+constexpr size_t rec_bytes(int G) { return sizeof(unsigned long long) * 4 * kMaxR * (size_t)G; }
 constexpr size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 size_t work_bytes(size_t n, int G) {
-  return 4 * align256(n * sizeof(c64)) + align256(sizeof(double) * 2 * kMaxR * (size_t)G) + align256(sizeof(PcgState));
+  return 4 * align256(n * sizeof(c64)) + align256(rec_bytes(G)) + align256(sizeof(PcgState));
 }
 
 PcgWork carve(unsigned char* base, size_t n, int G) {
@@ -659,8 +697,8 @@ PcgWork carve(unsigned char* base, size_t n, int G) {
   w.p0 = reinterpret_cast<c64*>(base + v);
   w.p1 = reinterpret_cast<c64*>(base + 2 * v);
   w.w = reinterpret_cast<c64*>(base + 3 * v);
-  w.part = reinterpret_cast<double*>(base + 4 * v);
-  w.st = reinterpret_cast<PcgState*>(base + 4 * v + align256(sizeof(double) * 2 * kMaxR * (size_t)G));
+  w.rec = reinterpret_cast<unsigned long long*>(base + 4 * v);
+  w.st = reinterpret_cast<PcgState*>(base + 4 * v + align256(rec_bytes(G)));
   return w;
 }
 
@@ -714,9 +752,10 @@ int launch_solve(hdcg* h, const PcgWork& wk, int mode, int mt, int G, int mprec,
   a.p0 = wk.p0;
   a.p1 = wk.p1;
   a.w = wk.w;
-  a.part = wk.part;
+  a.rec = wk.rec;
   a.st = wk.st;
-  hipLaunchKernelGGL(k_pcg_reset, dim3(1), dim3(256), 0, st, a.st, G);
+  const int nrec = 4 * kMaxR * G;
+  hipLaunchKernelGGL(k_pcg_reset, dim3((std::max(nrec, 512) + 255) / 256), dim3(256), 0, st, a.st, a.rec, G, nrec);
   HDCG_HIP(hipGetLastError());
   return pcg_dispatch(mode, mt, use_k32(mode, nv), nr, false, &a, G, nullptr, st);
 }
@@ -744,7 +783,7 @@ PcgWork handle_work(hdcg* h) {
   w.p0 = h->cw[1].as<c64>();
   w.p1 = h->cw[2].as<c64>();
   w.w = h->cw[5].as<c64>();
-  w.part = h->pcg_part.as<double>();
+  w.rec = h->pcg_part.as<unsigned long long>();
   w.st = h->pcg_state.as<PcgState>();
   return w;
 }
@@ -752,7 +791,7 @@ PcgWork handle_work(hdcg* h) {
 int ensure_handle_work(hdcg* h, int nr, int G) {
   const size_t n = (size_t)h->Nc * h->nvec * nr;
   for (int i : {0, 1, 2, 5}) HDCG_TRY(h->cw[i].ensure(n * sizeof(c128)));
-  HDCG_TRY(h->pcg_part.ensure(sizeof(double) * 2 * kMaxR * (size_t)G));
+  HDCG_TRY(h->pcg_part.ensure(rec_bytes(G)));
   HDCG_TRY(h->pcg_state.ensure(sizeof(PcgState)));
   return DWF_OK;
 }
@@ -789,7 +828,7 @@ int coarse_cg_persistent_deferred(hdcg* h, int mprec, c64* x, const c64* b, int 
   if (!plan(h, mprec, nr, &mode, &mt, &G)) return DWF_OK;
   if ((mprec == DWF_BF16 || mprec == DWF_F16) && !mfma_ready(h, mprec)) return DWF_OK;
   const size_t n = (size_t)h->Nc * h->nvec * nr;
-  if (h->cw[5].bytes < n * sizeof(c128) || h->pcg_part.bytes < sizeof(double) * 2 * kMaxR * (size_t)G ||
+  if (h->cw[5].bytes < n * sizeof(c128) || h->pcg_part.bytes < rec_bytes(G) ||
       h->pcg_state.bytes < sizeof(PcgState))
     return DWF_OK;
   HDCG_TRY(launch_solve(h, handle_work(h), mode, mt, G, mprec, x, b, nr, tol, maxiter, st, 1));
