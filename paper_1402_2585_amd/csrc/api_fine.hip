@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "fine_op.h"
+#include "blas.h"
 
 namespace hdk {
 
@@ -59,6 +60,8 @@ static int cg_one(dwf_op* op, c128* x, const c128* b, double tol, int maxiter, i
   double* rr_slot[2] = {sc + 0, sc + 1};
   double* pap = sc + 2;
   double* bb = sc + 3;
+  double* alpha = sc + 4;
+  const Red red{op->red.partials.as<double>(), op->red.counters.as<unsigned>()};
   double* hp = op->pinned;  // [kRing + 4]
   hipEvent_t ev[kRing];
   for (int i = 0; i < kRing; ++i) HDCG_HIP(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming));
@@ -130,11 +133,11 @@ static int cg_one(dwf_op* op, c128* x, const c128* b, double tol, int maxiter, i
       if (it + k < maxiter) {
         double* cur = rr_slot[k & 1];
         double* nxt = rr_slot[(k + 1) & 1];
-        // w = H p with pap = <p, H p> = |M_pc p|^2 fused into stage 2
-        CG_TRY(launch_mpcdagmpc<double>(op, w, p, 1, stream, pap));
-        CG_TRY(launch_cg_update<double>(op, x, r, p, w, cur, pap, nullptr, nxt, 1, stream));
-        CG_TRY(launch_xpay<double>(op, p, r, nxt, cur, nullptr, 1, stream));
-        CG_HIP(hipMemcpyAsync(hp + (k % kRing), nxt, sizeof(double), hipMemcpyDeviceToHost, stream));
+        // pap = <p, H p> = |M_pc p|^2 in stage 2, r -= alpha H p and |r|^2
+        // (to the host too) in the last stage
+        CG_TRY(launch_cg_residual<double>(op, r, p, 1, CgStep{cur, nullptr, 0.0, pap, alpha, nxt, hp + (k % kRing)},
+                                          stream));
+        CG_TRY(b_cg_xp(red, x, p, r, n, 1, alpha, nxt, cur, false, nullptr, stream));
         CG_HIP(hipEventRecord(ev[k % kRing], stream));
         ++k;
       }
@@ -178,13 +181,14 @@ static int cg_inner64(dwf_op* op, c64* e, const c64* f, double rtol, int maxiter
                       hipStream_t stream) {
   constexpr int kLag = 2, kRing = 8;
   const size_t n = op->field_elems(1);
-  for (int i = 0; i < 3; ++i) HDCG_TRY(op->mgw[i].ensure(n * sizeof(c64)));
+  for (int i = 0; i < 2; ++i) HDCG_TRY(op->mgw[i].ensure(n * sizeof(c64)));
   c64* r = op->mgw[0].as<c64>();
   c64* p = op->mgw[1].as<c64>();
-  c64* w = op->mgw[2].as<c64>();
   double* sc = op->red.results.as<double>() + 128;
   double* rr_slot[2] = {sc + 8, sc + 9};
   double* pap = sc + 10;
+  double* alpha = sc + 11;
+  const Red red{op->red.partials.as<double>(), op->red.counters.as<unsigned>()};
   double* hp = op->pinned;
   HDCG_HIP(hipMemsetAsync(e, 0, n * sizeof(c64), stream));
   HDCG_HIP(hipMemcpyAsync(r, f, n * sizeof(c64), hipMemcpyDeviceToDevice, stream));
@@ -204,11 +208,8 @@ static int cg_inner64(dwf_op* op, c64* e, const c64* f, double rtol, int maxiter
     if (k < maxiter) {
       double* cur = rr_slot[k & 1];
       double* nxt = rr_slot[(k + 1) & 1];
-      rc = launch_mpcdagmpc<float>(op, w, p, 1, stream, pap);
-      if (rc == DWF_OK) rc = launch_cg_update<float>(op, e, r, p, w, cur, pap, nullptr, nxt, 1, stream);
-      if (rc == DWF_OK) rc = launch_xpay<float>(op, p, r, nxt, cur, nullptr, 1, stream);
-      if (rc == DWF_OK && hipMemcpyAsync(hp + (k % kRing), nxt, sizeof(double), hipMemcpyDeviceToHost, stream) != hipSuccess)
-        rc = fail(DWF_ERR_HIP, "copy of the residual norm failed");
+      rc = launch_cg_residual<float>(op, r, p, 1, CgStep{cur, nullptr, 0.0, pap, alpha, nxt, hp + (k % kRing)}, stream);
+      if (rc == DWF_OK) rc = b_cg_xp(red, e, p, r, n, 1, alpha, nxt, cur, false, nullptr, stream);
       if (rc == DWF_OK && hipEventRecord(ev[k % kRing], stream) != hipSuccess) rc = fail(DWF_ERR_HIP, "event record failed");
       ++k;
     }
@@ -245,12 +246,12 @@ static int cg_mixed_one(dwf_op* op, c128* x, const c128* b, double tol, double i
   const size_t n = op->field_elems(1);
   HDCG_TRY(ensure_reducer(op));
   for (int i = 0; i < 2; ++i) HDCG_TRY(op->cgw[i].ensure(n * sizeof(c128)));
+  HDCG_TRY(op->mgw[2].ensure(n * sizeof(c64)));
   HDCG_TRY(op->mgw[3].ensure(n * sizeof(c64)));
-  HDCG_TRY(op->mgw[4].ensure(n * sizeof(c64)));
   c128* r = op->cgw[0].as<c128>();
   c128* t = op->cgw[1].as<c128>();
-  c64* f = op->mgw[3].as<c64>();
-  c64* e = op->mgw[4].as<c64>();
+  c64* f = op->mgw[2].as<c64>();
+  c64* e = op->mgw[3].as<c64>();
   double* sc = op->red.results.as<double>() + 128;
   double* hp = op->pinned;
   HDCG_TRY(launch_norm2<double>(op, b, 1, sc + 12, stream));

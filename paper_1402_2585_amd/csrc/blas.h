@@ -37,6 +37,16 @@ int b_update(Red red, cplx<R>* x, cplx<R>* r, const cplx<R>* p, const cplx<R>* w
 template <typename R>
 int b_xpay(Red red, cplx<R>* p, const cplx<R>* y, size_t n, int nrhs, const double* num, bool cnum,
            const double* den, double sign, double* pp, hipStream_t st, int dstr = 1);
+// The parts of a CG step on fields of T (c128, c64 or bf16c) outside the hop
+// kernels; alpha per right-hand side from the device.
+// x += alpha p (x0: x = alpha p), then p = r + (num / den) p ; pp = |p|^2 (if pp)
+template <typename T>
+int b_cg_xp(Red red, T* x, T* p, const T* r, size_t n, int nrhs, const double* alpha, const double* num,
+            const double* den, bool x0, double* pp, hipStream_t st);
+// r -= alpha (w + lam p) ; rr = |r|^2, also to rr_host (nullable, pinned)
+template <typename T>
+int b_cg_r(Red red, T* r, const T* p, const T* w, size_t n, int nrhs, const double* alpha, double lam, double* rr,
+           double* rr_host, hipStream_t st);
 // y = a x + b y over `total` elements (host coefficients)
 template <typename R>
 int b_axpby(cplx<R>* y, const cplx<R>* x, double a, double b, size_t total, hipStream_t st);
@@ -52,13 +62,6 @@ int b_scale_copy(cplx<Ry>* y, const cplx<Rx>* x, const double* v, bool invsqrt, 
 template <typename R>
 int b_zero(cplx<R>* y, size_t total, hipStream_t st);
 
-// The real-coefficient forms of the above on fields stored in 16 bits
-// (bf16c): FP32 arithmetic on each loaded value, results rounded to nearest
-// even on store, FP64 accumulation of the norms.
-int b_norm2(Red red, const bf16c* x, size_t n, int nrhs, double* res, hipStream_t st);
-int b_update(Red red, bf16c* x, bf16c* r, const bf16c* p, const bf16c* w, size_t n, int nrhs,
-             const double* num, const double* den, const double* den2, double lam, double* rr,
-             hipStream_t st, int mode = 0);
 // fixed-count CG on 16-bit fields: r = p = 16-bit b (complex64 [site][12][Ls]
 // to the 16-bit [site][Ls][12] layout), rr = |r|^2 of the stored values; and
 // its last step x_out (complex64 layout) = 16-bit(x + alpha p), x == nullptr
@@ -67,8 +70,5 @@ int b_mirs16_init(Red red, bf16c* r, bf16c* p, const c64* b, size_t n, int nrhs,
                   hipStream_t st);
 int b_mirs16_last(c64* x_out, const bf16c* x, const bf16c* p, size_t n, int nrhs, int Ls, const double* num,
                   const double* den, const double* den2, double lam, hipStream_t st);
-int b_xpay(Red red, bf16c* p, const bf16c* y, size_t n, int nrhs, const double* num,
-           const double* den, double* pp, hipStream_t st);
-int b_zero(bf16c* y, size_t total, hipStream_t st);
 
 }  // namespace hdk

@@ -66,7 +66,7 @@ __device__ __forceinline__ void reset_ticket(unsigned* c) {
   __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <int NQ>
-__device__ __forceinline__ void reduce_out(double (&v)[NQ], Red red, int rhs, double* res) {
+__device__ __forceinline__ void reduce_out(double (&v)[NQ], Red red, int rhs, double* res, double* host = nullptr) {
   __shared__ double lds[NQ * 16];
   __shared__ int last;
   constexpr int nslots = kMaxPartials / NQ;
@@ -112,6 +112,7 @@ __device__ __forceinline__ void reduce_out(double (&v)[NQ], Red red, int rhs, do
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) res[NQ * rhs + q] = s[q];
+    if (host) __hip_atomic_store(host + rhs, s[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -123,7 +124,8 @@ __device__ __forceinline__ void reduce_out(double (&v)[NQ], Red red, int rhs, do
 constexpr int kFinT = 1024;
 template <int NQ>
 __global__ void __launch_bounds__(kFinT) k_finalize(const double* __restrict__ partials, int nslots,
-                                                    int nblocks, size_t rstride, double* __restrict__ res) {
+                                                    int nblocks, size_t rstride, double* __restrict__ res,
+                                                    FinCg cg) {
   const int rhs = blockIdx.x;
   const double* p = partials + (size_t)rhs * rstride;
   __shared__ double lds[kFinT / 64];
@@ -144,6 +146,11 @@ __global__ void __launch_bounds__(kFinT) k_finalize(const double* __restrict__ p
       double r = 0.0;
       for (int w = 0; w < kFinT / 64; ++w) r += lds[w];
       res[NQ * rhs + q] = r;
+      if (NQ == 1 && cg.also) __hip_atomic_store(cg.also + rhs, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (NQ == 1 && cg.alpha) {
+        const double d = cg.lam != 0.0 ? r + cg.lam * cg.den2[rhs] : r;
+        cg.alpha[rhs] = d == 0.0 ? 0.0 : cg.num[rhs] / d;
+      }
     }
     __syncthreads();
   }
@@ -331,6 +338,90 @@ k_xpay(T* __restrict__ p, const T* __restrict__ y, size_t n, const double* num, 
   }
 }
 
+// The rest of a CG step whose residual the hop has updated: x += alpha p and
+// p = r + beta p in one pass (five fields instead of the six that an update
+// of x and one of p would move), alpha as formed with <p, H p>, beta = num / den.
+template <typename T, bool X0>
+__global__ void __launch_bounds__(kT)
+k_cg_xp(T* __restrict__ x, T* __restrict__ p, const T* __restrict__ r, size_t n, const double* alpha,
+        const double* num, const double* den, Red red, double* pp) {
+  using R = typename St<T>::R;
+  const int rhs = blockIdx.y;
+  const size_t off = rhs * n;
+  double bre, bim;
+  coef(num, false, den, nullptr, 0.0, rhs, bre, bim, 1);
+  const R a = (R)alpha[rhs], b = (R)bre;
+  constexpr int V = Vec<T>::V;
+  x += off;
+  p += off;
+  r += off;
+  double acc = 0.0;
+  stream2(n / V, [&](const auto& at) {
+    constexpr int U = sizeof(at) / sizeof(at[0]);
+    cplx<R> xv[U][V], pv[U][V], rv[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      Vec<T>::ld(p, at[u], pv[u]);
+      Vec<T>::ld(r, at[u], rv[u]);
+      if constexpr (!X0) Vec<T>::ld(x, at[u], xv[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        xv[u][k] = X0 ? a * pv[u][k] : xv[u][k] + a * pv[u][k];
+        pv[u][k] = rv[u][k] + b * pv[u][k];
+        acc += nrm(pv[u][k]);
+      }
+      Vec<T>::st(x, at[u], xv[u]);
+      Vec<T>::st(p, at[u], pv[u]);
+    }
+  });
+  if (pp) {
+    double v[1] = {acc};
+    reduce_out<1>(v, red, rhs, pp);
+  }
+}
+
+// r -= alpha (w + lam p), rr = |r|^2 (rr_host, nullable: pinned memory that
+// takes it too)
+template <typename T>
+__global__ void __launch_bounds__(kT)
+k_cg_r(T* __restrict__ r, const T* __restrict__ p, const T* __restrict__ w, size_t n, const double* alpha, double lam,
+       Red red, double* rr, double* rr_host) {
+  using R = typename St<T>::R;
+  const int rhs = blockIdx.y;
+  const size_t off = rhs * n;
+  const R a = (R)alpha[rhs], l = (R)lam;
+  constexpr int V = Vec<T>::V;
+  r += off;
+  p += off;
+  w += off;
+  double acc = 0.0;
+  stream2(n / V, [&](const auto& at) {
+    constexpr int U = sizeof(at) / sizeof(at[0]);
+    cplx<R> rv[U][V], pv[U][V], wv[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      Vec<T>::ld(r, at[u], rv[u]);
+      Vec<T>::ld(w, at[u], wv[u]);
+      if (lam != 0.0) Vec<T>::ld(p, at[u], pv[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        if (lam != 0.0) wv[u][k] = wv[u][k] + l * pv[u][k];
+        rv[u][k] = rv[u][k] - a * wv[u][k];
+        acc += nrm(rv[u][k]);
+      }
+      Vec<T>::st(r, at[u], rv[u]);
+    }
+  });
+  double v[1] = {acc};
+  reduce_out<1>(v, red, rhs, rr, rr_host);
+}
+
 // Fixed-count CG on 16-bit fields (M_IRS), first step: r = p = bf16(b) for
 // b complex64 [site][12][Ls] and r, p 16-bit [site][Ls][12] (rounded to
 // nearest even as every 16-bit store), and rr[rhs] = |r|^2 of the rounded
@@ -442,12 +533,12 @@ __global__ void k_zero(T* __restrict__ y, size_t total) {
 #define LAUNCH_CHECK() HDCG_HIP(hipGetLastError())
 
 int launch_finalize(int nq, const double* partials, int nslots, int nblocks, int nrhs, double* res,
-                    hipStream_t st, size_t rstride) {
+                    hipStream_t st, size_t rstride, const FinCg& cg) {
   if (nblocks > nslots || (size_t)nq * nslots > rstride) return fail(DWF_ERR_ARG, "too many partial sums");
   if (nq == 1)
-    hipLaunchKernelGGL((k_finalize<1>), dim3(nrhs), dim3(kFinT), 0, st, partials, nslots, nblocks, rstride, res);
+    hipLaunchKernelGGL((k_finalize<1>), dim3(nrhs), dim3(kFinT), 0, st, partials, nslots, nblocks, rstride, res, cg);
   else
-    hipLaunchKernelGGL((k_finalize<2>), dim3(nrhs), dim3(kFinT), 0, st, partials, nslots, nblocks, rstride, res);
+    hipLaunchKernelGGL((k_finalize<2>), dim3(nrhs), dim3(kFinT), 0, st, partials, nslots, nblocks, rstride, res, cg);
   LAUNCH_CHECK();
   return DWF_OK;
 }
@@ -499,6 +590,27 @@ int xpay_t(Red red, T* p, const T* y, size_t n, int nrhs, const double* num, boo
   return DWF_OK;
 }
 template <typename T>
+int b_cg_xp(Red red, T* x, T* p, const T* r, size_t n, int nrhs, const double* alpha, const double* num,
+            const double* den, bool x0, double* pp, hipStream_t st) {
+  if (n % Vec<T>::V) return fail(DWF_ERR_ARG, "16-bit fields need a multiple of 4 complex values");
+  if (nrhs > 64) return fail(DWF_ERR_ARG, "nrhs > 64");
+  const dim3 grid(nblocks(n, nrhs), nrhs);
+  if (x0) hipLaunchKernelGGL((k_cg_xp<T, true>), grid, dim3(kT), 0, st, x, p, r, n, alpha, num, den, red, pp);
+  else hipLaunchKernelGGL((k_cg_xp<T, false>), grid, dim3(kT), 0, st, x, p, r, n, alpha, num, den, red, pp);
+  LAUNCH_CHECK();
+  return DWF_OK;
+}
+template <typename T>
+int b_cg_r(Red red, T* r, const T* p, const T* w, size_t n, int nrhs, const double* alpha, double lam, double* rr,
+           double* rr_host, hipStream_t st) {
+  if (n % Vec<T>::V) return fail(DWF_ERR_ARG, "16-bit fields need a multiple of 4 complex values");
+  if (nrhs > 64) return fail(DWF_ERR_ARG, "nrhs > 64");
+  hipLaunchKernelGGL((k_cg_r<T>), dim3(nblocks(n, nrhs), nrhs), dim3(kT), 0, st, r, p, w, n, alpha, lam, red, rr,
+                     rr_host);
+  LAUNCH_CHECK();
+  return DWF_OK;
+}
+template <typename T>
 int zero_t(T* y, size_t total, hipStream_t st) {
   if (total % Vec<T>::V) return fail(DWF_ERR_ARG, "16-bit fields need a multiple of 4 complex values");
   hipLaunchKernelGGL((k_zero<T>), dim3(nblocks(total)), dim3(kT), 0, st, y, total);
@@ -526,14 +638,6 @@ int b_xpay(Red red, cplx<R>* p, const cplx<R>* y, size_t n, int nrhs, const doub
            const double* den, double sign, double* pp, hipStream_t st, int dstr) {
   return xpay_t(red, p, y, n, nrhs, num, cnum, den, sign, pp, st, dstr);
 }
-int b_norm2(Red red, const bf16c* x, size_t n, int nrhs, double* res, hipStream_t st) {
-  return norm2_t(red, x, n, nrhs, res, st);
-}
-int b_update(Red red, bf16c* x, bf16c* r, const bf16c* p, const bf16c* w, size_t n, int nrhs,
-             const double* num, const double* den, const double* den2, double lam, double* rr,
-             hipStream_t st, int mode) {
-  return update_t(red, x, r, p, w, n, nrhs, num, false, den, den2, lam, rr, st, 1, mode);
-}
 int b_mirs16_init(Red red, bf16c* r, bf16c* p, const c64* b, size_t n, int nrhs, int Ls, double* rr,
                   hipStream_t st) {
   if (n % 12 || (n / 12) % Ls) return fail(DWF_ERR_ARG, "M_IRS: field size not a whole number of site rows");
@@ -550,11 +654,6 @@ int b_mirs16_last(c64* x_out, const bf16c* x, const bf16c* p, size_t n, int nrhs
   LAUNCH_CHECK();
   return DWF_OK;
 }
-int b_xpay(Red red, bf16c* p, const bf16c* y, size_t n, int nrhs, const double* num,
-           const double* den, double* pp, hipStream_t st) {
-  return xpay_t(red, p, y, n, nrhs, num, false, den, 1.0, pp, st, 1);
-}
-int b_zero(bf16c* y, size_t total, hipStream_t st) { return zero_t(y, total, st); }
 template <typename R>
 int b_axpby(cplx<R>* y, const cplx<R>* x, double a, double b, size_t total, hipStream_t st) {
   hipLaunchKernelGGL((k_axpby<R>), dim3(nblocks(total)), dim3(kT), 0, st, y, x, (R)a, (R)b, total);
@@ -580,6 +679,15 @@ template <typename R>
 int b_zero(cplx<R>* y, size_t total, hipStream_t st) {
   return zero_t(y, total, st);
 }
+
+#define INST_CG(T)                                                                                                   \
+  template int b_cg_xp<T>(Red, T*, T*, const T*, size_t, int, const double*, const double*, const double*, bool,      \
+                          double*, hipStream_t);                                                                      \
+  template int b_cg_r<T>(Red, T*, const T*, const T*, size_t, int, const double*, double, double*, double*,           \
+                         hipStream_t);
+INST_CG(c128)
+INST_CG(c64)
+INST_CG(bf16c)
 
 #define INST(R)                                                                                   \
   template int b_norm2<R>(Red, const cplx<R>*, size_t, int, double*, hipStream_t);               \

@@ -265,9 +265,19 @@ __device__ __forceinline__ void store_partial(const double (&v)[NQ], double* par
   }
 }
 
+// What a finalize launch (nq = 1) forms beside the sums: also (nullable,
+// pinned host memory) takes them too; alpha (nullable) takes num / (sum + lam
+// den2), or 0 for a zero denominator (den2 only for lam != 0).
+struct FinCg {
+  double* also = nullptr;
+  const double *num = nullptr, *den2 = nullptr;
+  double lam = 0.0;
+  double* alpha = nullptr;
+};
+
 // res[nq * rhs + q] = sum_{i < nblocks} partials[rhs * rstride + q * nslots + i]
 int launch_finalize(int nq, const double* partials, int nslots, int nblocks, int nrhs, double* res,
-                    hipStream_t st, size_t rstride = kMaxPartials);
+                    hipStream_t st, size_t rstride = kMaxPartials, const FinCg& cg = FinCg());
 
 // Map blockIdx.x so that each of the 8 XCDs (workgroups are dispatched to
 // XCDs round-robin) receives one contiguous range of tiles: neighbouring

@@ -55,7 +55,7 @@ struct dwf_op {
   hdk::DevBuf pw128, pw64;        // closed-form table on the device
   hdk::DevBuf tmp[3][3];          // [c128, c64, bf16][t_e, chi, s_e] work fields
   hdk::DevBuf cgw[4];             // CG work fields (c128): r, p, w, spare
-  hdk::DevBuf mgw[5];             // mixed-precision CG work fields (c64): r, p, w, source, correction
+  hdk::DevBuf mgw[4];             // mixed-precision CG work fields (c64): r, p, source, correction
   hdk::DevBuf msw[4];             // multi-shift CG: p_j (c128), r, w, device scalars
   hdk::Reducer red;
   hdk::DevBuf hop_part;           // fused-norm partials of the hop stage: [rhs][workgroups]
@@ -103,6 +103,28 @@ int launch_mpc(dwf_op* op, T* out, const T* in, bool dagger, int nrhs, hipStream
 template <typename R, typename T = cplx<R>>
 int launch_mpcdagmpc(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t stream,
                      double* pap_result /*nullable: <in, H in> = |M_pc in|^2 per rhs*/);
+
+// One CG step on H + lam, but for x and the next p: pap = <p, H p>, alpha =
+// num / (pap + lam den2) (0 for a zero denominator), r -= alpha (H p + lam p),
+// rr = |r|^2.  The residual is updated by the last hop stage as it forms H p,
+// which is never stored (Ls <= 16; one update kernel otherwise): of a step's
+// 19 field transfers three less, and four launches less (7 iterations of
+// M_IRS in complex64 on 16^3 x 32 x 16: 3.34 -> 2.91 ms, a sixteenth of it
+// the last step's unneeded half of H; complex128 CG on 8^3 x 16 x 8: 51 ->
+// 45 us a step).  Device
+// doubles, one per right-hand side; den2 (= |p|^2) only for lam != 0; rr_host,
+// nullable: pinned memory that takes rr too.
+struct CgStep {
+  const double* num;
+  const double* den2;
+  double lam;
+  double *pap, *alpha, *rr, *rr_host;
+};
+template <typename R, typename T = cplx<R>>
+int launch_cg_residual(dwf_op* op, T* r, const T* p, int nrhs, const CgStep& cg, hipStream_t stream);
+// pap = <p, H p> alone: the last step of a fixed count needs no H p
+template <typename R, typename T = cplx<R>>
+int launch_cg_norm(dwf_op* op, const T* p, int nrhs, double* pap, hipStream_t stream);
 
 // BLAS-1 (FP64 accumulation); results are device doubles, one per rhs.
 template <typename R, typename T = cplx<R>>

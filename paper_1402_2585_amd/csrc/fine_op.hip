@@ -20,6 +20,7 @@
 // Epilogues (the fifth-dimension factors of M_pc, Sec. IV):
 //   EPI_INV  out = M_5^-1 (Dh in)          or M_5^-+ (Dh^+ in)   [dense in s]
 //   EPI_SUB  out = M_5 c - 1/4 (Dh in)      or M_5^+ c - 1/4 (Dh^+ in)
+//   EPI_RES  out -= a (w + lam p), w the result of EPI_SUB (Ls <= 16: a CG step's residual)
 // hop_kernel's EPI_INV stages the hop result in LDS and solves the Ls x Ls
 // system per (site, component) with the O(Ls) recurrence of the closed-form
 // inverse.
@@ -27,10 +28,11 @@
 #include <type_traits>
 
 #include "fine_op.h"
+#include "blas.h"
 
 namespace hdk {
 
-enum { EPI_INV = 0, EPI_SUB = 1 };
+enum { EPI_INV = 0, EPI_SUB = 1, EPI_RES = 2 };
 
 // ------------------------------------------------------------ coordinates --
 struct Site {
@@ -324,7 +326,11 @@ struct HopArgs {
   // Mobius C_5 = b5 + c5 K (K: P+ from s-1, P- from s+1, -mass at the wrap)
   double alpha, beta, ia, kap, b5, c5, mass;
   double kp[4];       // kap^1, kap^2, kap^4, kap^8
-  double* partials;   // EPI_SUB norm: [rhs][pstride] per-workgroup partials (nullable)
+  // EPI_RES: a per right-hand side (device), lam and p (nullable: no shift)
+  const double* cg_alpha;
+  const void* cg_p;
+  double cg_lam;
+  double* partials;   // norm of the output (not EPI_INV): [rhs][pstride] per-workgroup partials (nullable)
   size_t pstride;     // = number of workgroups
   unsigned* counters; // [rhs]
   double* result;     // [rhs]
@@ -861,7 +867,9 @@ static void launch_split_ls(bool dagger, int epi, dim3 grid, dim3 block, size_t 
                             const T* in, const T* center, const cplx<R>* G, const R* pw, const HopArgs& A) {
 #define HDCG_SPLIT(D, E) \
   hipLaunchKernelGGL((hop_split_kernel<R, D, E, LS, MOB, T, LOOP>), grid, block, lds, stream, out, in, center, G, pw, A)
-  if (epi == EPI_INV) {
+  if (epi == EPI_RES) {
+    HDCG_SPLIT(true, EPI_RES);  // the last stage of H
+  } else if (epi == EPI_INV) {
     if (dagger) HDCG_SPLIT(true, EPI_INV);
     else HDCG_SPLIT(false, EPI_INV);
   } else {
@@ -901,7 +909,9 @@ static void launch_march_ls(bool dagger, int epi, dim3 grid, dim3 block, size_t 
                             const T* in, const T* center, const cplx<R>* G, const R* pw, const HopArgs& A) {
 #define HDCG_MARCH(D, E) \
   hipLaunchKernelGGL((hop_march_kernel<R, D, E, LS, T>), grid, block, lds, stream, out, in, center, G, pw, A)
-  if (epi == EPI_INV) {
+  if (epi == EPI_RES) {
+    HDCG_MARCH(true, EPI_RES);
+  } else if (epi == EPI_INV) {
     if (dagger) HDCG_MARCH(true, EPI_INV);
     else HDCG_MARCH(false, EPI_INV);
   } else {
@@ -1026,9 +1036,19 @@ static const int* hop_order_table(dwf_op* op, const HopArgs& A, int kind, hipStr
 template <typename R, typename T = cplx<R>>
 static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
                       bool dagger, int epi, int out_parity, int nrhs, hipStream_t stream,
-                      double* norm_result) {
+                      double* norm_result, const CgStep* cg = nullptr, const void* cg_p = nullptr,
+                      double* alpha = nullptr) {
   const Geom& g = op->g;
   HopArgs A;
+  // a CG step: stage 2 ends with its alpha, the last stage updates r with it
+  A.cg_alpha = alpha;
+  A.cg_p = cg && cg->lam != 0.0 ? cg_p : nullptr;
+  A.cg_lam = cg ? cg->lam : 0.0;
+  FinCg fin;
+  if (epi == EPI_RES)
+    fin.also = cg->rr_host;
+  else if (cg)
+    fin = {nullptr, cg->num, cg->den2, cg->lam, alpha};
   A.g = g;
   A.out_parity = out_parity;
   // linear order: four waves of the split kernel, or one wave's worth of
@@ -1126,7 +1146,7 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
     else if (g.Ls == 12) launch_march_ls<R, T, 12>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
     else launch_march_ls<R, T, 8>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
     HDCG_HIP(hipGetLastError());
-    if (norm_result) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride);
+    if (norm_result) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride, fin);
     return DWF_OK;
   }
   dim3 grid(nwg, (nrhs + A.rg - 1) / A.rg), block(threads);
@@ -1148,7 +1168,7 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   else
     launch_hop<R, 2, false, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
   HDCG_HIP(hipGetLastError());
-  if (norm_result) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride);
+  if (norm_result) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride, fin);
   return DWF_OK;
 }
 
@@ -1297,6 +1317,35 @@ static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t s
   return DWF_OK;
 }
 
+// The CG operations on H (declared with CgStep).  Scratch for the autotuner's
+// first call and, for Ls > 16, for w: the third work field.
+template <typename R, typename T>
+int launch_cg_norm(dwf_op* op, const T* p, int nrhs, double* pap, hipStream_t stream) {
+  const int pi = tmp_index(std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>());
+  HDCG_TRY((ensure_tmp(op, std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>(), nrhs)));
+  HDCG_TRY((select_shape<R, T>(op, op->tmp[pi][2].as<T>(), p, nrhs, stream)));
+  return launch_mpc<R, T>(op, op->tmp[pi][1].as<T>(), p, false, nrhs, stream, pap);
+}
+
+template <typename R, typename T>
+int launch_cg_residual(dwf_op* op, T* r, const T* p, int nrhs, const CgStep& cg, hipStream_t stream) {
+  const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>(), pi = tmp_index(prec);
+  if (kSMajor<T> && (!aligned16(r) || !aligned16(p))) return fail(DWF_ERR_ARG, "16-bit fields must be 16-byte aligned");
+  HDCG_TRY(ensure_tmp(op, prec, nrhs));
+  T* te = op->tmp[pi][0].as<T>();
+  T* chi = op->tmp[pi][1].as<T>();
+  T* w = op->tmp[pi][2].as<T>();
+  HDCG_TRY((select_shape<R, T>(op, w, p, nrhs, stream)));
+  HDCG_TRY((hop_launch<R, T>(op, te, p, nullptr, false, EPI_INV, 0, nrhs, stream, nullptr)));
+  HDCG_TRY((hop_launch<R, T>(op, chi, te, p, false, EPI_SUB, 1, nrhs, stream, cg.pap, &cg, nullptr, cg.alpha)));
+  HDCG_TRY((hop_launch<R, T>(op, te, chi, nullptr, true, EPI_INV, 0, nrhs, stream, nullptr)));
+  if (op->g.Ls <= 16)
+    return hop_launch<R, T>(op, r, te, chi, true, EPI_RES, 1, nrhs, stream, cg.rr, &cg, p, cg.alpha);
+  HDCG_TRY((hop_launch<R, T>(op, w, te, chi, true, EPI_SUB, 1, nrhs, stream, nullptr)));
+  return b_cg_r(Red{op->red.partials.as<double>(), op->red.counters.as<unsigned>()}, r, p, w, op->field_elems(1), nrhs,
+                cg.alpha, cg.lam, cg.rr, cg.rr_host, stream);
+}
+
 template <typename R, typename T>
 int launch_mpcdagmpc(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t stream, double* pap_result) {
   HDCG_TRY((select_shape<R, T>(op, out, in, nrhs, stream)));
@@ -1397,6 +1446,12 @@ int launch_convert(Td* dst, const Ts* src, size_t n, hipStream_t stream) {
                                hipStream_t);
 INST(double)
 INST(float)
+template int launch_cg_norm<double, c128>(dwf_op*, const c128*, int, double*, hipStream_t);
+template int launch_cg_norm<float, c64>(dwf_op*, const c64*, int, double*, hipStream_t);
+template int launch_cg_norm<float, bf16c>(dwf_op*, const bf16c*, int, double*, hipStream_t);
+template int launch_cg_residual<double, c128>(dwf_op*, c128*, const c128*, int, const CgStep&, hipStream_t);
+template int launch_cg_residual<float, c64>(dwf_op*, c64*, const c64*, int, const CgStep&, hipStream_t);
+template int launch_cg_residual<float, bf16c>(dwf_op*, bf16c*, const bf16c*, int, const CgStep&, hipStream_t);
 template int launch_mpc<float, bf16c>(dwf_op*, bf16c*, const bf16c*, bool, int, hipStream_t, double*);
 template int launch_mpcdagmpc<float, bf16c>(dwf_op*, bf16c*, const bf16c*, int, hipStream_t, double*);
 template int launch_norm2<float, bf16c>(dwf_op*, const bf16c*, int, double*, hipStream_t);

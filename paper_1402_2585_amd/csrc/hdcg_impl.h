@@ -59,9 +59,9 @@ struct hdcg {
   hdk::DevBuf gram, rinv;     // [Nc][nvec][nvec] c128 Cholesky-QR work
   hdk::DevBuf flag;           // int error flag
   hdk::DevBuf cw[10];         // coarse work vectors (c64/c128); 6-9: truncated-operator preconditioner
-  hdk::DevBuf fw64[12];       // fine c64 work fields: 0-7 solver, 8-10 fine CG
+  hdk::DevBuf fw64[12];       // fine c64 work fields: 0-7 solver, 8-9 fine CG
   hdk::DevBuf fw128[3];       // fine c128 work fields
-  hdk::DevBuf fw16[4];        // fine 16-bit work fields of M_IRS: x, r, p, w
+  hdk::DevBuf fw16[3];        // fine 16-bit work fields of M_IRS: x, r, p
   hdk::DevBuf scal;           // device scalars
   hdk::DevBuf probe_c;        // coarse probe vectors for the build
   hdk::DevBuf mf_rho, mf_smax;      // per-matrix scales of the 16-bit coarse storage

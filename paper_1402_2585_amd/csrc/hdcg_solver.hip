@@ -36,7 +36,7 @@ int check_m1_prec(int prec, int nvec) {
 
 // device scalar slots, 128 doubles each (room for 64 right-hand sides x 2)
 enum {
-  S_RR0, S_RR1, S_PAP, S_PP,                       // fine CG
+  S_RR0, S_RR1, S_PAP, S_PP, S_CG_ALPHA,           // fine CG
   S_CRR0, S_CRR1, S_CPAP, S_CPP, S_CPR, S_CWY,      // coarse CG, coarse ADEF1
   S_ARR, S_APR, S_AWY, S_ARY0, S_ARY1, S_AINIT, S_APW,  // A-DEF2 (own slots: M_IRS runs inside)
   S_ORR, S_OBB,                                     // outer loop
@@ -169,16 +169,16 @@ int fine_cg(hdcg* h, c64* x, const c64* b, int nr, double lam, int fixed, double
             int* iters, hipStream_t st) {
   dwf_op* op = h->op;
   const size_t n = fine_elems(h);
-  for (int i = 8; i <= 10; ++i) HDCG_TRY(ensure_fine64(h, i, nr));
+  for (int i = 8; i <= 9; ++i) HDCG_TRY(ensure_fine64(h, i, nr));
   c64* r = h->fw64[8].as<c64>();
   c64* p = h->fw64[9].as<c64>();
-  c64* w = h->fw64[10].as<c64>();
   const Red red = red_of(op);
   double* rr[2] = {slot(h, S_RR0), slot(h, S_RR1)};
   double* pap = slot(h, S_PAP);
   double* pp = slot(h, S_PP);
-  // a fixed count writes x in its first step (x = alpha p) and skips the r,
-  // p and norm work of its last one, whose results nothing reads
+  double* alpha = slot(h, S_CG_ALPHA);
+  // a fixed count writes x in its first step (x = alpha p) and skips all but
+  // <p, H p> and x in its last one, whose other results nothing reads
   if (fixed <= 0) HDCG_TRY(b_zero<float>(x, n * nr, st));
   HDCG_HIP(hipMemcpyAsync(r, b, n * nr * sizeof(c64), hipMemcpyDeviceToDevice, st));
   HDCG_HIP(hipMemcpyAsync(p, b, n * nr * sizeof(c64), hipMemcpyDeviceToDevice, st));
@@ -198,17 +198,20 @@ int fine_cg(hdcg* h, c64* x, const c64* b, int nr, double lam, int fixed, double
   while (!done && k < limit) {
     double* cur = rr[k & 1];
     double* nxt = rr[(k + 1) & 1];
+    const bool last = fixed > 0 && k == fixed - 1, x0 = fixed > 0 && k == 0;
+    double* p2 = lam != 0.0 ? pp : nullptr;
     {
       Phase ph(h, PH_FINE_SP, st);
-      HDCG_TRY(launch_mpcdagmpc<float>(op, w, p, nr, st, pap));
+      if (last) HDCG_TRY(launch_cg_norm<float>(op, p, nr, pap, st));
+      else HDCG_TRY(launch_cg_residual<float>(op, r, p, nr, CgStep{cur, p2, lam, pap, alpha, nxt, nullptr}, st));
     }
     {
       Phase ph(h, PH_LINALG, st);
-      const bool last = fixed > 0 && k == fixed - 1;
-      const int mode = (fixed > 0 && k == 0 ? kUpdX0 : 0) | (last ? kUpdXOnly : 0);
-      HDCG_TRY(b_update<float>(red, x, r, p, w, n, nr, cur, false, pap, lam != 0.0 ? pp : nullptr, lam,
-                               last ? nullptr : nxt, st, 1, mode));
-      if (!last) HDCG_TRY(b_xpay<float>(red, p, r, n, nr, nxt, false, cur, 1.0, lam != 0.0 ? pp : nullptr, st));
+      if (last)
+        HDCG_TRY(b_update<float>(red, x, r, p, r, n, nr, cur, false, pap, p2, lam, nullptr, st, 1,
+                                 kUpdXOnly | (x0 ? kUpdX0 : 0)));
+      else
+        HDCG_TRY(b_cg_xp(red, x, p, r, n, nr, alpha, nxt, cur, x0, p2, st));
     }
     ++k;
     if (fixed > 0) continue;
@@ -238,15 +241,15 @@ int fine_cg_bf16(hdcg* h, c64* x_out, const c64* b, int nr, double lam, int fixe
   dwf_op* op = h->op;
   const size_t n = fine_elems(h);
   if (fixed <= 0) return b_zero<float>(x_out, n * nr, st);
-  for (int i = 0; i < 4; ++i) HDCG_TRY(h->fw16[i].ensure(n * nr * sizeof(bf16c)));
+  for (int i = 0; i < 3; ++i) HDCG_TRY(h->fw16[i].ensure(n * nr * sizeof(bf16c)));
   bf16c* x = h->fw16[0].as<bf16c>();
   bf16c* r = h->fw16[1].as<bf16c>();
   bf16c* p = h->fw16[2].as<bf16c>();
-  bf16c* w = h->fw16[3].as<bf16c>();
   const Red red = red_of(op);
   double* rr[2] = {slot(h, S_RR0), slot(h, S_RR1)};
   double* pap = slot(h, S_PAP);
   double* pp = lam != 0.0 ? slot(h, S_PP) : nullptr;
+  double* alpha = slot(h, S_CG_ALPHA);
   {
     // r = p = b in 16 bits, |r|^2; x is first written by the first step
     Phase ph(h, PH_CONVERT, st);
@@ -258,15 +261,15 @@ int fine_cg_bf16(hdcg* h, c64* x_out, const c64* b, int nr, double lam, int fixe
     double* nxt = rr[(k + 1) & 1];
     {
       Phase ph(h, PH_FINE_SP, st);
-      HDCG_TRY((launch_mpcdagmpc<float, bf16c>(op, w, p, nr, st, pap)));
+      if (k == fixed - 1) HDCG_TRY((launch_cg_norm<float, bf16c>(op, p, nr, pap, st)));
+      else HDCG_TRY((launch_cg_residual<float, bf16c>(op, r, p, nr, CgStep{cur, pp, lam, pap, alpha, nxt, nullptr}, st)));
     }
     Phase ph(h, PH_LINALG, st);
     if (k == fixed - 1) {
       // the last step: x_out = x + alpha p, rounded as the stored x would be
       HDCG_TRY(b_mirs16_last(x_out, k == 0 ? nullptr : x, p, n, nr, op->g.Ls, cur, pap, pp, lam, st));
     } else {
-      HDCG_TRY(b_update(red, x, r, p, w, n, nr, cur, pap, pp, lam, nxt, st, k == 0 ? kUpdX0 : 0));
-      HDCG_TRY(b_xpay(red, p, r, n, nr, nxt, cur, pp, st));
+      HDCG_TRY(b_cg_xp(red, x, p, r, n, nr, alpha, nxt, cur, k == 0, pp, st));
     }
   }
   return DWF_OK;

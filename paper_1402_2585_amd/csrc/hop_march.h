@@ -96,6 +96,13 @@ __device__ __forceinline__ void march_halo(Tri<T>& a, Tri<T>& b, const T* __rest
   b = y;
 }
 
+// EPI_RES: this lane's values of r and p (if wanted)
+template <typename T, int COL>
+__device__ __forceinline__ void march_step(Tri<T>& r, Tri<T>& p, const T* rf, const T* pf, int v, int off, int cs) {
+  r.ld(rf + (size_t)v * COL + off, cs);
+  if (pf) p.ld(pf + (size_t)v * COL + off, cs);
+}
+
 // Grid: tiles x right-hand sides.  A.fold: blockIdx.x runs over both, the
 // right-hand sides of a tile one after another on the same XCD, which then
 // serves the links of all but the first from its L2.  by, bz >= 2.
@@ -159,15 +166,16 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
   T* const ring = reinterpret_cast<T*>(smem_raw);
   cplx<R>* const links = reinterpret_cast<cplx<R>*>(smem_raw + links_at) + p * kLinkLd;
   const T* inr = in + rhs * A.field;
-  const T* cen = EPI == EPI_SUB ? center + rhs * A.field : nullptr;
+  const T* cen = EPI != EPI_INV ? center + rhs * A.field : nullptr;
   const int e0 = q.row * LS + q.s;  // this lane's first element of the column and of the links
   const int at_z = xh + g.Xh * (y + g.Y * zn), at_row = g.Xh * (y + g.Y * z);
 
   // b: the output site of the pair is the odd-x one; the pair's own column is
   // then its x- neighbour and x+ is the next pair's
   const int par = y + z + A.out_parity;
-  Tri<T> hau, hal, hbu, hbl, cx, cy;
-  hau.zero(), hal.zero(), hbu.zero(), hbl.zero(), cx.zero(), cy.zero();
+  Tri<T> hau, hal, hbu, hbl, cx, cy, rv, pv;
+  hau.zero(), hal.zero(), hbu.zero(), hbl.zero(), cx.zero(), cy.zero(), rv.zero(), pv.zero();
+  const T* pstep = EPI == EPI_RES && A.cg_p ? static_cast<const T*>(A.cg_p) + rhs * A.field : nullptr;
   {
     const Share<T> oa = march_col<T, LS>(inr, own + plane * (t0 == 0 ? g.T - 1 : t0 - 1), e0);
     const Share<T> ob = march_col<T, LS>(inr, own + plane * t0, e0);
@@ -177,7 +185,8 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
     const bool ha = zt ? edge_z : (b ? xl == A.bx - 1 : xl == 0);
     march_halo<T, col>(hau, hal, inr, (zt ? at_z : at_row + (b ? xp : xm)) + plane * t0, offu, offl, cs, ha);
     march_halo<T, col>(hbu, hbl, inr, at_b + plane * t0, offu, offl, cs, halo_b);
-    if (EPI == EPI_SUB) march_halo<T, col>(cx, cy, cen, own + plane * t0, offo, offn, cs, true);
+    if (EPI != EPI_INV) march_halo<T, col>(cx, cy, cen, own + plane * t0, offo, offn, cs, true);
+    if (EPI == EPI_RES) march_step<T, col>(rv, pv, out + rhs * A.field, pstep, own + plane * t0, offo, cs);
     march_put<T, LS>(ring + p * col, e0, oa);
     march_put<T, LS>(ring + slot_sz + p * col, e0, ob);
     march_put<T, LS>(ring + 2 * slot_sz + p * col, e0, oc);
@@ -239,7 +248,8 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
     cplx<R> acc[3];
     split_finish<R, DAG, EPI, LS, false>(acc, U, L, cx, cy, q, Ls, A, coef);
     {
-      if (EPI == EPI_SUB && active) {
+      if (EPI == EPI_RES) split_residual<R, T>(acc, rv, pv, A, rhs);
+      if (EPI != EPI_INV && active) {
 #pragma unroll
         for (int c = 0; c < 3; ++c)
           nrm += (double)acc[c].re * (double)acc[c].re + (double)acc[c].im * (double)acc[c].im;
@@ -249,7 +259,8 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
         // the plane behind is read by its own wave alone, and that is done
         march_put<T, LS>(ring + s_prev * slot_sz + p * col, e0, oc);
         march_put_links<R, LS>(links, e0, lk);
-        if (EPI == EPI_SUB) march_halo<T, col>(cx, cy, cen, own + plane * t1, offo, offn, cs, true);
+        if (EPI != EPI_INV) march_halo<T, col>(cx, cy, cen, own + plane * t1, offo, offn, cs, true);
+        if (EPI == EPI_RES) march_step<T, col>(rv, pv, out + rhs * A.field, pstep, own + plane * t1, offo, cs);
       }
     }
     lds_barrier();
@@ -258,7 +269,7 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
     s_cur = s_next;
     s_next = s_free;
   }
-  if (EPI == EPI_SUB && A.partials) {
+  if (EPI != EPI_INV && A.partials) {
     double vv[1] = {nrm};
     __shared__ double red[16];
     block_sum<1>(vv, red);

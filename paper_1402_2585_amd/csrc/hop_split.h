@@ -302,7 +302,7 @@ __device__ __forceinline__ void split_m5inv(cplx<R> (&v)[3], const SplitLane& q,
 // The row's spin of the stage's output from the rows' parts U, L of the hop:
 // reduction over the rows, then the fifth-dimension factors (wrap: split_wrap's
 // coefficient, EPI_INV; cx, cy: the
-// centre field at s and at the slice M_5 couples it to, EPI_SUB).
+// centre field at s and at the slice M_5 couples it to, the other stages).
 template <typename R, bool DAG, int EPI, int LS, bool MOB, typename T>
 __device__ __forceinline__ void split_finish(cplx<R> (&acc)[3], const cplx<R> (&U)[3], const cplx<R> (&L)[3],
                                              const Tri<T>& cx, const Tri<T>& cy, const SplitLane& q, int Ls,
@@ -325,6 +325,18 @@ __device__ __forceinline__ void split_finish(cplx<R> (&acc)[3], const cplx<R> (&
     const R f = wall ? -m * be : be;
 #pragma unroll
     for (int k = 0; k < 3; ++k) acc[k] = al * cx.get(k) + f * cy.get(k) - qu * acc[k];
+  }
+}
+
+// acc <- r - a (acc + lam p): the residual of a CG step from w = acc
+template <typename R, typename T>
+__device__ __forceinline__ void split_residual(cplx<R> (&acc)[3], const Tri<T>& r, const Tri<T>& p, const HopArgs& A,
+                                               int rhs) {
+  const R a = (R)A.cg_alpha[rhs], l = (R)A.cg_lam;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if (A.cg_p) acc[k] = acc[k] + l * p.get(k);
+    acc[k] = r.get(k) - a * acc[k];
   }
 }
 
@@ -386,7 +398,7 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
       const int vloc = LS > 8 || active ? want : 0;
       Site c;
       const int v = hop_site(A, wg, vloc, c);
-      Tri<T> u[4], l[4], cx, cy;
+      Tri<T> u[4], l[4], cx, cy, rv, pv;
       Tri<T> us[C5IN ? 4 : 1], ls[C5IN ? 4 : 1];
       const int s_dn = q.s > 0 ? q.s - 1 : Ls - 1, s_up = q.s + 1 < Ls ? q.s + 1 : 0;
       cplx<R> lk[NL];
@@ -423,7 +435,7 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
             }
           }
         }
-        if (EPI == EPI_SUB) {
+        if (EPI != EPI_INV) {
           const T* cen = center + rhs * A.field + (size_t)v * col;
           const int sn = (q.upper != DAG) ? s_dn : s_up;
           if constexpr (kSMajor<T>) {
@@ -433,6 +445,11 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
             if (NT && A.nt & 4) cx.ld1(cen + q.spin * 3 * Ls + q.s, Ls); else cx.ld(cen + q.spin * 3 * Ls + q.s, Ls);
             if (NT && A.nt & 4) cy.ld1(cen + q.spin * 3 * Ls + sn, Ls); else cy.ld(cen + q.spin * 3 * Ls + sn, Ls);
           }
+        }
+        if (EPI == EPI_RES) {
+          const size_t at = rhs * A.field + (size_t)v * col + (kSMajor<T> ? q.s * 12 + q.spin * 3 : q.spin * 3 * Ls + q.s);
+          rv.ld(out + at, Ls);
+          if (A.cg_p) pv.ld(static_cast<const T*>(A.cg_p) + at, Ls);
         }
         if constexpr (LS > 0) {
           if (!LOOP || rr == 0) {
@@ -472,7 +489,8 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
       }
       cplx<R> acc[3];
       split_finish<R, DAG, EPI, LS, MOB>(acc, U, L, cx, cy, q, Ls, A, wrap);
-      if (EPI == EPI_SUB && active) {
+      if (EPI == EPI_RES) split_residual<R, T>(acc, rv, pv, A, rhs);
+      if (EPI != EPI_INV && active) {
 #pragma unroll
         for (int k = 0; k < 3; ++k)
           nrm += (double)acc[k].re * (double)acc[k].re + (double)acc[k].im * (double)acc[k].im;
@@ -485,7 +503,7 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
           tri_st<T>(o + q.spin * 3 * Ls + q.s, Ls, acc, A.nt & 1);
       }
     }
-    if (EPI == EPI_SUB && A.partials) {
+    if (EPI != EPI_INV && A.partials) {
       double vv[1] = {nrm};
       __shared__ double red[2][16];  // two: a wave may be one right-hand side ahead of thread 0
       block_sum<1>(vv, red[rr & 1]);
