@@ -85,6 +85,7 @@ struct PcgState {
 
 struct PcgArgs {
   int Nc, nvec, nr, maxiter, ksteps, gmax;
+  int kl;                     // one right-hand side, complex64: rows of the operator kept in LDS
   int accumulate;             // 1: add this solve's counts to the totals (deferred solves)
   double tol2;
   unsigned spin_limit;
@@ -313,6 +314,64 @@ __device__ __forceinline__ void flag_error(PcgState* st, int accumulate) {
   if (accumulate && blockIdx.x == 0 && threadIdx.x == 0) st->tot.err |= ld_flag(&st->res.err) | 1u;
 }
 
+// The complex64 mat-vec of a solve with one right-hand side is bound by
+// reading the operator (191 MB a step on 512 sites x 24, from the Infinity
+// Cache), which never changes: the part of a workgroup's first site that its
+// registers and LDS have room for is read once and kept.  A thread owns the
+// rows q = part + parts i of column j (capply_site); rows i < kKeep stay in
+// its registers, the next A.kl in LDS ([row][thread], after s_in), and the
+// rest is streamed, its first loads issued before the kept rows' arithmetic.
+// The sums run in capply_site's order.  512 sites x 24, 28 steps: 1000 -> 875
+// us with 8 rows in registers and 14 in LDS (of 93; 16 in registers spill:
+// 960), and 8 rows of loads in flight (12: 897).
+constexpr int kKeep = 8;
+constexpr size_t kPcgLds = 72 * 1024;  // dynamic LDS of a workgroup at most: two fit a CU's 160 KB
+
+template <int U>
+__device__ __forceinline__ void capply_kept(const c64* __restrict__ AT, const c64* in, c64* __restrict__ out, int a,
+                                            int nvec, const c64 (&keep)[kKeep], const c64* cache, int kl, bool kept,
+                                            c64* red) {
+  const int parts = kCT / nvec, K = kStencil * nvec, step = parts * nvec;
+  const int j = threadIdx.x % nvec, part = threadIdx.x / nvec;
+  const int mine = part < parts ? K - part : 0;  // row i is in range for parts * i < mine
+  const unsigned own = part < parts ? threadIdx.x : 0;
+  const c64* Aa = AT + (size_t)a * K * nvec;
+  const c64* x = in + own / nvec;
+  c64 acc = cmk(0.f, 0.f), Av[U];
+  int i0 = kept ? kKeep + kl : 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const c64* row = Aa + (size_t)(i0 + u) * step;
+    Av[u] = parts * (i0 + u) < mine ? row[own] : cmk(0.f, 0.f);
+  }
+  if (kept) {
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i)
+      if (parts * i < mine) cmac(acc, keep[i], x[parts * i]);
+#pragma unroll 4
+    for (int i = 0; i < kl; ++i)
+      if (parts * (kKeep + i) < mine) cmac(acc, cache[i * kCT + threadIdx.x], x[parts * (kKeep + i)]);
+  }
+  for (; parts * i0 < K; i0 += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (parts * (i0 + u) < mine) cmac(acc, Av[u], x[parts * (i0 + u)]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const c64* row = Aa + (size_t)(i0 + U + u) * step;
+      Av[u] = parts * (i0 + U + u) < mine ? row[own] : cmk(0.f, 0.f);
+    }
+  }
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  if (threadIdx.x < nvec) {
+    c64 s = cmk(0.f, 0.f);
+    for (int p = 0; p < parts; ++p) s = s + red[p * nvec + threadIdx.x];
+    out[(size_t)a * nvec + threadIdx.x] = s;
+  }
+  __syncthreads();
+}
+
 // One right-hand side.  MODE 0: complex64 VALU operator; 1: bf16 MFMA;
 // 2: fp16 MFMA (MT M tiles).
 constexpr int kMaxNvec = 64;
@@ -321,7 +380,8 @@ template <int MODE, int MT, bool K32>
 __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k_coarse_cg(PcgArgs A) {
   constexpr int kRedBytes = MODE == 0 ? kCT * (int)sizeof(c64) : 8 * MT * 64 * (int)sizeof(f32x4);
   __shared__ __align__(16) unsigned char red_raw[kRedBytes];
-  __shared__ c64 s_in[kStencil * kMaxNvec];  // the site's operand at its neighbours
+  extern __shared__ __align__(16) unsigned char dyn[];
+  c64* const s_in = reinterpret_cast<c64*>(dyn);  // [kStencil * nvec]: the site's operand at its neighbours
   __shared__ double s_tmp[8];
   __shared__ double s_rr, s_pap;
   const int G = gridDim.x, wg = blockIdx.x, tid = threadIdx.x;
@@ -338,6 +398,18 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
       st_coherent(A.p1 + idx, cmk(0.f, 0.f));
       acc += (double)bv.re * bv.re + (double)bv.im * bv.im;
     }
+  // MODE 0: the kept rows of the first site
+  c64 keep[MODE == 0 ? kKeep : 1];
+  c64* const cache = s_in + kStencil * nvec;
+  if constexpr (MODE == 0) {
+    const int parts = kCT / nvec, part = tid / nvec, K = kStencil * nvec, step = parts * nvec;
+    const int mine = part < parts ? K - part : 0;
+    const c64* Aa = A.AT + (size_t)wg * K * nvec;
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) keep[i] = parts * i < mine ? (Aa + (size_t)i * step)[tid] : cmk(0.f, 0.f);
+    for (int i = 0; i < A.kl; ++i)
+      if (parts * (kKeep + i) < mine) cache[i * kCT + tid] = (Aa + (size_t)(kKeep + i) * step)[tid];
+  }
   unsigned epoch = 0;
   if (!barrier_sum(A.st, A.rec, A.gmax, 1, ++epoch, A.spin_limit, one_sum(acc, s_tmp), &s_rr))
     return flag_error(A.st, A.accumulate);
@@ -377,7 +449,7 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
         __syncthreads();
       }
       if constexpr (MODE == 0) {
-        capply_site<float, 1, 12, true>(A.AT, A.nbr, s_in, A.w, a, Nc, nvec, 1, 0, reinterpret_cast<c64*>(red_raw));
+        capply_kept<8>(A.AT, s_in, A.w, a, nvec, keep, cache, A.kl, a == wg, reinterpret_cast<c64*>(red_raw));
       } else {
         capply_site_mfma<MODE == 1, MT, 1, 8, (K32 ? 2 : (MT >= 3 ? 3 : 4)), true, false, K32>(
             A.F, A.rho, A.smax, A.nbr, s_in, A.w, a, Nc, nvec, 1, A.ksteps, reinterpret_cast<f32x4*>(red_raw));
@@ -613,7 +685,8 @@ int max_grid(int* out) {
     int dev = 0, cus = 0, per = 0;
     HDCG_HIP(hipGetDevice(&dev));
     HDCG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    HDCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel_of<MODE, MT, NT, BATCH, K32>(), kCT, 0));
+    HDCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel_of<MODE, MT, NT, BATCH, K32>(), kCT,
+                                                          BATCH ? 0 : MODE == 0 ? kPcgLds : kStencil * kMaxNvec * sizeof(c64)));
     cached = per * cus;
   }
   *out = cached;
@@ -632,7 +705,8 @@ int pcg_call(bool query, const PcgArgs* a, int G, int* gmax, hipStream_t st) {
   if constexpr (BATCH)
     hipLaunchKernelGGL((k_coarse_cg_mrhs<MODE, MT, NT, K32>), dim3(G), dim3(kCT), 0, st, *a);
   else
-    hipLaunchKernelGGL((k_coarse_cg<MODE, MT, K32>), dim3(G), dim3(kCT), 0, st, *a);
+    hipLaunchKernelGGL((k_coarse_cg<MODE, MT, K32>), dim3(G), dim3(kCT),
+                       sizeof(c64) * (size_t)(kStencil * a->nvec + a->kl * kCT), st, *a);
   HDCG_HIP(hipGetLastError());
   return DWF_OK;
 }
@@ -739,6 +813,12 @@ int launch_solve(hdcg* h, const PcgWork& wk, int mode, int mt, int G, int mprec,
   a.accumulate = accumulate;
   a.ksteps = mfma_ksteps(kStencil * nv);
   a.gmax = G;
+  // rows of the operator kept in LDS: what is left beside s_in
+  a.kl = 0;
+  if (mode == 0 && nr == 1) {
+    const int rows = (kStencil * nv + kCT / nv - 1) / (kCT / nv) - kKeep;
+    a.kl = std::max(0, std::min(rows, (int)((kPcgLds / sizeof(c64) - kStencil * nv) / kCT)));
+  }
   a.tol2 = tol * tol;
   a.spin_limit = 1u << 21;  // >= 50 ms of waiting at 64+ cycles per poll
   a.AT = h->AT64.as<c64>();
