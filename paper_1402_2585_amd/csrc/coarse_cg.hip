@@ -497,8 +497,18 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
 // Element slots: thread tid owns the elements e = tid and e = tid + kCT of
 // every site (e = rhs * nvec + j < nr * nvec <= 2 kCT), so each thread's
 // partial sums belong to two fixed right-hand sides.
-template <int MODE, int MT, int NT, bool K32>
+//
+// STG: where every workgroup has one site and the operand of all right-hand
+// sides at its 81 neighbours fits in LDS, a step is bound by its barriers and
+// by latency, and the operand is p_k = r_k + beta p_{k-1} formed as it is
+// gathered by coherent loads, as in k_coarse_cg: no third barrier to publish
+// p, and no acquire, which would drop the operator from the L2.  (162 sites,
+// 8 vectors, 4 right-hand sides: 391 -> 235 us a solve.)  More sites a
+// workgroup gather p through the caches instead, where 81 sites share it.
+template <int MODE, int MT, int NT, bool K32, bool STG>
 __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k_coarse_cg_mrhs(PcgArgs A) {
+  extern __shared__ __align__(16) unsigned char dyn[];
+  c64* const s_in = reinterpret_cast<c64*>(dyn);  // STG: [nr][kStencil * nvec]
   constexpr int NR0 = 4 * NT;                        // MODE 0: right-hand sides per pass
   constexpr int U0 = NR0 >= 16 ? 2 : (NR0 >= 8 ? 4 : 8);  // and columns in flight
   constexpr int kRedBytes = MODE == 0 ? kCT * NR0 * (int)sizeof(c64) : 8 * MT * NT * 64 * (int)sizeof(f32x4);
@@ -526,15 +536,25 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
     if (has0) {
       const c64 bv = A.b[o0 + so];
       A.x[o0 + so] = cmk(0.f, 0.f);
-      A.r[o0 + so] = bv;
-      st_coherent(A.p0 + o0 + so, bv);
+      if constexpr (STG) {
+        st_coherent(A.r + o0 + so, bv);
+        st_coherent(A.p1 + o0 + so, cmk(0.f, 0.f));
+      } else {
+        A.r[o0 + so] = bv;
+        st_coherent(A.p0 + o0 + so, bv);
+      }
       acc0 += (double)bv.re * bv.re + (double)bv.im * bv.im;
     }
     if (has1) {
       const c64 bv = A.b[o1 + so];
       A.x[o1 + so] = cmk(0.f, 0.f);
-      A.r[o1 + so] = bv;
-      st_coherent(A.p0 + o1 + so, bv);
+      if constexpr (STG) {
+        st_coherent(A.r + o1 + so, bv);
+        st_coherent(A.p1 + o1 + so, cmk(0.f, 0.f));
+      } else {
+        A.r[o1 + so] = bv;
+        st_coherent(A.p0 + o1 + so, bv);
+      }
       acc1 += (double)bv.re * bv.re + (double)bv.im * bv.im;
     }
   }
@@ -546,6 +566,7 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
     s_bb[tid] = s_rr[tid];
     s_act[tid] = 1;
     s_it[tid] = 0;
+    s_beta[tid] = 0.f;
   }
   __syncthreads();
 
@@ -567,27 +588,52 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
     }
     __syncthreads();
     if (!s_any || k >= A.maxiter) break;
-    const c64* pk = (k & 1) ? A.p1 : A.p0;
-    c64* pn = (k & 1) ? A.p0 : A.p1;
+    c64* pk = (k & 1) ? A.p1 : A.p0;
+    c64* pn = (k & 1) ? A.p0 : A.p1;  // p_{k+1}'s, and p_{k-1} (STG)
 
     // ---- phase A: w = A p_k for all right-hand sides, partial <p_k, w>
     // (p_k, published by coherent stores before the barrier, is gathered
     // through the caches after an agent-scope acquire, which drops this
     // XCD's stale lines, so that its 81-fold reuse across the sites hits L2)
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if constexpr (!STG) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     acc0 = acc1 = 0.0;
     for (int ia = wg; ia < Nc; ia += G) {
       const int a = xcd_remap(ia, Nc);  // each XCD owns a contiguous slab (xcd_site)
+      if constexpr (STG) {
+        const int* nb = A.nbr + (size_t)a * kStencil;
+        const int kn = kStencil * nvec, n = nr * kn;
+        for (int e = tid; e < n; e += kCT) {
+          const int q = e / kn, rem = e - q * kn, l = rem / nvec;
+          const size_t i = ((size_t)q * Nc + nb[l]) * nvec + (rem - l * nvec);
+          const c64 rv = ld_coherent(A.r + i), qv = ld_coherent(pn + i);
+          const float be = s_beta[q];
+          s_in[e] = cmk(fmaf(be, qv.re, rv.re), fmaf(be, qv.im, rv.im));
+        }
+        const size_t so = (size_t)a * nvec;
+        if (has0) {
+          const c64 rv = ld_coherent(A.r + o0 + so), qv = ld_coherent(pn + o0 + so);
+          const float be = s_beta[q0];
+          st_coherent(pk + o0 + so, cmk(fmaf(be, qv.re, rv.re), fmaf(be, qv.im, rv.im)));
+        }
+        if (has1) {
+          const c64 rv = ld_coherent(A.r + o1 + so), qv = ld_coherent(pn + o1 + so);
+          const float be = s_beta[q1];
+          st_coherent(pk + o1 + so, cmk(fmaf(be, qv.re, rv.re), fmaf(be, qv.im, rv.im)));
+        }
+        __syncthreads();
+      }
+      const c64* src = STG ? s_in : pk;
       if constexpr (MODE == 0) {
         for (int r0 = 0; r0 < nr; r0 += NR0)
-          capply_site<float, NR0, U0, false, kStencil, false>(A.AT, A.nbr, pk, A.w, a, Nc, nvec, nr, r0,
-                                                              reinterpret_cast<c64*>(red_raw));
+          capply_site<float, NR0, U0, STG, kStencil, false>(
+              A.AT, A.nbr, STG ? s_in + (size_t)r0 * kStencil * nvec : pk, A.w, a, Nc, nvec, nr, r0,
+              reinterpret_cast<c64*>(red_raw));
       } else if constexpr (MODE == 3) {
-        capply_site_cmfma<float, MT, NT, 8, 2>(A.AT, A.nbr, pk, A.w, a, Nc, nvec, nr,
+        capply_site_cmfma<float, MT, NT, 8, 2, kStencil, STG>(A.AT, A.nbr, src, A.w, a, Nc, nvec, nr,
                                                 reinterpret_cast<f32x4*>(red_raw));
       } else {
-        capply_site_mfma<MODE == 1, MT, NT, 8, (K32 ? 2 : (MT >= 3 ? 3 : 4)), false, false, K32>(
-            A.F, A.rho, A.smax, A.nbr, pk, A.w, a, Nc, nvec, nr, A.ksteps, reinterpret_cast<f32x4*>(red_raw));
+        capply_site_mfma<MODE == 1, MT, NT, 8, (K32 ? 2 : (MT >= 3 ? 3 : 4)), STG, false, K32>(
+            A.F, A.rho, A.smax, A.nbr, src, A.w, a, Nc, nvec, nr, A.ksteps, reinterpret_cast<f32x4*>(red_raw));
       }
       const size_t so = (size_t)a * nvec;
       if (has0) {
@@ -614,21 +660,23 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
         if (has0) {
           const size_t i = o0 + so;
           const c64 pv = ld_coherent(pk + i), wv = A.w[i];
-          c64 xv = A.x[i], rv = A.r[i];
+          c64 xv = A.x[i], rv = STG ? ld_coherent(A.r + i) : A.r[i];
           xv = cmk(fmaf(al0, pv.re, xv.re), fmaf(al0, pv.im, xv.im));
           rv = cmk(fmaf(-al0, wv.re, rv.re), fmaf(-al0, wv.im, rv.im));
           A.x[i] = xv;
-          A.r[i] = rv;
+          if constexpr (STG) st_coherent(A.r + i, rv);
+          else A.r[i] = rv;
           acc0 += (double)rv.re * rv.re + (double)rv.im * rv.im;
         }
         if (has1) {
           const size_t i = o1 + so;
           const c64 pv = ld_coherent(pk + i), wv = A.w[i];
-          c64 xv = A.x[i], rv = A.r[i];
+          c64 xv = A.x[i], rv = STG ? ld_coherent(A.r + i) : A.r[i];
           xv = cmk(fmaf(al1, pv.re, xv.re), fmaf(al1, pv.im, xv.im));
           rv = cmk(fmaf(-al1, wv.re, rv.re), fmaf(-al1, wv.im, rv.im));
           A.x[i] = xv;
-          A.r[i] = rv;
+          if constexpr (STG) st_coherent(A.r + i, rv);
+          else A.r[i] = rv;
           acc1 += (double)rv.re * rv.re + (double)rv.im * rv.im;
         }
       }
@@ -643,7 +691,7 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
     __syncthreads();
 
     // ---- phase P: p_{k+1} = r_{k+1} + beta_k p_k on own sites
-    {
+    if constexpr (!STG) {
       const float be0 = s_beta[q0], be1 = s_beta[q1];
       for (int ia = wg; ia < Nc; ia += G) {
       const int a = xcd_remap(ia, Nc);  // each XCD owns a contiguous slab (xcd_site)
@@ -660,7 +708,8 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
         }
       }
     }
-    if (!grid_barrier(A.st, G, ++epoch, A.spin_limit)) return flag_error(A.st, A.accumulate);
+    if constexpr (!STG)
+      if (!grid_barrier(A.st, G, ++epoch, A.spin_limit)) return flag_error(A.st, A.accumulate);
   }
   if (tid < nr && s_act[tid]) s_it[tid] = (unsigned)k;  // still unconverged at maxiter
   __syncthreads();
@@ -668,25 +717,29 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
   finish(A.st, k, nr, s_rr, s_it, A.accumulate);
 }
 
-// kernel of (single or batched, mode, M tiles, N tiles, MFMA form)
-template <int MODE, int MT, int NT, bool BATCH, bool K32>
+// kernel of (single or batched, mode, M tiles, N tiles, MFMA form, staged)
+template <int MODE, int MT, int NT, bool BATCH, bool K32, bool STG>
 const void* kernel_of() {
   if constexpr (BATCH)
-    return reinterpret_cast<const void*>(&k_coarse_cg_mrhs<MODE, MT, NT, K32>);
+    return reinterpret_cast<const void*>(&k_coarse_cg_mrhs<MODE, MT, NT, K32, STG>);
   else
     return reinterpret_cast<const void*>(&k_coarse_cg<MODE, MT, K32>);
 }
 
+// The staged operand of several right-hand sides at most (beside up to 72 KB
+// of static LDS; one workgroup a CU).
+constexpr size_t kStgLds = 80 * 1024;
+
 // Workgroups of the kernel that can be resident at once, cached per kernel.
-template <int MODE, int MT, int NT, bool BATCH, bool K32>
+template <int MODE, int MT, int NT, bool BATCH, bool K32, bool STG>
 int max_grid(int* out) {
   static int cached = 0;
   if (!cached) {
     int dev = 0, cus = 0, per = 0;
     HDCG_HIP(hipGetDevice(&dev));
     HDCG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    HDCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel_of<MODE, MT, NT, BATCH, K32>(), kCT,
-                                                          BATCH ? 0 : MODE == 0 ? kPcgLds : kStencil * kMaxNvec * sizeof(c64)));
+    HDCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel_of<MODE, MT, NT, BATCH, K32, STG>(), kCT,
+                                                          STG ? kStgLds : BATCH ? 0 : MODE == 0 ? kPcgLds : kStencil * kMaxNvec * sizeof(c64)));
     cached = per * cus;
   }
   *out = cached;
@@ -701,10 +754,16 @@ int max_grid(int* out) {
 // error instead of hanging.
 template <int MODE, int MT, int NT, bool BATCH, bool K32>
 int pcg_call(bool query, const PcgArgs* a, int G, int* gmax, hipStream_t st) {
-  if (query) return max_grid<MODE, MT, NT, BATCH, K32>(gmax);
-  if constexpr (BATCH)
-    hipLaunchKernelGGL((k_coarse_cg_mrhs<MODE, MT, NT, K32>), dim3(G), dim3(kCT), 0, st, *a);
-  else
+  if (query) return max_grid<MODE, MT, NT, BATCH, K32, false>(gmax);
+  if constexpr (BATCH) {
+    int gs = 0;
+    HDCG_TRY((max_grid<MODE, MT, NT, BATCH, K32, true>(&gs)));
+    const size_t lds = sizeof(c64) * (size_t)kStencil * a->nvec * a->nr;
+    if (G == a->Nc && G <= gs && lds <= kStgLds)
+      hipLaunchKernelGGL((k_coarse_cg_mrhs<MODE, MT, NT, K32, true>), dim3(G), dim3(kCT), lds, st, *a);
+    else
+      hipLaunchKernelGGL((k_coarse_cg_mrhs<MODE, MT, NT, K32, false>), dim3(G), dim3(kCT), 0, st, *a);
+  } else
     hipLaunchKernelGGL((k_coarse_cg<MODE, MT, K32>), dim3(G), dim3(kCT),
                        sizeof(c64) * (size_t)(kStencil * a->nvec + a->kl * kCT), st, *a);
   HDCG_HIP(hipGetLastError());

@@ -205,7 +205,6 @@ __device__ __forceinline__ void capply_site_mfma(const unsigned short* __restric
                                                  const c64* __restrict__ in, c64* __restrict__ out, int a,
                                                  int Nc, int nvec, int nrhs, int ksteps, f32x4* red) {
   using frag = std::conditional_t<K32, s16x8, s16x4>;
-  static_assert(!STAGED || NT == 1, "the LDS-staged operand serves one right-hand side");
   constexpr int KL = K32 ? 8 : 4;  // K values per lane and step
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int kn = NS * nvec;
@@ -246,21 +245,27 @@ __device__ __forceinline__ void capply_site_mfma(const unsigned short* __restric
       }
     }
     if constexpr (STAGED) {
-      // one right-hand side, operand in LDS: each step's run converted as read
+      // operand in LDS ([rhs][l][k]): each step's run converted as read
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int rem = K32 ? 16 * (s0 + u) + 8 * (kg & 1) : 16 * ((s0 + u) >> 1) + 4 * kg;
         const int part = K32 ? kg >> 1 : (s0 + u) & 1;
-        bf[u][0] = frag{};
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) bf[u][nt] = frag{};
         if (cok && s0 + u < nsteps && rem < kn) {
           const float r = rh[rem / nvec];
-          frag b;
+          const c64* xp = in + rr * kn + rem;
 #pragma unroll
-          for (int i = 0; i < KL; ++i) {
-            const c64 x = in[rem + i];
-            b[i] = (short)to16<BF16>(r * (im1 ? (part == 0 ? x.im : x.re) : (part == 0 ? x.re : -x.im)));
+          for (int nt = 0; nt < NT; ++nt) {
+            const bool imcol = NT == 2 ? nt == 1 : im1;
+            frag b;
+#pragma unroll
+            for (int i = 0; i < KL; ++i) {
+              const c64 x = xp[i];
+              b[i] = (short)to16<BF16>(r * (imcol ? (part == 0 ? x.im : x.re) : (part == 0 ? x.re : -x.im)));
+            }
+            bf[u][nt] = b;
           }
-          bf[u][0] = b;
         }
       }
     } else {
@@ -389,7 +394,7 @@ __device__ __forceinline__ macc_t<R> mfma_4(R a, R b, macc_t<R> c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-template <typename R, int MT, int NT, int NW, int U, int NS = kStencil>
+template <typename R, int MT, int NT, int NW, int U, int NS = kStencil, bool STAGED = false>
 __device__ __forceinline__ void capply_site_cmfma(const cplx<R>* __restrict__ AT, const int* __restrict__ nbr,
                                                   const cplx<R>* __restrict__ in, cplx<R>* __restrict__ out, int a,
                                                   int Nc, int nvec, int nrhs, macc_t<R>* red) {
@@ -408,7 +413,7 @@ __device__ __forceinline__ void capply_site_cmfma(const cplx<R>* __restrict__ AT
   const int rr = NT == 2 ? r16 : (r16 < nrhs ? r16 : r16 - nrhs);
   const bool cok = NT == 2 ? r16 < nrhs : r16 < 2 * nrhs;
   const bool im1 = NT == 1 && r16 >= nrhs;
-  const size_t rbase = (size_t)(cok ? rr : 0) * Nc * nvec;
+  const size_t rbase = (size_t)(cok ? rr : 0) * (STAGED ? NS : Nc) * nvec;
   for (int g0 = wave * U; g0 < ngroups; g0 += NW * U) {
     cplx<R> av[U][4][MT];
     cplx<R> xv[U][4];
@@ -429,7 +434,7 @@ __device__ __forceinline__ void capply_site_cmfma(const cplx<R>* __restrict__ AT
           av[u][i][mt] = Aa[(size_t)(qc + i) * nvec + (m < nvec ? m : 0)];
         }
       const int l = qc / nvec, k = qc - l * nvec;
-      const cplx<R>* xp = in + rbase + (size_t)nb[l] * nvec + k;
+      const cplx<R>* xp = in + rbase + (STAGED ? (size_t)qc : (size_t)nb[l] * nvec + k);
 #pragma unroll
       for (int i = 0; i < 4; ++i) xv[u][i] = xp[i];
     }

@@ -39,3 +39,30 @@ def test_kept_rows_solve_to_tolerance(nvec, dims):
     assert res <= 2e-5, (res, it)
     h.close()
     op.close()
+
+
+@pytest.mark.parametrize("nvec,nr,prec,dims", [(8, 4, hd.DWF_C64, (12, 12, 12, 12)), (8, 15, hd.DWF_C64, (12, 12, 12, 12)),
+                                               (8, 16, hd.DWF_C64, (12, 12, 12, 12)), (7, 2, hd.DWF_C64, (12, 12, 12, 16)),
+                                               (7, 6, hd.DWF_C64, (12, 12, 12, 12)), (9, 14, hd.DWF_C64, (12, 12, 12, 12)),
+                                               (40, 3, hd.DWF_C64, (12, 12, 12, 12)), (12, 3, hd.DWF_C64, (24, 24, 24, 12)),
+                                               (8, 4, hd.DWF_BF16, (12, 12, 12, 16)), (12, 10, hd.DWF_BF16, (12, 12, 12, 12)),
+                                               (12, 11, hd.DWF_BF16, (12, 12, 12, 12)), (40, 3, hd.DWF_F16, (12, 12, 12, 12))])
+def test_several_right_hand_sides_solve_to_tolerance(nvec, nr, prec, dims):
+    Ls = 1
+    banner(f"coarse CG staged {dims} nvec {nvec} nr {nr} prec {prec}")
+    op = hd.FineOperator(synth.gauge_field(dims, 0.3, 472), dims, Ls, 1.8, 0.3)
+    h = hd.HDCG(op, (4, 4, 4, 4), synth.gaussian_half_field(dims, Ls, 473, nrhs=nvec))
+    Nc = dims[0] * dims[1] * dims[2] * dims[3] // 256
+    g = torch.Generator(device="cuda").manual_seed(6)
+    b = torch.randn((nr, Nc, nvec), generator=g, device="cuda", dtype=torch.complex64)
+    b[nr - 1] *= 1e-3
+    x = torch.zeros_like(b)
+    rc, it = hd.hdcg_coarse_solve(h.h, x, b, prec, nr, 1e-5 if prec == hd.DWF_C64 else 1e-3, 5000)
+    assert rc == 0 and it > 0
+    ax = torch.zeros((nr, Nc, nvec), device="cuda", dtype=torch.complex128)
+    hd.coarse_apply(h.h, ax, x.to(torch.complex128), hd.DWF_C128, nr)
+    for r in range(nr):
+        res = ((b[r] - ax[r]).norm() / b[r].norm()).item()
+        assert res <= (2e-5 if prec == hd.DWF_C64 else 2e-2), (r, res, it)
+    h.close()
+    op.close()
