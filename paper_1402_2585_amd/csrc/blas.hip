@@ -59,12 +59,6 @@ __device__ __forceinline__ void coef(const double* num, bool cnum, const double*
 // one after another (about 10 ns each), so a single counter would hold 1024
 // workgroups up for 10 us.  No workgroup waits for another, and no cache
 // maintenance is needed.
-__device__ __forceinline__ unsigned take_ticket(unsigned* c) {
-  return __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void reset_ticket(unsigned* c) {
-  __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 template <int NQ>
 __device__ __forceinline__ void reduce_out(double (&v)[NQ], Red red, int rhs, double* res, double* host = nullptr) {
   __shared__ double lds[NQ * 16];
@@ -77,16 +71,7 @@ __device__ __forceinline__ void reduce_out(double (&v)[NQ], Red red, int rhs, do
     for (int q = 0; q < NQ; ++q)
       __hip_atomic_store(part + q * nslots + blockIdx.x, v[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_s_waitcnt(0);
-    unsigned* line = red.counters + (size_t)rhs * (kTicketSubs + 1) * kTicketLine;
-    const unsigned G = gridDim.x, i = blockIdx.x % kTicketSubs;
-    unsigned* sub = line + (i + 1) * kTicketLine;
-    bool mine = take_ticket(sub) == (G - i - 1) / kTicketSubs;  // the last of this counter's workgroups
-    if (mine) {
-      reset_ticket(sub);
-      mine = take_ticket(line) == (G < kTicketSubs ? G : kTicketSubs) - 1;
-      if (mine) reset_ticket(line);
-    }
-    last = mine;
+    last = last_ticket(red.counters, rhs, gridDim.x, blockIdx.x);
   }
   __syncthreads();
   if (!last) return;
@@ -145,12 +130,8 @@ __global__ void __launch_bounds__(kFinT) k_finalize(const double* __restrict__ p
     if (threadIdx.x == 0) {
       double r = 0.0;
       for (int w = 0; w < kFinT / 64; ++w) r += lds[w];
-      res[NQ * rhs + q] = r;
-      if (NQ == 1 && cg.also) __hip_atomic_store(cg.also + rhs, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      if (NQ == 1 && cg.alpha) {
-        const double d = cg.lam != 0.0 ? r + cg.lam * cg.den2[rhs] : r;
-        cg.alpha[rhs] = d == 0.0 ? 0.0 : cg.num[rhs] / d;
-      }
+      if (NQ == 1) fin_store(r, rhs, res, cg);
+      else res[NQ * rhs + q] = r;
     }
     __syncthreads();
   }

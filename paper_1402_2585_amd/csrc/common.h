@@ -265,6 +265,29 @@ __device__ __forceinline__ void store_partial(const double (&v)[NQ], double* par
   }
 }
 
+// Tickets of a grid that finishes its own reduction: whether this workgroup
+// (number b of G, one call by one of its threads, after its partial sums have
+// been written) is the last of right-hand side rhs; the counters are left
+// zero.  Two levels, each counter on a cache line of its own.
+__device__ __forceinline__ unsigned take_ticket(unsigned* c) {
+  return __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void reset_ticket(unsigned* c) {
+  __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool last_ticket(unsigned* counters, int rhs, unsigned G, unsigned b) {
+  unsigned* line = counters + (size_t)rhs * (kTicketSubs + 1) * kTicketLine;
+  const unsigned i = b % kTicketSubs;
+  unsigned* sub = line + (i + 1) * kTicketLine;
+  bool mine = take_ticket(sub) == (G - i - 1) / kTicketSubs;  // the last of this counter's workgroups
+  if (mine) {
+    reset_ticket(sub);
+    mine = take_ticket(line) == (G < kTicketSubs ? G : kTicketSubs) - 1;
+    if (mine) reset_ticket(line);
+  }
+  return mine;
+}
+
 // What a finalize launch (nq = 1) forms beside the sums: also (nullable,
 // pinned host memory) takes them too; alpha (nullable) takes num / (sum + lam
 // den2), or 0 for a zero denominator (den2 only for lam != 0).
@@ -274,6 +297,16 @@ struct FinCg {
   double lam = 0.0;
   double* alpha = nullptr;
 };
+
+// one right-hand side's sum, by one thread
+__device__ __forceinline__ void fin_store(double sum, int rhs, double* res, const FinCg& cg) {
+  res[rhs] = sum;
+  if (cg.also) __hip_atomic_store(cg.also + rhs, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (cg.alpha) {
+    const double d = cg.lam != 0.0 ? sum + cg.lam * cg.den2[rhs] : sum;
+    cg.alpha[rhs] = d == 0.0 ? 0.0 : cg.num[rhs] / d;
+  }
+}
 
 // res[nq * rhs + q] = sum_{i < nblocks} partials[rhs * rstride + q * nslots + i]
 int launch_finalize(int nq, const double* partials, int nslots, int nblocks, int nrhs, double* res,

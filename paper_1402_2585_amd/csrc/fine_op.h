@@ -111,9 +111,8 @@ int launch_mpcdagmpc(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t stre
 // 19 field transfers three less, and four launches less (7 iterations of
 // M_IRS in complex64 on 16^3 x 32 x 16: 3.34 -> 2.91 ms, a sixteenth of it
 // the last step's unneeded half of H; complex128 CG on 8^3 x 16 x 8: 51 ->
-// 45 us a step).  Device
-// doubles, one per right-hand side; den2 (= |p|^2) only for lam != 0; rr_host,
-// nullable: pinned memory that takes rr too.
+// 46 us a step).  Device doubles, one per right-hand side; den2 (= |p|^2)
+// only for lam != 0; rr_host, nullable: pinned memory that takes rr too.
 struct CgStep {
   const double* num;
   const double* den2;

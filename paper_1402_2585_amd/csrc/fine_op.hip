@@ -332,8 +332,9 @@ struct HopArgs {
   double cg_lam;
   double* partials;   // norm of the output (not EPI_INV): [rhs][pstride] per-workgroup partials (nullable)
   size_t pstride;     // = number of workgroups
-  unsigned* counters; // [rhs]
+  unsigned* counters; // nullable: the grid finishes the norm itself, into
   double* result;     // [rhs]
+  FinCg fin;
 };
 
 // Block coordinates of workgroup wg in the block grid (lexicographic or
@@ -1130,7 +1131,6 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
     if (nrhs > 64) return fail(DWF_ERR_ARG, "nrhs > 64");
     HDCG_TRY(op->hop_part.ensure(sizeof(double) * (size_t)nwg * nrhs));
     A.partials = op->hop_part.as<double>();
-    A.counters = op->red.counters.as<unsigned>();
     A.result = norm_result;
   }
   const bool dbl = sizeof(R) == 8;
@@ -1158,6 +1158,15 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   // Ls > 16: directions whose neighbour loads are in flight together, 8 /
   // phases (the Mobius kernels are built for four phases only)
   const int phases = op->tune.phases > 0 ? op->tune.phases : (sizeof(R) == 8 ? 4 : 2);
+  // Up to 2048 workgroups of four waves fill the chip at once: the last to
+  // end sums the norm's partials, which costs it about as much as the
+  // finalize kernel's launch costs the stream twice (CG in complex128 on 8^3
+  // x 16 x 8: 46.4 -> 45.3 us a step).  With more, the first to end would hold
+  // their slots for the tickets' round trips.
+  if (split && norm_result && (size_t)grid.x * grid.y <= 2048) {
+    A.counters = op->red.counters.as<unsigned>();
+    A.fin = fin;
+  }
   if (split)
     launch_split<R, T>(dagger, epi, mob, g.Ls, A.rg > 1 || A.spw > waves * (16 / g.Ls), grid, block, lds, stream, out,
                        in, center, G, pw, A);
@@ -1168,7 +1177,7 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   else
     launch_hop<R, 2, false, T>(dagger, epi, grid, block, lds, stream, out, in, center, G, pw, A);
   HDCG_HIP(hipGetLastError());
-  if (norm_result) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride, fin);
+  if (norm_result && !A.counters) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride, fin);
   return DWF_OK;
 }
 

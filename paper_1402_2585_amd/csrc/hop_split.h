@@ -340,6 +340,33 @@ __device__ __forceinline__ void split_residual(cplx<R> (&acc)[3], const Tri<T>& 
   }
 }
 
+// The norm of one right-hand side, finished by the grid's last workgroup in a
+// fixed order (sum: the workgroup's, in thread 0)
+__device__ __forceinline__ void split_norm(double sum, const HopArgs& A, int rhs, int wg) {
+  __shared__ int last;
+  __shared__ double lds[16];
+  double* part = A.partials + (size_t)rhs * A.pstride;
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(part + wg, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0);
+    last = last_ticket(A.counters, rhs, gridDim.x, blockIdx.x);
+  }
+  __syncthreads();
+  if (!last) return;
+  double s[1] = {0.0};
+  const int G = (int)gridDim.x, B = (int)blockDim.x;
+  for (int i0 = threadIdx.x; i0 < G; i0 += 4 * B) {
+    double a[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      a[u] = i0 + u * B < G ? __hip_atomic_load(part + i0 + u * B, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s[0] += a[u];
+  }
+  block_sum<1>(s, lds);
+  if (threadIdx.x == 0) fin_store(s[0], rhs, A.result, A.fin);
+}
+
 // LS > 0 fixes Ls at compile time.  LOOP: a wave takes several sites of the
 // workgroup's block and several right-hand sides one after another (else
 // exactly one of each).  Dynamic LDS: spw * kLinkLd complex.
@@ -507,7 +534,10 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
       double vv[1] = {nrm};
       __shared__ double red[2][16];  // two: a wave may be one right-hand side ahead of thread 0
       block_sum<1>(vv, red[rr & 1]);
-      store_partial<1>(vv, A.partials + (size_t)rhs * A.pstride, 0, wg);
+      if (A.counters)
+        split_norm(vv[0], A, rhs, wg);
+      else
+        store_partial<1>(vv, A.partials + (size_t)rhs * A.pstride, 0, wg);
     }
   }
 }
