@@ -88,12 +88,12 @@ def hop_json(dirs, out_path, root, shapes=None):
                            "copy_kernel": "hdcg_prof copy 1024 3: 1 GiB read + 1 GiB write per launch"}}
     for tag, cb, gb in (("c128", 16, 16), ("c64", 8, 8), ("bf16", 4, 8)):
         fetch_db, write_db = dirs[tag]
-        def epi(name):  # the third template argument of hop_kernel<R, DAG, EPI, NPH, LS, MOB, T>
-            return name[name.index("hop_kernel<") + len("hop_kernel<"):].split(",")[2].strip()
+        def epi(name):  # the third template argument of hop_kernel, hop_split_kernel and hop_march_kernel
+            return name.split("kernel<", 1)[1].split(",")[2].strip()
 
-        f_inv = [r["avg"] for r in pmc_rows(fetch_db, "hop_kernel") if r["counter"] == "FETCH_SIZE" and epi(r["kernel"]) == "0"]
-        f_sub = [r["avg"] for r in pmc_rows(fetch_db, "hop_kernel") if r["counter"] == "FETCH_SIZE" and epi(r["kernel"]) == "1"]
-        w = [r["avg"] for r in pmc_rows(write_db, "hop_kernel") if r["counter"] == "WRITE_SIZE"]
+        f_inv = [r["avg"] for r in pmc_rows(fetch_db, "hdk::hop_") if r["counter"] == "FETCH_SIZE" and epi(r["kernel"]) == "0"]
+        f_sub = [r["avg"] for r in pmc_rows(fetch_db, "hdk::hop_") if r["counter"] == "FETCH_SIZE" and epi(r["kernel"]) == "1"]
+        w = [r["avg"] for r in pmc_rows(write_db, "hdk::hop_") if r["counter"] == "WRITE_SIZE"]
         fi, fs, ww = sum(f_inv) / len(f_inv), sum(f_sub) / len(f_sub), sum(w) / len(w)
         per_launch = ((fi + fs) / 2 * fscale + ww * wscale) * 1024.0
         alg = (10 * half * cb + 4 * V * 36 * gb) / 4
