@@ -1206,7 +1206,9 @@ int launch_mpc(dwf_op* op, T* out, const T* in, bool dagger, int nrhs, hipStream
 // complex64 on 24^3 x 48 x 16 1.69 against 1.87 ms, on 32^3 x 64 x 16 4.65
 // against 5.95 ms, on 16^3 x 32 x 16 0.316 against 0.352 ms; on 16^4 and on
 // 16-bit fields (half the bytes for the same instructions) the split form
-// stays ahead (0.142 against 0.150 ms; 0.95 against 1.05 ms on 24^3 x 48).
+// stays ahead (0.142 against 0.150 ms; 0.95 against 1.05 ms on 24^3 x 48; 8
+// right-hand sides on 16^3 x 32 1.53 against 1.56 ms, though the march wins
+// the tuner's short bursts there at a higher clock: it is not tried).
 struct HopShape {
   int block[4];
   int remap;
@@ -1238,7 +1240,7 @@ bool hop_shape_of(const dwf_op* op, int prec, int c, int shape[7]) {
   if (!s.march) return true;
   const Geom& g = op->g;
   int best = 0;
-  for (int n = 4; n <= g.T; n *= 2) {
+  for (int n = 4; n <= g.T && prec != DWF_BF16; n *= 2) {
     const int b[4] = {s.block[0], s.block[1], s.block[2], n};
     if (march_fits(g, op->f5.mobius, prec, b) &&
         (best == 0 || (long)g.Vh / (b[0] * b[1] * b[2] * n) >= s.march))
