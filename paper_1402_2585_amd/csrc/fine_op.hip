@@ -20,6 +20,8 @@
 // Epilogues (the fifth-dimension factors of M_pc, Sec. IV):
 //   EPI_INV  out = M_5^-1 (Dh in)          or M_5^-+ (Dh^+ in)   [dense in s]
 //   EPI_SUB  out = M_5 c - 1/4 (Dh in)      or M_5^+ c - 1/4 (Dh^+ in)
+//            (Ls <= 16, complex64 and complex128: EPI_INV leaves its result times
+//            alpha, and EPI_SUB has 1 / (4 alpha); one rounding less)
 //   EPI_RES  out -= a (w + lam p), w the result of EPI_SUB (Ls <= 16: a CG step's residual)
 // hop_kernel's EPI_INV stages the hop result in LDS and solves the Ls x Ls
 // system per (site, component) with the O(Ls) recurrence of the closed-form
@@ -326,6 +328,8 @@ struct HopArgs {
   // Mobius C_5 = b5 + c5 K (K: P+ from s-1, P- from s+1, -mass at the wrap)
   double alpha, beta, ia, kap, b5, c5, mass;
   double kp[4];       // kap^1, kap^2, kap^4, kap^8
+  double qia;         // ia / 4: the factor of a hop whose input is alpha M_5^-1 Dh in (Ls <= 16, not 16 bits)
+  double kc;          // kap / (1 + mass kap^16)
   // EPI_RES: a per right-hand side (device), lam and p (nullable: no shift)
   const double* cg_alpha;
   const void* cg_p;
@@ -1112,6 +1116,8 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   A.ia = op->f5.ia;
   A.kap = op->f5.kap;
   for (int k = 0; k < 4; ++k) A.kp[k] = k == 0 ? A.kap : A.kp[k - 1] * A.kp[k - 1];
+  A.qia = 0.25 * A.ia;
+  A.kc = A.kap / (1.0 + op->f5.mass * A.kp[3] * A.kp[3]);
   A.b5 = op->f5.b5;
   A.c5 = op->f5.c5;
   A.mass = op->f5.mass;

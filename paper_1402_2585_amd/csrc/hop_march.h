@@ -192,7 +192,8 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
     march_put<T, LS>(ring + 2 * slot_sz + p * col, e0, oc);
     march_put_links<R, LS>(links, e0, lk);
   }
-  const R coef = EPI == EPI_INV ? split_wrap<DAG ? kRowsDn : kRowsUp>(q, Ls, A, pw) : (R)0;
+  InvCoef<R> inv;
+  if (EPI == EPI_INV) inv = split_inv_coef<LS, DAG ? kRowsDn : kRowsUp, !kSMajor<T>>(q, Ls, A, pw);
   lds_barrier();
 
   double nrm = 0.0;
@@ -246,7 +247,7 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
       }
     }
     cplx<R> acc[3];
-    split_finish<R, DAG, EPI, LS, false>(acc, U, L, cx, cy, q, Ls, A, coef);
+    split_finish<R, DAG, EPI, LS, false>(acc, U, L, cx, cy, q, Ls, A, inv);
     {
       if (EPI == EPI_RES) split_residual<R, T>(acc, rv, pv, A, rhs);
       if (EPI != EPI_INV && active) {

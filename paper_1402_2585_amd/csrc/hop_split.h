@@ -17,14 +17,14 @@
 // gfx950's row swaps, so that row 0 ends with spin 0, row 1 with spin 3, row
 // 2 with spin 1 and row 3 with spin 2, three colours each: no LDS, no
 // barrier.  The fifth-dimension factors are DPP shifts along j: the
-// recurrence of M_5^-1 is a scan of log2(Ls) steps and one broadcast.
+// recurrence of M_5^-1 is a scan of log2(Ls) steps and one step more.
 #pragma once
 
 #include "fine_op.h"
 
 namespace hdk {
 
-constexpr int kDppShl = 0x100, kDppShr = 0x110, kDppRor = 0x120, kDppBcast = 0x150;
+constexpr int kDppShl = 0x100, kDppShr = 0x110, kDppRor = 0x120;
 constexpr int kRowsUp = 0x5, kRowsDn = 0xa;  // rows that end with upper (P+) and lower (P-) spins
 
 // lanes of the rows in MA take x shifted by DPP control CA, the other rows by
@@ -213,100 +213,168 @@ __device__ __forceinline__ void split_bcs(cplx<R> (&v)[3], const SplitLane& q, i
 
 // One step of the scan of M_5^-1: t += kap^K * (t K slices earlier in the
 // row's chain), the chain ascending in s in the rows MLOW
-template <int LS, int MLOW, int K, typename R>
+template <int MLOW, int K, typename R>
 __device__ __forceinline__ void split_scan(cplx<R> (&t)[3], R kapk, int pos) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    R re = dpp_rows<kDppShr + K, kDppShl + K, MLOW>(t[k].re);
-    R im = dpp_rows<kDppShr + K, kDppShl + K, MLOW>(t[k].im);
-    if (LS != 16) {  // the chain starts inside the row
-      re = pos >= K ? re : (R)0;
-      im = pos >= K ? im : (R)0;
-    }
-    t[k].re = fma(kapk, re, t[k].re);
-    t[k].im = fma(kapk, im, t[k].im);
+    const R re = dpp_rows<kDppShr + K, kDppShl + K, MLOW>(t[k].re);
+    const R im = dpp_rows<kDppShr + K, kDppShl + K, MLOW>(t[k].im);
+    // the chain starts inside the row
+    t[k].re = fma(kapk, pos >= K ? re : (R)0, t[k].re);
+    t[k].im = fma(kapk, pos >= K ? im : (R)0, t[k].im);
   }
 }
-
-// the coefficient of z_{Ls-1} in split_m5inv (its load is issued with the
-// kernel's first ones)
-template <int MLOW, typename R>
-__device__ __forceinline__ R split_wrap(const SplitLane& q, int Ls, const HopArgs& A, const R* __restrict__ pw) {
-  return (R)(A.mass * A.alpha * A.kap) * pw[((MLOW >> q.row) & 1) ? q.s : Ls - 1 - q.s];
-}
-
-// The whole scan and the broadcast of its end for six FP32 values at Ls = 16:
-// two row-masked v_fmac_f32_dpp a value and step (the rows of each chain
-// direction; lanes shifted in from outside the row keep their value) instead
-// of two moves and a multiply-add.  A value is read by DPP at least five
-// instructions after it was written (two wait states are needed).
-template <int MLOW>
-__device__ __forceinline__ void split_scan16(cplx<float> (&t)[3], float k1, float k2, float k4, float k8, float mw) {
-#define HDCG_DPP6(COEF, CTRL, MASK)                                                        \
-  "v_fmac_f32_dpp %0, %0, " COEF " " CTRL " row_mask:" MASK " bank_mask:0xf\n\t"            \
-  "v_fmac_f32_dpp %1, %1, " COEF " " CTRL " row_mask:" MASK " bank_mask:0xf\n\t"            \
-  "v_fmac_f32_dpp %2, %2, " COEF " " CTRL " row_mask:" MASK " bank_mask:0xf\n\t"            \
-  "v_fmac_f32_dpp %3, %3, " COEF " " CTRL " row_mask:" MASK " bank_mask:0xf\n\t"            \
-  "v_fmac_f32_dpp %4, %4, " COEF " " CTRL " row_mask:" MASK " bank_mask:0xf\n\t"            \
-  "v_fmac_f32_dpp %5, %5, " COEF " " CTRL " row_mask:" MASK " bank_mask:0xf\n\t"
-#define HDCG_SCAN16(LO, HI)                                                                     \
-  asm("s_nop 1\n\t" HDCG_DPP6("%6", "row_shr:1", LO) HDCG_DPP6("%6", "row_shl:1", HI)            \
-          HDCG_DPP6("%7", "row_shr:2", LO) HDCG_DPP6("%7", "row_shl:2", HI)                      \
-              HDCG_DPP6("%8", "row_shr:4", LO) HDCG_DPP6("%8", "row_shl:4", HI)                  \
-                  HDCG_DPP6("%9", "row_shr:8", LO) HDCG_DPP6("%9", "row_shl:8", HI)              \
-                      HDCG_DPP6("%10", "row_newbcast:15", LO) HDCG_DPP6("%10", "row_newbcast:0", HI) \
-      : "+v"(t[0].re), "+v"(t[0].im), "+v"(t[1].re), "+v"(t[1].im), "+v"(t[2].re), "+v"(t[2].im) \
-      : "v"(k1), "v"(k2), "v"(k4), "v"(k8), "v"(mw))
-  if (MLOW == kRowsUp)
-    HDCG_SCAN16("0x5", "0xa");
-  else
-    HDCG_SCAN16("0xa", "0x5");
-#undef HDCG_SCAN16
-#undef HDCG_DPP6
-}
-
-// v <- M_5^-1 v (rows MLOW: the lower-triangular recurrence): with
-// z_s = ia x_s + kap z_{s-1} from z_{-1} = 0, the wrapped entry -mass gives
-// y_s = z_s - mass kap^{s+1} / (1 + mass kap^Ls) z_{Ls-1}
-template <int LS, int MLOW, typename R>
-__device__ __forceinline__ void split_m5inv(cplx<R> (&v)[3], const SplitLane& q, int Ls, const HopArgs& A, R w) {
-  const bool low = (MLOW >> q.row) & 1;
-  const int pos = low ? q.s : Ls - 1 - q.s;
-  const R ia = (R)A.ia;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) v[k] = ia * v[k];
-  if constexpr (LS == 16 && sizeof(R) == 4) {
-    split_scan16<MLOW>(v, (R)A.kp[0], (R)A.kp[1], (R)A.kp[2], (R)A.kp[3], -w);
-    return;
-  }
-  if (LS == 16 || Ls > 1) split_scan<LS, MLOW, 1>(v, (R)A.kp[0], pos);
-  if (LS == 16 || Ls > 2) split_scan<LS, MLOW, 2>(v, (R)A.kp[1], pos);
-  if (LS == 16 || Ls > 4) split_scan<LS, MLOW, 4>(v, (R)A.kp[2], pos);
-  if (LS == 16 || Ls > 8) split_scan<LS, MLOW, 8>(v, (R)A.kp[3], pos);
-  const int last = q.row * 16 + q.sub * Ls + (low ? Ls - 1 : 0);
+// ... and with Ls = 16, round the row: o += kapk * (t K slices earlier)
+template <int MLOW, int K, typename R>
+__device__ __forceinline__ void split_turn(cplx<R> (&o)[3], const cplx<R> (&t)[3], R kapk) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    R re, im;
-    if constexpr (LS == 16) {
-      re = dpp_rows<kDppBcast + 15, kDppBcast + 0, MLOW>(v[k].re);
-      im = dpp_rows<kDppBcast + 15, kDppBcast + 0, MLOW>(v[k].im);
-    } else {
-      re = lane_get(v[k].re, last);
-      im = lane_get(v[k].im, last);
+    o[k].re = fma(kapk, dpp_rows<kDppRor + K, kDppRor + 16 - K, MLOW>(t[k].re), o[k].re);
+    o[k].im = fma(kapk, dpp_rows<kDppRor + K, kDppRor + 16 - K, MLOW>(t[k].im), o[k].im);
+  }
+}
+
+// The coefficients of split_m5inv for this lane.
+template <typename R>
+struct InvCoef {
+  R k[4];  // of the scan's steps
+  R last;  // of its last one
+};
+template <int LS, int MLOW, bool LAST, typename R>
+__device__ __forceinline__ InvCoef<R> split_inv_coef(const SplitLane& q, int Ls, const HopArgs& A,
+                                                     const R* __restrict__ pw) {
+  const int pos = ((MLOW >> q.row) & 1) ? q.s : Ls - 1 - q.s;
+  InvCoef<R> c;
+  if constexpr (LS == 16) {
+    const R m = (R)A.mass;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c.k[i] = pos < (1 << i) ? -m * (R)A.kp[i] : (R)A.kp[i];
+    c.last = !LAST ? pw[0] : pos < 1 ? -m * (R)A.kc : (R)A.kc;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c.k[i] = (R)A.kp[i];
+    c.last = -(R)(A.mass * A.alpha * (LAST ? 1.0 : A.kap)) * pw[pos];
+  }
+  return c;
+}
+
+// split_m5inv's steps for six FP32 values at Ls = 16: two row-masked
+// v_fmac_f32_dpp a value and step (the rows of each chain direction) instead
+// of two moves and a multiply-add.  A value is read by DPP at least five
+// instructions after it was written (two wait states are needed, which the
+// compiler does not insert around inline assembly: hence the nops at both
+// ends, the second for a reader of the results that is a DPP move).
+#define HDCG_FMAC(D, S, COEF, CTRL, MASK) \
+  "v_fmac_f32_dpp %" #D ", %" #S ", %" #COEF " " CTRL " row_mask:" MASK " bank_mask:0xf\n\t"
+#define HDCG_STEP(COEF, CTRL, MASK)                                                                        \
+  HDCG_FMAC(0, 0, COEF, CTRL, MASK) HDCG_FMAC(1, 1, COEF, CTRL, MASK) HDCG_FMAC(2, 2, COEF, CTRL, MASK)     \
+      HDCG_FMAC(3, 3, COEF, CTRL, MASK) HDCG_FMAC(4, 4, COEF, CTRL, MASK) HDCG_FMAC(5, 5, COEF, CTRL, MASK)
+#define HDCG_LAST(COEF, CTRL, MASK)                                                                        \
+  HDCG_FMAC(6, 0, COEF, CTRL, MASK) HDCG_FMAC(7, 1, COEF, CTRL, MASK) HDCG_FMAC(8, 2, COEF, CTRL, MASK)     \
+      HDCG_FMAC(9, 3, COEF, CTRL, MASK) HDCG_FMAC(10, 4, COEF, CTRL, MASK) HDCG_FMAC(11, 5, COEF, CTRL, MASK)
+#define HDCG_SCAN16(A, B, C, D, LO, HI)                                                                    \
+  "s_nop 1\n\t" HDCG_STEP(A, "row_ror:1", LO) HDCG_STEP(A, "row_ror:15", HI) HDCG_STEP(B, "row_ror:2", LO) \
+      HDCG_STEP(B, "row_ror:14", HI) HDCG_STEP(C, "row_ror:4", LO) HDCG_STEP(C, "row_ror:12", HI)           \
+          HDCG_STEP(D, "row_ror:8", LO) HDCG_STEP(D, "row_ror:8", HI)
+#define HDCG_SIX(t) "+v"(t[0].re), "+v"(t[0].im), "+v"(t[1].re), "+v"(t[1].im), "+v"(t[2].re), "+v"(t[2].im)
+template <int MLOW>
+__device__ __forceinline__ void split_scan16(cplx<float> (&x)[3], const InvCoef<float>& k) {
+#define HDCG_ASM(LO, HI)                               \
+  asm(HDCG_SCAN16(6, 7, 8, 9, LO, HI) "s_nop 1"        \
+      : HDCG_SIX(x)                                    \
+      : "v"(k.k[0]), "v"(k.k[1]), "v"(k.k[2]), "v"(k.k[3]))
+  if (MLOW == kRowsUp)
+    HDCG_ASM("0x5", "0xa");
+  else
+    HDCG_ASM("0xa", "0x5");
+#undef HDCG_ASM
+}
+template <int MLOW>
+__device__ __forceinline__ void split_inv16(cplx<float> (&x)[3], const InvCoef<float>& k) {
+  cplx<float> t[3] = {x[0], x[1], x[2]};
+#define HDCG_ASM(LO, HI)                                                                                        \
+  asm(HDCG_SCAN16(12, 13, 14, 15, LO, HI) HDCG_LAST(16, "row_ror:1", LO) HDCG_LAST(16, "row_ror:15", HI) "s_nop 1" \
+      : HDCG_SIX(t), HDCG_SIX(x)                                                                                \
+      : "v"(k.k[0]), "v"(k.k[1]), "v"(k.k[2]), "v"(k.k[3]), "v"(k.last))
+  if (MLOW == kRowsUp)
+    HDCG_ASM("0x5", "0xa");
+  else
+    HDCG_ASM("0xa", "0x5");
+#undef HDCG_ASM
+}
+#undef HDCG_SIX
+#undef HDCG_SCAN16
+#undef HDCG_LAST
+#undef HDCG_STEP
+#undef HDCG_FMAC
+
+// x <- alpha M_5^-1 x (rows MLOW: ascending in s): y = x + kap S y, S the
+// shift along the row's chain with -mass at the wall.  The factor 1 / alpha is
+// left to the stage that reads the result (HopArgs::qia).
+//
+// A scan gives y up to its own roundings, log2(Ls) of the size of y; one more
+// step of the equation, from x itself, leaves one rounding of that size and
+// damps the others by kap.  Without it M_5^-1 had 1.5 times the rounding error
+// of the O(Ls) recurrence (FP32, Ls 16: 5.6e-8 against 3.7e-8 or 2.9e-8 with
+// either choice of fused multiply-adds; with it 2.9e-8).  H against 64 bits,
+// recurrence, scan alone, with the step: complex64 on 8^3 x 16 x 16 8.00e-8,
+// 8.08e-8, 7.69e-8; complex128 on 16^4 x 16 1.910e-16, 1.952e-16, 1.896e-16.
+//   Ls = 16: shifts round the whole row, t = (1 + k S)(1 + k^2 S^2) ... x
+//     = (1 + mass kap^16) y, and y = x + kap / (1 + mass kap^16) S t;
+//   else: z from z_{-1} = 0, and with c_s = mass kap^s / (1 + mass kap^Ls)
+//     y_s = x_s + kap (z_{s-1} - c_s z_{Ls-1}).
+// LAST = false: x <- M_5^-1 x without that step, for fields that are rounded
+// to 16 bits next (2^-8 against a few 2^-24).
+template <int LS, int MLOW, bool LAST, typename R>
+__device__ __forceinline__ void split_m5inv(cplx<R> (&x)[3], const SplitLane& q, int Ls, const InvCoef<R>& k, R ia) {
+  if constexpr (!LAST) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) x[c] = (LS == 16 ? k.last : ia) * x[c];
+  }
+  if constexpr (LS == 16 && sizeof(R) == 4) {
+    if constexpr (LAST) split_inv16<MLOW>(x, k);
+    else split_scan16<MLOW>(x, k);
+  } else if constexpr (LS == 16) {
+    static_assert(LAST, "16-bit fields compute in FP32");
+    cplx<R> t[3] = {x[0], x[1], x[2]};
+    split_turn<MLOW, 1>(t, t, k.k[0]);
+    split_turn<MLOW, 2>(t, t, k.k[1]);
+    split_turn<MLOW, 4>(t, t, k.k[2]);
+    split_turn<MLOW, 8>(t, t, k.k[3]);
+    split_turn<MLOW, 1>(x, t, k.last);
+  } else {
+    const bool low = (MLOW >> q.row) & 1;
+    const int pos = low ? q.s : Ls - 1 - q.s;
+    cplx<R> t[3] = {x[0], x[1], x[2]};
+    if (Ls > 1) split_scan<MLOW, 1>(t, k.k[0], pos);
+    if (Ls > 2) split_scan<MLOW, 2>(t, k.k[1], pos);
+    if (Ls > 4) split_scan<MLOW, 4>(t, k.k[2], pos);
+    if (Ls > 8) split_scan<MLOW, 8>(t, k.k[3], pos);
+    const int last = q.row * 16 + q.sub * Ls + (low ? Ls - 1 : 0);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const R re = lane_get(t[c].re, last), im = lane_get(t[c].im, last);
+      if constexpr (LAST) {
+        const R pre = dpp_rows<kDppShr + 1, kDppShl + 1, MLOW>(t[c].re);
+        const R pim = dpp_rows<kDppShr + 1, kDppShl + 1, MLOW>(t[c].im);
+        x[c].re = fma(k.k[0], fma(k.last, re, pos >= 1 ? pre : (R)0), x[c].re);
+        x[c].im = fma(k.k[0], fma(k.last, im, pos >= 1 ? pim : (R)0), x[c].im);
+      } else {
+        x[c] = cmk(fma(k.last, re, t[c].re), fma(k.last, im, t[c].im));
+      }
     }
-    v[k].re = fma(-w, re, v[k].re);
-    v[k].im = fma(-w, im, v[k].im);
   }
 }
 
 // The row's spin of the stage's output from the rows' parts U, L of the hop:
-// reduction over the rows, then the fifth-dimension factors (wrap: split_wrap's
-// coefficient, EPI_INV; cx, cy: the
-// centre field at s and at the slice M_5 couples it to, the other stages).
+// reduction over the rows, then the fifth-dimension factors (inv: M_5^-1's
+// coefficients, EPI_INV; cx, cy: the centre field at s and at the slice M_5
+// couples it to, the other stages, whose input is alpha times M_5^-1's result
+// but for 16-bit fields).
 template <typename R, bool DAG, int EPI, int LS, bool MOB, typename T>
 __device__ __forceinline__ void split_finish(cplx<R> (&acc)[3], const cplx<R> (&U)[3], const cplx<R> (&L)[3],
                                              const Tri<T>& cx, const Tri<T>& cy, const SplitLane& q, int Ls,
-                                             const HopArgs& A, R wrap) {
+                                             const HopArgs& A, const InvCoef<R>& inv) {
   const bool row3 = q.row == 3;
 #pragma unroll
   for (int k = 0; k < 3; ++k)
@@ -315,12 +383,12 @@ __device__ __forceinline__ void split_finish(cplx<R> (&acc)[3], const cplx<R> (&
   // (P+ from s+1, P- from s-1)
   if (MOB && DAG) split_bcs<LS, kRowsUp>(acc, q, Ls, (R)A.b5, (R)A.c5, (R)A.mass);
   if (EPI == EPI_INV) {
-    split_m5inv<LS, DAG ? kRowsDn : kRowsUp>(acc, q, Ls, A, wrap);
+    split_m5inv<LS, DAG ? kRowsDn : kRowsUp, !kSMajor<T>>(acc, q, Ls, inv, (R)A.ia);
     // Mobius: C_5 after M_5^-1, for the second hop (P+ from s-1, P- from s+1)
     if (MOB && !DAG) split_bcs<LS, kRowsDn>(acc, q, Ls, (R)A.b5, (R)A.c5, (R)A.mass);
   } else {
     // M_5 couples P+ to s-1 and P- to s+1; the adjoint swaps the two
-    const R al = (R)A.alpha, be = (R)A.beta, m = (R)A.mass, qu = (R)0.25;
+    const R al = (R)A.alpha, be = (R)A.beta, m = (R)A.mass, qu = kSMajor<T> ? (R)0.25 : (R)A.qia;
     const bool wall = (q.upper != DAG) ? q.s == 0 : q.s == Ls - 1;
     const R f = wall ? -m * be : be;
 #pragma unroll
@@ -409,7 +477,8 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
   constexpr int NL = LS > 0 ? (72 + 4 * LS - 1) / (4 * LS) : 1;
   const int e0 = q.row * Ls + q.s;
 
-  const R wrap = EPI == EPI_INV ? split_wrap<DAG ? kRowsDn : kRowsUp>(q, Ls, A, pw) : (R)0;
+  InvCoef<R> inv;
+  if (EPI == EPI_INV) inv = split_inv_coef<LS, DAG ? kRowsDn : kRowsUp, !kSMajor<T>>(q, Ls, A, pw);
   for (int rr = 0; rr < nr; ++rr) {
     const int rhs = rhs0 + rr;
     const T* __restrict__ inr = in + rhs * A.field;
@@ -515,7 +584,7 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
         }
       }
       cplx<R> acc[3];
-      split_finish<R, DAG, EPI, LS, MOB>(acc, U, L, cx, cy, q, Ls, A, wrap);
+      split_finish<R, DAG, EPI, LS, MOB>(acc, U, L, cx, cy, q, Ls, A, inv);
       if (EPI == EPI_RES) split_residual<R, T>(acc, rv, pv, A, rhs);
       if (EPI != EPI_INV && active) {
 #pragma unroll
