@@ -179,11 +179,11 @@ __device__ __forceinline__ bool record_value(unsigned long long lo, unsigned lon
 __device__ __forceinline__ unsigned long long ld_word(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// The sum of records g = lane, lane + 64, ... < n of the array p, eight loads
-// at a time in flight (false after spin_limit polls; `it` counts them).
+// The sum of records g = lane, lane + 64, ... < n of the array p, four at a
+// time in flight (false after spin_limit polls; `it` counts them).
 __device__ __forceinline__ bool sum_records(const unsigned long long* p, int n, int lane, unsigned epoch, double* sum,
                                             unsigned& it, unsigned spin_limit) {
-  constexpr int U = 8;
+  constexpr int U = 4;
   double s = 0.0;
   for (int g0 = lane; g0 < n; g0 += 64 * U) {
     for (;;) {
@@ -451,7 +451,8 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
       if constexpr (MODE == 0) {
         capply_kept<8>(A.AT, s_in, A.w, a, nvec, keep, cache, A.kl, a == wg, reinterpret_cast<c64*>(red_raw));
       } else {
-        capply_site_mfma<MODE == 1, MT, 1, 8, (K32 ? 2 : (MT >= 3 ? 3 : 4)), true, false, K32>(
+        // (K steps in flight: what 120 registers hold, max_grid)
+        capply_site_mfma<MODE == 1, MT, 1, 8, (K32 ? (MT >= 3 ? 1 : 2) : (MT >= 3 ? 2 : 3)), true, false, K32>(
             A.F, A.rho, A.smax, A.nbr, s_in, A.w, a, Nc, nvec, 1, A.ksteps, reinterpret_cast<f32x4*>(red_raw));
       }
       for (int e = tid; e < nvec; e += kCT) {
@@ -731,6 +732,15 @@ const void* kernel_of() {
 constexpr size_t kStgLds = 80 * 1024;
 
 // Workgroups of the kernel that can be resident at once, cached per kernel.
+// Every workgroup waits for all others, so all of them have to find room
+// whatever else runs when the grid starts.  A wave's registers are contiguous
+// in its SIMD's 512: one wave of another kernel (another stream's) among them
+// splits what is left, and where the grid needed all of it a workgroup finds
+// no room even after that wave has gone.  So the registers are never filled:
+// 120 a lane leave room for 2 workgroups of 8 waves on a CU, 128 for one.
+// Several right-hand sides take one workgroup a CU in any case (512 sites, 8
+// vectors, 4 right-hand sides: 1.15 ms with 256 workgroups, 1.39 ms with 512,
+// whose acquires and barriers cost more than the second site).
 template <int MODE, int MT, int NT, bool BATCH, bool K32, bool STG>
 int max_grid(int* out) {
   static int cached = 0;
@@ -740,6 +750,10 @@ int max_grid(int* out) {
     HDCG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     HDCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel_of<MODE, MT, NT, BATCH, K32, STG>(), kCT,
                                                           STG ? kStgLds : BATCH ? 0 : MODE == 0 ? kPcgLds : kStencil * kMaxNvec * sizeof(c64)));
+    hipFuncAttributes fa;
+    HDCG_HIP(hipFuncGetAttributes(&fa, kernel_of<MODE, MT, NT, BATCH, K32, STG>()));
+    const int regs = std::max(8, (fa.numRegs + 7) / 8 * 8);  // a lane's, as allocated
+    per = std::min(per, BATCH ? 1 : 511 / (kCT / 64 / 4 * regs));
     cached = per * cus;
   }
   *out = cached;
