@@ -85,7 +85,7 @@ struct PcgState {
 
 struct PcgArgs {
   int Nc, nvec, nr, maxiter, ksteps, gmax;
-  int kl;                     // one right-hand side, complex64: rows of the operator kept in LDS
+  int kl;                     // one right-hand side, complex64: rows of the operator kept in LDS (-1: none kept at all)
   int accumulate;             // 1: add this solve's counts to the totals (deferred solves)
   double tol2;
   unsigned spin_limit;
@@ -321,16 +321,25 @@ __device__ __forceinline__ void flag_error(PcgState* st, int accumulate) {
 // rows q = part + parts i of column j (capply_site); rows i < kKeep stay in
 // its registers, the next A.kl in LDS ([row][thread], after s_in), and the
 // rest is streamed, its first loads issued before the kept rows' arithmetic.
-// The sums run in capply_site's order.  512 sites x 24, 28 steps: 1000 -> 875
-// us with 8 rows in registers and 14 in LDS (of 93; 16 in registers spill:
-// 960), and 8 rows of loads in flight (12: 897).
+// The sums run in capply_site's order.  512 sites x 24, 28 steps: 1024 -> 902
+// us with 8 rows in registers and 14 in LDS (of 93; 16 in registers spill).
+//
+// The registers that hold kept rows are taken from the loads in flight (8
+// instead of 11), so it only pays where the operator's traffic is the bound
+// (keep_pays):
+//   - every workgroup has one site (2592 sites x 8: 1.34 ms kept, 1.16 not);
+//   - the operator exceeds the eight 4 MB L2s (512 x 8, 21 MB: 377 and 364
+//     us; 512 x 12, 48 MB: 393 and 469; 256 x 12, 24 MB: 225 and 220);
+//   - more workgroups than CUs (384 x 48: 2.76 and 2.96 ms; 162 x 48: 1.21
+//     and 0.93 ms, 162 x 24: 427 and 385 us), or as many and at least an
+//     eighth of the rows kept (256 x 24: 400 and 412 us; 256 x 48: 1.40 and
+//     1.35 ms).
 constexpr int kKeep = 8;
 constexpr size_t kPcgLds = 72 * 1024;  // dynamic LDS of a workgroup at most: two fit a CU's 160 KB
 
 template <int U>
 __device__ __forceinline__ void capply_kept(const c64* __restrict__ AT, const c64* in, c64* __restrict__ out, int a,
-                                            int nvec, const c64 (&keep)[kKeep], const c64* cache, int kl, bool kept,
-                                            c64* red) {
+                                            int nvec, const c64 (&keep)[kKeep], const c64* cache, int kl, c64* red) {
   const int parts = kCT / nvec, K = kStencil * nvec, step = parts * nvec;
   const int j = threadIdx.x % nvec, part = threadIdx.x / nvec;
   const int mine = part < parts ? K - part : 0;  // row i is in range for parts * i < mine
@@ -338,20 +347,18 @@ __device__ __forceinline__ void capply_kept(const c64* __restrict__ AT, const c6
   const c64* Aa = AT + (size_t)a * K * nvec;
   const c64* x = in + own / nvec;
   c64 acc = cmk(0.f, 0.f), Av[U];
-  int i0 = kept ? kKeep + kl : 0;
+  int i0 = kKeep + kl;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const c64* row = Aa + (size_t)(i0 + u) * step;
     Av[u] = parts * (i0 + u) < mine ? row[own] : cmk(0.f, 0.f);
   }
-  if (kept) {
 #pragma unroll
-    for (int i = 0; i < kKeep; ++i)
-      if (parts * i < mine) cmac(acc, keep[i], x[parts * i]);
+  for (int i = 0; i < kKeep; ++i)
+    if (parts * i < mine) cmac(acc, keep[i], x[parts * i]);
 #pragma unroll 4
-    for (int i = 0; i < kl; ++i)
-      if (parts * (kKeep + i) < mine) cmac(acc, cache[i * kCT + threadIdx.x], x[parts * (kKeep + i)]);
-  }
+  for (int i = 0; i < kl; ++i)
+    if (parts * (kKeep + i) < mine) cmac(acc, cache[i * kCT + threadIdx.x], x[parts * (kKeep + i)]);
   for (; parts * i0 < K; i0 += U) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -373,10 +380,11 @@ __device__ __forceinline__ void capply_kept(const c64* __restrict__ AT, const c6
 }
 
 // One right-hand side.  MODE 0: complex64 VALU operator; 1: bf16 MFMA;
-// 2: fp16 MFMA (MT M tiles).
+// 2: fp16 MFMA (MT M tiles).  KEEP (MODE 0): rows of the operator are kept on
+// chip (every workgroup has one site).
 constexpr int kMaxNvec = 64;
 // K32: the 16x16x32 MFMA form (nvec % 8 == 0), else 16x16x16.
-template <int MODE, int MT, bool K32>
+template <int MODE, int MT, bool K32, bool KEEP>
 __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k_coarse_cg(PcgArgs A) {
   constexpr int kRedBytes = MODE == 0 ? kCT * (int)sizeof(c64) : 8 * MT * 64 * (int)sizeof(f32x4);
   __shared__ __align__(16) unsigned char red_raw[kRedBytes];
@@ -398,10 +406,9 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
       st_coherent(A.p1 + idx, cmk(0.f, 0.f));
       acc += (double)bv.re * bv.re + (double)bv.im * bv.im;
     }
-  // MODE 0: the kept rows of the first site
-  c64 keep[MODE == 0 ? kKeep : 1];
+  c64 keep[KEEP ? kKeep : 1];  // of this workgroup's site
   c64* const cache = s_in + kStencil * nvec;
-  if constexpr (MODE == 0) {
+  if constexpr (KEEP) {
     const int parts = kCT / nvec, part = tid / nvec, K = kStencil * nvec, step = parts * nvec;
     const int mine = part < parts ? K - part : 0;
     const c64* Aa = A.AT + (size_t)wg * K * nvec;
@@ -448,8 +455,11 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(4))) k
         }
         __syncthreads();
       }
-      if constexpr (MODE == 0) {
-        capply_kept<8>(A.AT, s_in, A.w, a, nvec, keep, cache, A.kl, a == wg, reinterpret_cast<c64*>(red_raw));
+      if constexpr (KEEP) {
+        capply_kept<8>(A.AT, s_in, A.w, a, nvec, keep, cache, A.kl, reinterpret_cast<c64*>(red_raw));
+      } else if constexpr (MODE == 0) {
+        // (11 loads in flight: one round for 8 vectors, and 120 registers)
+        capply_site<float, 1, 11, true>(A.AT, A.nbr, s_in, A.w, a, Nc, nvec, 1, 0, reinterpret_cast<c64*>(red_raw));
       } else {
         // (K steps in flight: what 120 registers hold, max_grid)
         capply_site_mfma<MODE == 1, MT, 1, 8, (K32 ? (MT >= 3 ? 1 : 2) : (MT >= 3 ? 2 : 3)), true, false, K32>(
@@ -718,13 +728,14 @@ __global__ void __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(2))) k
   finish(A.st, k, nr, s_rr, s_it, A.accumulate);
 }
 
-// kernel of (single or batched, mode, M tiles, N tiles, MFMA form, staged)
-template <int MODE, int MT, int NT, bool BATCH, bool K32, bool STG>
+// kernel of (single or batched, mode, M tiles, N tiles, MFMA form, on-chip
+// form: of one right-hand side KEEP, of several STG)
+template <int MODE, int MT, int NT, bool BATCH, bool K32, bool ON>
 const void* kernel_of() {
   if constexpr (BATCH)
-    return reinterpret_cast<const void*>(&k_coarse_cg_mrhs<MODE, MT, NT, K32, STG>);
+    return reinterpret_cast<const void*>(&k_coarse_cg_mrhs<MODE, MT, NT, K32, ON>);
   else
-    return reinterpret_cast<const void*>(&k_coarse_cg<MODE, MT, K32>);
+    return reinterpret_cast<const void*>(&k_coarse_cg<MODE, MT, K32, ON>);
 }
 
 // The staged operand of several right-hand sides at most (beside up to 72 KB
@@ -741,17 +752,17 @@ constexpr size_t kStgLds = 80 * 1024;
 // Several right-hand sides take one workgroup a CU in any case (512 sites, 8
 // vectors, 4 right-hand sides: 1.15 ms with 256 workgroups, 1.39 ms with 512,
 // whose acquires and barriers cost more than the second site).
-template <int MODE, int MT, int NT, bool BATCH, bool K32, bool STG>
+template <int MODE, int MT, int NT, bool BATCH, bool K32, bool ON>
 int max_grid(int* out) {
   static int cached = 0;
   if (!cached) {
     int dev = 0, cus = 0, per = 0;
     HDCG_HIP(hipGetDevice(&dev));
     HDCG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    HDCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel_of<MODE, MT, NT, BATCH, K32, STG>(), kCT,
-                                                          STG ? kStgLds : BATCH ? 0 : MODE == 0 ? kPcgLds : kStencil * kMaxNvec * sizeof(c64)));
+    HDCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel_of<MODE, MT, NT, BATCH, K32, ON>(), kCT,
+                                                          BATCH ? (ON ? kStgLds : 0) : ON ? kPcgLds : kStencil * kMaxNvec * sizeof(c64)));
     hipFuncAttributes fa;
-    HDCG_HIP(hipFuncGetAttributes(&fa, kernel_of<MODE, MT, NT, BATCH, K32, STG>()));
+    HDCG_HIP(hipFuncGetAttributes(&fa, kernel_of<MODE, MT, NT, BATCH, K32, ON>()));
     const int regs = std::max(8, (fa.numRegs + 7) / 8 * 8);  // a lane's, as allocated
     per = std::min(per, BATCH ? 1 : 511 / (kCT / 64 / 4 * regs));
     cached = per * cus;
@@ -777,9 +788,17 @@ int pcg_call(bool query, const PcgArgs* a, int G, int* gmax, hipStream_t st) {
       hipLaunchKernelGGL((k_coarse_cg_mrhs<MODE, MT, NT, K32, true>), dim3(G), dim3(kCT), lds, st, *a);
     else
       hipLaunchKernelGGL((k_coarse_cg_mrhs<MODE, MT, NT, K32, false>), dim3(G), dim3(kCT), 0, st, *a);
-  } else
-    hipLaunchKernelGGL((k_coarse_cg<MODE, MT, K32>), dim3(G), dim3(kCT),
-                       sizeof(c64) * (size_t)(kStencil * a->nvec + a->kl * kCT), st, *a);
+  } else {
+    constexpr bool KEEP = MODE == 0;
+    int gk = 0;
+    if (KEEP) HDCG_TRY((max_grid<MODE, MT, NT, BATCH, K32, KEEP>(&gk)));
+    const size_t in = sizeof(c64) * (size_t)kStencil * a->nvec;
+    if (KEEP && a->kl >= 0 && G <= gk)
+      hipLaunchKernelGGL((k_coarse_cg<MODE, MT, K32, KEEP>), dim3(G), dim3(kCT), in + sizeof(c64) * (size_t)a->kl * kCT,
+                         st, *a);
+    else
+      hipLaunchKernelGGL((k_coarse_cg<MODE, MT, K32, false>), dim3(G), dim3(kCT), in, st, *a);
+  }
   HDCG_HIP(hipGetLastError());
   return DWF_OK;
 }
@@ -873,6 +892,15 @@ bool plan(hdcg* h, int mprec, int nr, int* mode, int* mt, int* G) {
   return true;
 }
 
+// Whether keeping `kept` of a site's `rows` on chip pays (capply_kept).
+bool keep_pays(int Nc, int G, int nvec, int kept, int rows) {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return false;
+  const size_t op = sizeof(c64) * (size_t)Nc * kStencil * nvec * nvec;
+  return G == Nc && op > ((size_t)32 << 20) && (Nc > cus || (Nc == cus && 8 * kept >= rows));
+}
+
 // Enqueue one persistent solve on `st` (no host synchronisation).
 int launch_solve(hdcg* h, const PcgWork& wk, int mode, int mt, int G, int mprec, c64* x, const c64* b, int nr,
                  double tol, int maxiter, hipStream_t st, int accumulate = 0) {
@@ -887,10 +915,11 @@ int launch_solve(hdcg* h, const PcgWork& wk, int mode, int mt, int G, int mprec,
   a.ksteps = mfma_ksteps(kStencil * nv);
   a.gmax = G;
   // rows of the operator kept in LDS: what is left beside s_in
-  a.kl = 0;
+  a.kl = -1;
   if (mode == 0 && nr == 1) {
-    const int rows = (kStencil * nv + kCT / nv - 1) / (kCT / nv) - kKeep;
-    a.kl = std::max(0, std::min(rows, (int)((kPcgLds / sizeof(c64) - kStencil * nv) / kCT)));
+    const int rows = (kStencil * nv + kCT / nv - 1) / (kCT / nv);
+    const int kl = std::max(0, std::min(rows - kKeep, (int)((kPcgLds / sizeof(c64) - kStencil * nv) / kCT)));
+    if (keep_pays(h->Nc, G, nv, kKeep + kl, rows)) a.kl = kl;
   }
   a.tol2 = tol * tol;
   a.spin_limit = 1u << 21;  // >= 50 ms of waiting at 64+ cycles per poll

@@ -47,3 +47,28 @@ def test_more_sites_than_workgroups(nvec, prec):
             assert res <= (2e-5 if prec == hd.DWF_C64 else 2e-2), (nr, r, res, it)
     h.close()
     op.close()
+
+
+@pytest.mark.parametrize("nvec,dims", [(12, (20, 20, 16, 16)), (64, (20, 20, 16, 16)), (33, (20, 20, 16, 16)),
+                                       (10, (20, 20, 16, 16)), (16, (16, 16, 16, 16)), (28, (16, 16, 16, 16)),
+                                       (32, (16, 16, 16, 16)), (16, (12, 20, 16, 16))])
+def test_kept_rows_on_both_sides_of_their_rule(nvec, dims):
+    """Where rows of the operator are kept on chip (more sites than CUs, or as
+    many and an eighth of the rows, for an operator above 32 MB): all rows
+    kept, a few, one row beyond a whole wave, and the cases beside the rule."""
+    Ls = 1
+    banner(f"coarse CG kept rows {dims} nvec {nvec}")
+    op = hd.FineOperator(synth.gauge_field(dims, 0.3, 476), dims, Ls, 1.8, 0.3)
+    h = hd.HDCG(op, (4, 4, 4, 4), synth.gaussian_half_field(dims, Ls, 477, nrhs=nvec))
+    Nc = dims[0] * dims[1] * dims[2] * dims[3] // 256
+    g = torch.Generator(device="cuda").manual_seed(8)
+    b = torch.randn((1, Nc, nvec), generator=g, device="cuda", dtype=torch.complex64)
+    x = torch.zeros_like(b)
+    rc, it = hd.hdcg_coarse_solve(h.h, x, b, hd.DWF_C64, 1, 1e-5, 5000)
+    assert rc == 0 and it > 0
+    ax = torch.zeros((1, Nc, nvec), device="cuda", dtype=torch.complex128)
+    hd.coarse_apply(h.h, ax, x.to(torch.complex128), hd.DWF_C128, 1)
+    res = ((b - ax).norm() / b.norm()).item()
+    assert res <= 2e-5, (res, it)
+    h.close()
+    op.close()
