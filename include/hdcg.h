@@ -140,7 +140,7 @@ int dwf_set_hop_shape(dwf_op_t op, const int shape[10]);
 /* The hop launch shape in use for (prec DWF_C128 / DWF_C64 / DWF_BF16,
  * nrhs = 1 or more): shape[10] as dwf_set_hop_shape takes it; ms (nullable,
  * *ncand entries) the autotuner's milliseconds per H of each candidate, -1
- * before it has run.  Returns 1 (and the current shape) when the autotuner
+ * before it has run.  Returns 1 (and the default shape) when the autotuner
  * has not run yet for that storage and count. */
 int dwf_get_hop_shape(dwf_op_t op, int prec, int nrhs, int shape[10], float* ms, int* ncand);
 

@@ -422,16 +422,14 @@ int dwf_get_hop_shape(dwf_op_t op, int prec, int nrhs, int shape[10], float* ms,
   if (ncand) *ncand = n;
   if (ms)
     for (int i = 0; i < n; ++i) ms[i] = c >= 0 ? op->hop_ms[pi][ri][i] : -1.f;
-  int cand[7];
-  const bool tuned = op->hop_autotune && c >= 0;
-  if (tuned) (void)hop_shape_of(op, prec, c, cand);
-  for (int i = 0; i < 4; ++i) shape[i] = tuned ? cand[i] : op->tune.block[i];
-  shape[4] = tuned ? cand[4] : op->tune.remap;
-  shape[5] = op->tune.lds_kb;
-  shape[6] = op->tune.nt;
-  shape[7] = tuned ? cand[5] : op->tune.morton;
-  shape[8] = op->tune.phases;
-  shape[9] = tuned ? cand[6] : op->tune.rg;
+  const HopTune t = hop_shape(op, prec, nrhs);
+  for (int i = 0; i < 4; ++i) shape[i] = t.block[i];
+  shape[4] = t.remap;
+  shape[5] = t.lds_kb;
+  shape[6] = t.nt;
+  shape[7] = t.morton;
+  shape[8] = t.phases;
+  shape[9] = t.rg;
   return op->hop_autotune && c < 0 ? 1 : DWF_OK;
 }
 

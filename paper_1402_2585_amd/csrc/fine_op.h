@@ -46,6 +46,21 @@ struct dwf_op_impl;
 
 }  // namespace hdk
 
+namespace hdk {
+// Launch shape of a hop stage (dwf_set_hop_shape's entries).
+struct HopTune {
+  int block[4] = {2, 2, 1, 1};  // workgroup site block in (x/2, y, z, t), powers of two; 0 = linear
+  int remap = 1;                // XCD-contiguous workgroup order
+  int lds_kb = 0;               // minimum LDS per workgroup (caps occupancy)
+  int nt = 0;                   // non-temporal output stores
+  int morton = 1;               // block order: 0 lexicographic, 1 Morton (power-of-two block
+                                // grids), 2-4 per-XCD regions from a table
+  int phases = 0;               // neighbour-load phases per stage (2 or 4; 0: 4 for complex128,
+                                // 2 for the FP32 kernels, whose spinors take half the registers)
+  int rg = 1;                   // right-hand sides per workgroup (sharing the links staged in LDS)
+};
+}  // namespace hdk
+
 struct dwf_op {
   hdk::Geom g;
   double M5, mass;
@@ -59,19 +74,7 @@ struct dwf_op {
   hdk::DevBuf msw[4];             // multi-shift CG: p_j (c128), r, w, device scalars
   hdk::Reducer red;
   hdk::DevBuf hop_part;           // fused-norm partials of the hop stage: [rhs][workgroups]
-  struct {
-    // hop launch shape (measured best on MI355X at 16^4 and 24^3x48, Ls = 16;
-    // block, remap and order are the autotuner's)
-    int block[4] = {2, 2, 1, 1};  // workgroup site block in (x/2, y, z, t), powers of two; 0 = linear
-    int remap = 1;                // XCD-contiguous workgroup order
-    int lds_kb = 0;               // minimum LDS per workgroup (caps occupancy)
-    int nt = 0;                   // non-temporal output stores
-    int morton = 1;               // block order: 0 lexicographic, 1 Morton (power-of-two block
-                                  // grids), 2-4 per-XCD regions from a table
-    int phases = 0;               // neighbour-load phases per stage (2 or 4; 0: 4 for complex128,
-                                  // 2 for the FP32 kernels, whose spinors take half the registers)
-    int rg = 1;                   // right-hand sides per workgroup (sharing the links staged in LDS)
-  } tune;
+  hdk::HopTune tune;              // the fixed shape, while hop_autotune is off
   // launch-shape autotuner: the candidate chosen per (field storage c128 /
   // c64 / 16-bit, one / several right-hand sides), -1 before it has run;
   // off after dwf_set_hop_shape fixes a shape
@@ -166,11 +169,13 @@ int launch_convert(Td* dst, const Ts* src, size_t n, hipStream_t stream);
 int launch_convert16(dwf_op* op, bf16c* dst, const c64* src, int nrhs, hipStream_t stream);
 int launch_convert16(dwf_op* op, c64* dst, const bf16c* src, int nrhs, hipStream_t stream);
 
-// the hop launch-shape candidates of the autotuner: their number, and
-// candidate c as {bx, by, bz, bt, remap, order, rhs per workgroup} (false: it
-// does not fit, and the default block stands in)
+// the number of the autotuner's launch-shape candidates
 int hop_shape_candidates();
-bool hop_shape_of(const dwf_op* op, int prec, int c, int shape[7]);
+// The launch shape of the hop stages on fields of one storage: the fixed one,
+// or the autotuner's choice for (storage, one or several right-hand sides),
+// the default where it has not run.  No other storage's or count's choice
+// enters, so a call does what it does on a fresh operator.
+HopTune hop_shape(const dwf_op* op, int prec, int nrhs);
 
 int ensure_tmp(dwf_op* op, int prec, int nrhs);
 void release_tmp(dwf_op* op);  // drop the operator's work fields (regrown on demand)

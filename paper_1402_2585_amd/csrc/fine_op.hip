@@ -1039,7 +1039,7 @@ static const int* hop_order_table(dwf_op* op, const HopArgs& A, int kind, hipStr
 }
 
 template <typename R, typename T = cplx<R>>
-static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
+static int hop_launch(dwf_op* op, const HopTune& tune, T* out, const T* in, const T* center,
                       bool dagger, int epi, int out_parity, int nrhs, hipStream_t stream,
                       double* norm_result, const CgStep* cg = nullptr, const void* cg_p = nullptr,
                       double* alpha = nullptr) {
@@ -1063,8 +1063,8 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   A.bx = A.by = A.bz = A.bt = 0;
   A.lbx = A.lby = A.lbz = 0;
   A.nbx = A.nby = A.nbz = 1;
-  A.remap = op->tune.remap;
-  A.nt = op->tune.nt;
+  A.remap = tune.remap;
+  A.nt = tune.nt;
   A.morton = 0;
   A.nbt = 1;
   A.order = nullptr;
@@ -1072,9 +1072,9 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
   A.fold = 0;
   const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
   // a block of more than 256 / Ls sites is marched along t where that fits
-  const int* b = op->tune.block;
+  const int* b = tune.block;
   const bool march = b[0] * b[1] * b[2] * b[3] * g.Ls > 256 && march_fits(g, op->f5.mobius, prec, b);
-  A.rg = split ? std::max(1, std::min(op->tune.rg, nrhs)) : 1;
+  A.rg = split ? std::max(1, std::min(tune.rg, nrhs)) : 1;
   {
     auto pow2 = [](int n) { return n > 0 && (n & (n - 1)) == 0; };
     if (b[0] > 0 && pow2(b[0]) && pow2(b[1]) && pow2(b[2]) && pow2(b[3]) &&
@@ -1095,10 +1095,10 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
       A.lby = __builtin_ctz(b[1]);
       A.lbz = __builtin_ctz(b[2]);
       const bool p2 = pow2(A.nbx) && pow2(A.nby) && pow2(A.nbz) && pow2(A.nbt);
-      A.morton = op->tune.morton != 0 && p2;
-      if (op->tune.morton >= 2 && A.nbx <= 256 && A.nby <= 256 && A.nbz <= 256 && A.nbt <= 128) {
+      A.morton = tune.morton != 0 && p2;
+      if (tune.morton >= 2 && A.nbx <= 256 && A.nby <= 256 && A.nbz <= 256 && A.nbt <= 128) {
         int rc = DWF_OK;
-        A.order = hop_order_table(op, A, op->tune.morton, stream, &rc);
+        A.order = hop_order_table(op, A, tune.morton, stream, &rc);
         HDCG_TRY(rc);
       }
     }
@@ -1160,10 +1160,10 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
       !split && (epi == EPI_INV || (mob && dagger)) ? (size_t)A.spw * 12 * (g.Ls + 1) * sizeof(cplx<R>) : 0;
   const size_t link_lds = (size_t)A.spw * kLinkLd * sizeof(cplx<R>);
   // optional LDS request that caps the resident workgroups per CU
-  const size_t lds = std::max(std::max(epi_lds, link_lds), (size_t)op->tune.lds_kb * 1024);
+  const size_t lds = std::max(std::max(epi_lds, link_lds), (size_t)tune.lds_kb * 1024);
   // Ls > 16: directions whose neighbour loads are in flight together, 8 /
   // phases (the Mobius kernels are built for four phases only)
-  const int phases = op->tune.phases > 0 ? op->tune.phases : (sizeof(R) == 8 ? 4 : 2);
+  const int phases = tune.phases > 0 ? tune.phases : (sizeof(R) == 8 ? 4 : 2);
   // Up to 2048 workgroups of four waves fill the chip at once: the last to
   // end sums the norm's partials, which costs it about as much as the
   // finalize kernel's launch costs the stream twice (CG in complex128 on 8^3
@@ -1188,18 +1188,25 @@ static int hop_launch(dwf_op* op, T* out, const T* in, const T* center,
 }
 
 template <typename R, typename T>
-int launch_mpc(dwf_op* op, T* out, const T* in, bool dagger, int nrhs, hipStream_t stream,
-               double* norm_result) {
+static int mpc_stages(dwf_op* op, const HopTune& tune, T* out, const T* in, bool dagger, int nrhs, hipStream_t stream,
+                      double* norm_result) {
   const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
   if (kSMajor<T> && (!aligned16(out) || !aligned16(in)))
     return fail(DWF_ERR_ARG, "16-bit fields must be 16-byte aligned");
   HDCG_TRY(ensure_tmp(op, prec, nrhs));
   T* te = op->tmp[tmp_index(prec)][0].as<T>();
   // stage 1: t_e = M_5^-1 Dh_eo in    (adjoint: M_5^-+ Dh^+_eo in)
-  HDCG_TRY((hop_launch<R, T>(op, te, in, nullptr, dagger, EPI_INV, 0, nrhs, stream, nullptr)));
+  HDCG_TRY((hop_launch<R, T>(op, tune, te, in, nullptr, dagger, EPI_INV, 0, nrhs, stream, nullptr)));
   // stage 2: out = M_5 in - 1/4 Dh_oe t_e  (adjoint: M_5^+ in - 1/4 Dh^+_oe t_e)
-  HDCG_TRY((hop_launch<R, T>(op, out, te, in, dagger, EPI_SUB, 1, nrhs, stream, norm_result)));
+  HDCG_TRY((hop_launch<R, T>(op, tune, out, te, in, dagger, EPI_SUB, 1, nrhs, stream, norm_result)));
   return DWF_OK;
+}
+
+template <typename R, typename T>
+int launch_mpc(dwf_op* op, T* out, const T* in, bool dagger, int nrhs, hipStream_t stream,
+               double* norm_result) {
+  const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
+  return mpc_stages<R, T>(op, hop_shape(op, prec, nrhs), out, in, dagger, nrhs, stream, norm_result);
 }
 
 // ------------------------------------------------ launch-shape autotuner --
@@ -1237,12 +1244,13 @@ int hop_shape_candidates() { return kNumHopShapes; }
 // planes, a power of two dividing T and at least 4 (a chunk loads two planes
 // of its neighbours' columns besides its own), that leave `march`
 // workgroups; where none fits, the default block stands in.
-bool hop_shape_of(const dwf_op* op, int prec, int c, int shape[7]) {
+static bool hop_candidate(const dwf_op* op, int prec, int c, HopTune* shape) {
   const HopShape& s = kHopShapes[c];
-  for (int i = 0; i < 4; ++i) shape[i] = s.block[i];
-  shape[4] = s.remap;
-  shape[5] = s.order;
-  shape[6] = s.rg;
+  *shape = HopTune();
+  for (int i = 0; i < 4; ++i) shape->block[i] = s.block[i];
+  shape->remap = s.remap;
+  shape->morton = s.order;
+  shape->rg = s.rg;
   if (!s.march) return true;
   const Geom& g = op->g;
   int best = 0;
@@ -1253,28 +1261,28 @@ bool hop_shape_of(const dwf_op* op, int prec, int c, int shape[7]) {
       best = n;
   }
   if (best)
-    shape[3] = best;
+    shape->block[3] = best;
   else
-    for (int i = 0; i < 4; ++i) shape[i] = kHopShapes[0].block[i];
+    for (int i = 0; i < 4; ++i) shape->block[i] = kHopShapes[0].block[i];
   return best != 0;
 }
 
-static void apply_shape(dwf_op* op, int prec, int c) {
-  int s[7];
-  (void)hop_shape_of(op, prec, c, s);
-  for (int i = 0; i < 4; ++i) op->tune.block[i] = s[i];
-  op->tune.remap = s[4];
-  op->tune.morton = s[5];
-  op->tune.rg = s[6];
+HopTune hop_shape(const dwf_op* op, int prec, int nrhs) {
+  if (!op->hop_autotune) return op->tune;
+  const int c = op->hop_choice[tmp_index(prec)][nrhs > 1];
+  HopTune shape;
+  (void)hop_candidate(op, prec, c < 0 ? 0 : c, &shape);
+  return shape;
 }
 
 template <typename R, typename T>
-static int apply_mpcdagmpc(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t stream, double* pap_result) {
+static int apply_mpcdagmpc(dwf_op* op, const HopTune& tune, T* out, const T* in, int nrhs, hipStream_t stream,
+                           double* pap_result) {
   const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
   HDCG_TRY(ensure_tmp(op, prec, nrhs));
   T* chi = op->tmp[tmp_index(prec)][1].as<T>();
-  HDCG_TRY((launch_mpc<R, T>(op, chi, in, false, nrhs, stream, pap_result)));
-  HDCG_TRY((launch_mpc<R, T>(op, out, chi, true, nrhs, stream, nullptr)));
+  HDCG_TRY((mpc_stages<R, T>(op, tune, chi, in, false, nrhs, stream, pap_result)));
+  HDCG_TRY((mpc_stages<R, T>(op, tune, out, chi, true, nrhs, stream, nullptr)));
   return DWF_OK;
 }
 
@@ -1283,17 +1291,12 @@ static int apply_mpcdagmpc(dwf_op* op, T* out, const T* in, int nrhs, hipStream_
 // H per candidate, timed with HIP events on the stream), unless the stream is
 // being captured into a graph (then the default until a later call tunes).
 template <typename R, typename T>
-static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t st) {
-  if (!op->hop_autotune) return DWF_OK;
+static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t st, HopTune* shape) {
   const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
   const int pi = tmp_index(prec), ri = nrhs > 1;
   int& choice = op->hop_choice[pi][ri];
-  if (choice < 0) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-      apply_shape(op, prec, 0);
-      return DWF_OK;
-    }
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (op->hop_autotune && choice < 0 && hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
     hipEvent_t e0, e1;
     HDCG_HIP(hipEventCreate(&e0));
     HDCG_HIP(hipEventCreate(&e1));
@@ -1302,18 +1305,17 @@ static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t s
     for (int c = 0; c < kNumHopShapes && rc == DWF_OK; ++c) {
       op->hop_ms[pi][ri][c] = -1.f;
       if (kHopShapes[c].rg > 1 && nrhs == 1) continue;  // the same as its one-RHS form
-      int shape[7];
-      if (!hop_shape_of(op, prec, c, shape)) {
+      HopTune t;
+      if (!hop_candidate(op, prec, c, &t)) {
         op->hop_ms[pi][ri][c] = op->hop_ms[pi][ri][0];  // runs as the default block does
         continue;
       }
-      apply_shape(op, prec, c);
-      rc = apply_mpcdagmpc<R, T>(op, out, in, nrhs, st, nullptr);
+      rc = apply_mpcdagmpc<R, T>(op, t, out, in, nrhs, st, nullptr);
       float m = 1e30f;
       for (int rep = 0; rep < 3 && rc == DWF_OK; ++rep) {
         float x = 0.f;
         if (hipEventRecord(e0, st) != hipSuccess) rc = fail(DWF_ERR_HIP, "hop autotuner event failed");
-        if (rc == DWF_OK) rc = apply_mpcdagmpc<R, T>(op, out, in, nrhs, st, nullptr);
+        if (rc == DWF_OK) rc = apply_mpcdagmpc<R, T>(op, t, out, in, nrhs, st, nullptr);
         if (rc == DWF_OK && (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                              hipEventElapsedTime(&x, e0, e1) != hipSuccess))
           rc = fail(DWF_ERR_HIP, "hop autotuner event failed");
@@ -1330,7 +1332,7 @@ static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t s
     HDCG_TRY(rc);
     choice = best;
   }
-  apply_shape(op, prec, choice);
+  *shape = hop_shape(op, prec, nrhs);
   return DWF_OK;
 }
 
@@ -1340,8 +1342,9 @@ template <typename R, typename T>
 int launch_cg_norm(dwf_op* op, const T* p, int nrhs, double* pap, hipStream_t stream) {
   const int pi = tmp_index(std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>());
   HDCG_TRY((ensure_tmp(op, std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>(), nrhs)));
-  HDCG_TRY((select_shape<R, T>(op, op->tmp[pi][2].as<T>(), p, nrhs, stream)));
-  return launch_mpc<R, T>(op, op->tmp[pi][1].as<T>(), p, false, nrhs, stream, pap);
+  HopTune tune;
+  HDCG_TRY((select_shape<R, T>(op, op->tmp[pi][2].as<T>(), p, nrhs, stream, &tune)));
+  return mpc_stages<R, T>(op, tune, op->tmp[pi][1].as<T>(), p, false, nrhs, stream, pap);
 }
 
 template <typename R, typename T>
@@ -1352,21 +1355,23 @@ int launch_cg_residual(dwf_op* op, T* r, const T* p, int nrhs, const CgStep& cg,
   T* te = op->tmp[pi][0].as<T>();
   T* chi = op->tmp[pi][1].as<T>();
   T* w = op->tmp[pi][2].as<T>();
-  HDCG_TRY((select_shape<R, T>(op, w, p, nrhs, stream)));
-  HDCG_TRY((hop_launch<R, T>(op, te, p, nullptr, false, EPI_INV, 0, nrhs, stream, nullptr)));
-  HDCG_TRY((hop_launch<R, T>(op, chi, te, p, false, EPI_SUB, 1, nrhs, stream, cg.pap, &cg, nullptr, cg.alpha)));
-  HDCG_TRY((hop_launch<R, T>(op, te, chi, nullptr, true, EPI_INV, 0, nrhs, stream, nullptr)));
+  HopTune tune;
+  HDCG_TRY((select_shape<R, T>(op, w, p, nrhs, stream, &tune)));
+  HDCG_TRY((hop_launch<R, T>(op, tune, te, p, nullptr, false, EPI_INV, 0, nrhs, stream, nullptr)));
+  HDCG_TRY((hop_launch<R, T>(op, tune, chi, te, p, false, EPI_SUB, 1, nrhs, stream, cg.pap, &cg, nullptr, cg.alpha)));
+  HDCG_TRY((hop_launch<R, T>(op, tune, te, chi, nullptr, true, EPI_INV, 0, nrhs, stream, nullptr)));
   if (op->g.Ls <= 16)
-    return hop_launch<R, T>(op, r, te, chi, true, EPI_RES, 1, nrhs, stream, cg.rr, &cg, p, cg.alpha);
-  HDCG_TRY((hop_launch<R, T>(op, w, te, chi, true, EPI_SUB, 1, nrhs, stream, nullptr)));
+    return hop_launch<R, T>(op, tune, r, te, chi, true, EPI_RES, 1, nrhs, stream, cg.rr, &cg, p, cg.alpha);
+  HDCG_TRY((hop_launch<R, T>(op, tune, w, te, chi, true, EPI_SUB, 1, nrhs, stream, nullptr)));
   return b_cg_r(Red{op->red.partials.as<double>(), op->red.counters.as<unsigned>()}, r, p, w, op->field_elems(1), nrhs,
                 cg.alpha, cg.lam, cg.rr, cg.rr_host, stream);
 }
 
 template <typename R, typename T>
 int launch_mpcdagmpc(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t stream, double* pap_result) {
-  HDCG_TRY((select_shape<R, T>(op, out, in, nrhs, stream)));
-  return apply_mpcdagmpc<R, T>(op, out, in, nrhs, stream, pap_result);
+  HopTune tune;
+  HDCG_TRY((select_shape<R, T>(op, out, in, nrhs, stream, &tune)));
+  return apply_mpcdagmpc<R, T>(op, tune, out, in, nrhs, stream, pap_result);
 }
 
 template <typename R, typename T>
