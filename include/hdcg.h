@@ -129,9 +129,10 @@ int dwf_destroy(dwf_op_t op);
  * By default the block, remap, order and rg entries are chosen by the library's
  * autotuner: the first application of H for a field storage (complex128,
  * complex64, 16-bit) and for one or several right-hand sides times each
- * candidate block / order on that call's own operands (one warm-up, best of
- * three with HIP events; skipped while the stream is being captured) and
- * keeps the fastest for the operator; the other entries are
+ * candidate block / order on that call's own operands, back to back for some
+ * milliseconds where H fills the chip (about 0.1 s in all; 10 ms on small
+ * lattices; skipped while the stream is being captured), and
+ * keeps the fastest for that storage and count; the other entries are
  * {lds_kb 0, nt 0, phases 0}.  This call fixes a shape instead
  * (launch-shape sweeps and their tests); shape[0] = -1 returns to the
  * autotuned shapes.  DWF_ERR_ARG on an invalid entry. */
@@ -146,7 +147,7 @@ int dwf_get_hop_shape(dwf_op_t op, int prec, int nrhs, int shape[10], float* ms,
 
 /* Run the hop launch-shape autotuner now for (prec DWF_C128 / DWF_C64 /
  * DWF_BF16, one or several right-hand sides; nrhs sizes its trial fields)
- * on zero fields the call allocates and frees (2 x nrhs fields, plus the
+ * on fields of its own that the call allocates and frees (2 x nrhs fields, plus the
  * operator's work fields), so that a later timed application does not pay
  * the trials.  Nothing happens when that slot is tuned already or a fixed
  * shape is set.  Synchronises.  DWF_ERR_OOM when the trial fields do not

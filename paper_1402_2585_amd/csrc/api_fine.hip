@@ -577,7 +577,11 @@ int dwf_tune_hop(dwf_op_t op, int prec, int nrhs, void* stream) {
   DevBuf a, b;
   HDCG_TRY(a.ensure(bytes));
   HDCG_TRY(b.ensure(bytes));
-  int rc = hipMemsetAsync(a.ptr, 0, bytes, st) == hipSuccess ? DWF_OK : fail(DWF_ERR_HIP, "dwf_tune_hop: memset failed");
+  // not zeros: those take less power, and the ranking depends on it
+  const size_t n = op->field_elems(nrhs);
+  int rc = prec == DWF_C128   ? launch_noise(a.as<c128>(), n, st)
+           : prec == DWF_BF16 ? launch_noise(a.as<bf16c>(), n, st)
+                              : launch_noise(a.as<c64>(), n, st);
   if (rc == DWF_OK) rc = mpc_dag_mpc_apply(op, b.ptr, a.ptr, prec, nrhs, stream);
   if (rc == DWF_OK && hipStreamSynchronize(st) != hipSuccess) rc = fail(DWF_ERR_HIP, "dwf_tune_hop: sync failed");
   a.release();

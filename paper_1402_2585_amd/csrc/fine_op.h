@@ -169,6 +169,10 @@ int launch_convert(Td* dst, const Ts* src, size_t n, hipStream_t stream);
 int launch_convert16(dwf_op* op, bf16c* dst, const c64* src, int nrhs, hipStream_t stream);
 int launch_convert16(dwf_op* op, c64* dst, const bf16c* src, int nrhs, hipStream_t stream);
 
+// x = n values uniform in [-1, 1) in both parts (T: c128, c64 or bf16c)
+template <typename T>
+int launch_noise(T* x, size_t n, hipStream_t stream);
+
 // the number of the autotuner's launch-shape candidates
 int hop_shape_candidates();
 // The launch shape of the hop stages on fields of one storage: the fixed one,

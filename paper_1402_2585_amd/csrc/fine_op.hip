@@ -112,6 +112,19 @@ __global__ void field_layout_kernel(cplx<R>* __restrict__ dst, const cplx<R>* __
     dst[can] = src[idx];
 }
 
+// uniform values in [-1, 1) from the element's index (splitmix64)
+template <typename T>
+__global__ void noise_kernel(T* __restrict__ x, size_t n) {
+  using R = typename St<T>::R;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    unsigned long long z = (i + 1) * 0x9e3779b97f4a7c15ull;
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+    z ^= z >> 31;
+    St<T>::st(x + i, cmk((R)(int)(unsigned)z * (R)0x1p-31, (R)(int)(unsigned)(z >> 32) * (R)0x1p-31));
+  }
+}
+
 // dst (stored as Td) = src (stored as Ts), rounded to nearest (even)
 template <typename Td, typename Ts>
 __global__ void convert_kernel(Td* __restrict__ dst, const Ts* __restrict__ src, size_t n) {
@@ -1287,9 +1300,82 @@ static int apply_mpcdagmpc(dwf_op* op, const HopTune& tune, T* out, const T* in,
 }
 
 // The shape for (storage, right-hand sides): tuned on this call's own
-// operands the first time (one warm-up and the best of three applications of
-// H per candidate, timed with HIP events on the stream), unless the stream is
+// operands the first time, with HIP events on the stream, unless the stream is
 // being captured into a graph (then the default until a later call tunes).
+//
+// A candidate's figure is its mean over back-to-back applications of H.  Where
+// H fills the chip (100 us and more) its power sets the clock, some
+// milliseconds after it starts, and not alike for all candidates: first the
+// default runs for 8 ms, every candidate for 1 ms (three applications at least),
+// then the three fastest in turn, twice, for 4 ms each, which decides.  The best of three single
+// applications ranked differently: 16-bit fields, 8 right-hand sides on 16^3 x
+// 32 x 16, {1,2,2,1} in order 4 1.34 ms and {2,2,1,1} with rg 16 1.43 ms there
+// (on zero fields, which take less power), 1.55 and 1.53 ms sustained.
+template <typename R, typename T>
+static int tune_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t st, float* ms, int* best) {
+  const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  // mean milliseconds of `reps` applications
+  auto timed = [&](const HopTune& t, int reps, float* mean) {
+    if (hipEventRecord(e0, st) != hipSuccess) return fail(DWF_ERR_HIP, "hop autotuner event failed");
+    for (int i = 0; i < reps; ++i) HDCG_TRY((apply_mpcdagmpc<R, T>(op, t, out, in, nrhs, st, nullptr)));
+    if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+        hipEventElapsedTime(mean, e0, e1) != hipSuccess)
+      return fail(DWF_ERR_HIP, "hop autotuner event failed");
+    *mean /= (float)reps;
+    return (int)DWF_OK;
+  };
+  auto run = [&]() {
+    HopTune t[kNumHopShapes];
+    bool own[kNumHopShapes];
+    for (int c = 0; c < kNumHopShapes; ++c) {
+      ms[c] = -1.f;
+      own[c] = hop_candidate(op, prec, c, &t[c]) && !(kHopShapes[c].rg > 1 && nrhs == 1);
+    }
+    float x = 0.f;
+    HDCG_TRY(timed(t[0], 1, &x));
+    HDCG_TRY(timed(t[0], 2, &x));
+    const bool full = x >= 0.1f;
+    auto reps = [&](float total, float one) { return std::max(3, (int)(total / std::max(one, 1e-3f))); };
+    if (full) HDCG_TRY(timed(t[0], reps(8.f, x), &x));
+    for (int c = 0; c < kNumHopShapes; ++c) {
+      if (!own[c]) continue;
+      HDCG_TRY(timed(t[c], 1, &x));
+      HDCG_TRY(timed(t[c], full ? reps(1.f, x) : 8, &ms[c]));
+    }
+    int order[kNumHopShapes], n = 0;
+    for (int c = 0; c < kNumHopShapes; ++c)
+      if (own[c]) order[n++] = c;
+    std::stable_sort(order, order + n, [&](int a, int b) { return ms[a] < ms[b]; });
+    *best = order[0];
+    if (full) {
+      const int k = std::min(n, 3);
+      float sum[3] = {0.f, 0.f, 0.f};
+      for (int turn = 0; turn < 2; ++turn)
+        for (int i = 0; i < k; ++i) {
+          HDCG_TRY(timed(t[order[i]], reps(4.f, ms[order[i]]), &x));
+          sum[i] += 0.5f * x;
+        }
+      int win = 0;
+      for (int i = 0; i < k; ++i) {
+        ms[order[i]] = sum[i];
+        if (sum[i] < sum[win]) win = i;
+      }
+      *best = order[win];
+    }
+    // a tile that does not fit runs as the default block does
+    for (int c = 0; c < kNumHopShapes; ++c)
+      if (!own[c] && !(kHopShapes[c].rg > 1 && nrhs == 1)) ms[c] = ms[0];
+    return (int)DWF_OK;
+  };
+  int rc = hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess
+               ? run()
+               : fail(DWF_ERR_HIP, "hop autotuner event failed");
+  if (e0) (void)hipEventDestroy(e0);
+  if (e1) (void)hipEventDestroy(e1);
+  return rc;
+}
+
 template <typename R, typename T>
 static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t st, HopTune* shape) {
   const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
@@ -1297,39 +1383,8 @@ static int select_shape(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t s
   int& choice = op->hop_choice[pi][ri];
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (op->hop_autotune && choice < 0 && hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
-    hipEvent_t e0, e1;
-    HDCG_HIP(hipEventCreate(&e0));
-    HDCG_HIP(hipEventCreate(&e1));
-    int rc = DWF_OK, best = 0;
-    float bms = 0.f;
-    for (int c = 0; c < kNumHopShapes && rc == DWF_OK; ++c) {
-      op->hop_ms[pi][ri][c] = -1.f;
-      if (kHopShapes[c].rg > 1 && nrhs == 1) continue;  // the same as its one-RHS form
-      HopTune t;
-      if (!hop_candidate(op, prec, c, &t)) {
-        op->hop_ms[pi][ri][c] = op->hop_ms[pi][ri][0];  // runs as the default block does
-        continue;
-      }
-      rc = apply_mpcdagmpc<R, T>(op, t, out, in, nrhs, st, nullptr);
-      float m = 1e30f;
-      for (int rep = 0; rep < 3 && rc == DWF_OK; ++rep) {
-        float x = 0.f;
-        if (hipEventRecord(e0, st) != hipSuccess) rc = fail(DWF_ERR_HIP, "hop autotuner event failed");
-        if (rc == DWF_OK) rc = apply_mpcdagmpc<R, T>(op, t, out, in, nrhs, st, nullptr);
-        if (rc == DWF_OK && (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                             hipEventElapsedTime(&x, e0, e1) != hipSuccess))
-          rc = fail(DWF_ERR_HIP, "hop autotuner event failed");
-        m = std::min(m, x);
-      }
-      op->hop_ms[pi][ri][c] = m;
-      if (rc == DWF_OK && (c == 0 || m < bms)) {
-        bms = m;
-        best = c;
-      }
-    }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    HDCG_TRY(rc);
+    int best = 0;
+    HDCG_TRY((tune_shape<R, T>(op, out, in, nrhs, st, op->hop_ms[pi][ri], &best)));
     choice = best;
   }
   *shape = hop_shape(op, prec, nrhs);
@@ -1446,6 +1501,16 @@ int launch_convert16(dwf_op* op, c64* dst, const bf16c* src, int nrhs, hipStream
   HDCG_HIP(hipGetLastError());
   return DWF_OK;
 }
+
+template <typename T>
+int launch_noise(T* x, size_t n, hipStream_t stream) {
+  hipLaunchKernelGGL((noise_kernel<T>), dim3(red_blocks(n)), dim3(256), 0, stream, x, n);
+  HDCG_HIP(hipGetLastError());
+  return DWF_OK;
+}
+template int launch_noise<c128>(c128*, size_t, hipStream_t);
+template int launch_noise<c64>(c64*, size_t, hipStream_t);
+template int launch_noise<bf16c>(bf16c*, size_t, hipStream_t);
 
 template <typename Td, typename Ts>
 int launch_convert(Td* dst, const Ts* src, size_t n, hipStream_t stream) {
