@@ -39,12 +39,6 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// bytes of LDS of a tile of npair pairs (tb, rb: bytes of a stored and of a
-// link entry)
-inline size_t march_lds(int npair, int Ls, size_t tb, size_t rb) {
-  return ((size_t)3 * npair * 12 * Ls * tb + 15) / 16 * 16 + (size_t)npair * kLinkLd * rb;
-}
-
 // Keeps a direction's arithmetic in place: otherwise it is moved behind the
 // next plane's loads, with all its operands in registers.
 template <typename R>

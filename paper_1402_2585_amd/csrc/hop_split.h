@@ -20,7 +20,7 @@
 // recurrence of M_5^-1 is a scan of log2(Ls) steps and one step more.
 #pragma once
 
-#include "fine_op.h"
+#include "hop_dev.h"
 
 namespace hdk {
 

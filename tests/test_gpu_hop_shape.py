@@ -1,10 +1,12 @@
 """The hop's launch shape belongs to a field storage and to one or several
 right-hand sides: what the autotuner chose for one does not enter another's
 calls."""
+import numpy as np
 import pytest
 
 import synth
-from tests.gpu_util import banner
+from oracle.dwf import DWF
+from tests.gpu_util import banner, rel_err
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -43,3 +45,34 @@ def test_a_choice_stays_with_its_storage_and_count():
     assert tuple(hd.dwf_get_hop_shape(op.h, hd.DWF_C128, 1)[0]) == DEFAULT
     op.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("mobius", [False, True])
+@pytest.mark.parametrize("Ls", [6, 10, 14])
+def test_even_ls_against_oracle(Ls, mobius):
+    """The even Ls with code of their own that no other test covers, on
+    several right-hand sides at once and one, straight-line and looping.
+    Tolerances as for the other fine-operator tests."""
+    dims, nr = (6, 4, 4, 4), 3
+    banner(f"hop Ls{Ls} mobius={mobius}")
+    U = synth.gauge_field(dims, 0.7, 173 + Ls)
+    op = hd.FineOperator(U, dims, Ls, 1.8, 0.02, **(dict(b5=1.5, c5=0.5) if mobius else {}))
+    ref = DWF(U, dims, Ls, 1.8, 0.02, **({"b": 1.5, "c": 0.5} if mobius else {}))
+    b = synth.gaussian_half_field(dims, Ls, 174 + Ls, nrhs=nr)
+    for shape in ((0, 0, 0, 0, 0, 0, 0, 0, 0, 1), (1, 2, 2, 2, 0, 0, 0, 0, 0, 2)):
+        hd.dwf_set_hop_shape(op.h, shape)
+        for n in (1, nr):
+            want = [ref.H(v) for v in b[:n]]
+            for prec, tol in ((hd.DWF_C128, 1e-12), (hd.DWF_C64, 5e-6)):
+                got = op.to_canonical(op.H(op.to_native(b[:n], prec), prec, n), prec, n).cpu().numpy().reshape(b[:n].shape)
+                for r in range(n):
+                    assert rel_err(got[r], want[r]) < tol, (shape, n, prec, r)
+            # 16 bits: four stored fields round to 2^-8 each
+            x16 = op.convert(op.to_native(b[:n], hd.DWF_C64), hd.DWF_BF16, hd.DWF_C64, n)
+            xin = op.to_canonical(op.convert(x16, hd.DWF_C64, hd.DWF_BF16, n), hd.DWF_C64, n).cpu().numpy().reshape(b[:n].shape)
+            y = op.convert(op.H(x16, hd.DWF_BF16, n), hd.DWF_C64, hd.DWF_BF16, n)
+            got = op.to_canonical(y, hd.DWF_C64, n).cpu().numpy().reshape(b[:n].shape)
+            for r in range(n):
+                exact = ref.H(xin[r].astype(np.complex128))
+                assert np.linalg.norm((got[r] - exact).ravel()) / np.linalg.norm(exact.ravel()) < 4 * 2.0 ** -8, (shape, n, r)
+    op.close()
