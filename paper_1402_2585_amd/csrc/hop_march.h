@@ -244,7 +244,7 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
     split_finish<R, DAG, EPI, LS, false>(acc, U, L, cx, cy, q, Ls, A, inv);
     {
       if (EPI == EPI_RES) split_residual<R, T>(acc, rv, pv, A, rhs);
-      if (EPI != EPI_INV && active) {
+      if (EPI != EPI_INV && A.partials && active) {
 #pragma unroll
         for (int c = 0; c < 3; ++c)
           nrm += (double)acc[c].re * (double)acc[c].re + (double)acc[c].im * (double)acc[c].im;

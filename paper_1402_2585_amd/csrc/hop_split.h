@@ -586,7 +586,7 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
       cplx<R> acc[3];
       split_finish<R, DAG, EPI, LS, MOB>(acc, U, L, cx, cy, q, Ls, A, inv);
       if (EPI == EPI_RES) split_residual<R, T>(acc, rv, pv, A, rhs);
-      if (EPI != EPI_INV && active) {
+      if (EPI != EPI_INV && A.partials && active) {
 #pragma unroll
         for (int k = 0; k < 3; ++k)
           nrm += (double)acc[k].re * (double)acc[k].re + (double)acc[k].im * (double)acc[k].im;
