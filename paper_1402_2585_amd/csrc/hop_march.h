@@ -16,8 +16,8 @@
 // eight).  The next plane's column, links, face neighbours and centre values
 // are loaded while this plane is computed; one barrier per plane.
 //
-// Lanes and arithmetic are hop_split_kernel's: the results are the same up to
-// the compiler's choice of fused multiply-adds.
+// Lanes and arithmetic are hop_split_kernel's: the results are the same, bit
+// for bit.
 //
 // What bounds it now: in complex64 the vector units (600 instructions a site
 // and plane, 4 waves a SIMD) as much as HBM; a workgroup's 16 waves fill a
@@ -247,7 +247,7 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
       if (EPI != EPI_INV && A.partials && active) {
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-          nrm += (double)acc[c].re * (double)acc[c].re + (double)acc[c].im * (double)acc[c].im;
+          nrm = fma((double)acc[c].im, (double)acc[c].im, fma((double)acc[c].re, (double)acc[c].re, nrm));
       }
       if (active) tri_st<T>(out + rhs * A.field + (size_t)(own + plane * t) * col + offo, cs, acc, A.nt & 1);
       {

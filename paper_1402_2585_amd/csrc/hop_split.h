@@ -24,6 +24,12 @@
 
 namespace hdk {
 
+// The arithmetic of a stage is written with explicit fused multiply-adds, and
+// the compiler forms no others in the functions that begin with this: every
+// kernel they are part of (split or marched, one or several right-hand sides,
+// any launch shape) gives the same bits.
+#define HDCG_PINNED _Pragma("clang fp contract(off)")
+
 constexpr int kDppShl = 0x100, kDppShr = 0x110, kDppRor = 0x120;
 constexpr int kRowsUp = 0x5, kRowsDn = 0xa;  // rows that end with upper (P+) and lower (P-) spins
 
@@ -154,6 +160,7 @@ __device__ __forceinline__ cplx<R> tri_get(const cplx<R> (&t)[3], int c) {
 template <int KIND, bool FIRST = false, typename R, typename V>
 __device__ __forceinline__ void split_dir(cplx<R> (&U)[3], cplx<R> (&L)[3], const V& u, const V& l,
                                           const cplx<R>* __restrict__ w, R g) {
+  HDCG_PINNED
   cplx<R> h[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -163,7 +170,7 @@ __device__ __forceinline__ void split_dir(cplx<R> (&U)[3], cplx<R> (&L)[3], cons
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     const cplx<R> w0 = w[a * 3 + 0], w1 = w[a * 3 + 1], w2 = w[a * 3 + 2];
-    cplx<R> t = w0 * h[0];
+    cplx<R> t = cmk(fma(-w0.im, h[0].im, w0.re * h[0].re), fma(w0.im, h[0].re, w0.re * h[0].im));
     cmac(t, w1, h[1]);
     cmac(t, w2, h[2]);
     if (FIRST) {
@@ -171,7 +178,8 @@ __device__ __forceinline__ void split_dir(cplx<R> (&U)[3], cplx<R> (&L)[3], cons
       L[a] = KIND == 0 ? cmk(-g * t.im, g * t.re) : cmk(g * t.re, g * t.im);
       continue;
     }
-    U[a] = U[a] + t;
+    U[a].re += t.re;
+    U[a].im += t.im;
     if (KIND == 0) {
       L[a].re = fma(-g, t.im, L[a].re);
       L[a].im = fma(g, t.re, L[a].im);
@@ -180,6 +188,13 @@ __device__ __forceinline__ void split_dir(cplx<R> (&U)[3], cplx<R> (&L)[3], cons
       L[a].im = fma(g, t.im, L[a].im);
     }
   }
+}
+
+// b x + c y
+template <typename R>
+__device__ __forceinline__ cplx<R> split_c5(R b, cplx<R> x, R c, cplx<R> y) {
+  HDCG_PINNED
+  return cmk(fma(b, x.re, c * y.re), fma(b, x.im, c * y.im));
 }
 
 // Where a lane stands in its wave.
@@ -200,14 +215,15 @@ __device__ __forceinline__ R s_shift(R x, int src_lane) {
 // -m times the wrapped entry at the wall
 template <int LS, int MUP, typename R>
 __device__ __forceinline__ void split_bcs(cplx<R> (&v)[3], const SplitLane& q, int Ls, R b, R c, R m) {
+  HDCG_PINNED
   const bool up = (MUP >> q.row) & 1;
   const int sn = up ? (q.s + 1 < Ls ? q.s + 1 : 0) : (q.s > 0 ? q.s - 1 : Ls - 1);
   const R w = (up ? q.s + 1 < Ls : q.s > 0) ? c : -m * c;
   const int lane = q.row * 16 + q.sub * Ls + sn;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    v[k].re = b * v[k].re + w * s_shift<LS, MUP>(v[k].re, lane);
-    v[k].im = b * v[k].im + w * s_shift<LS, MUP>(v[k].im, lane);
+    v[k].re = fma(b, v[k].re, w * s_shift<LS, MUP>(v[k].re, lane));
+    v[k].im = fma(b, v[k].im, w * s_shift<LS, MUP>(v[k].im, lane));
   }
 }
 
@@ -318,7 +334,7 @@ __device__ __forceinline__ void split_inv16(cplx<float> (&x)[3], const InvCoef<f
 // of the O(Ls) recurrence (FP32, Ls 16: 5.6e-8 against 3.7e-8 or 2.9e-8 with
 // either choice of fused multiply-adds; with it 2.9e-8).  H against 64 bits,
 // recurrence, scan alone, with the step: complex64 on 8^3 x 16 x 16 8.00e-8,
-// 8.08e-8, 7.69e-8; complex128 on 16^4 x 16 1.910e-16, 1.952e-16, 1.896e-16.
+// 8.08e-8, 7.69e-8; complex128 on 16^4 x 16 1.910e-16, 1.952e-16, 1.902e-16.
 //   Ls = 16: shifts round the whole row, t = (1 + k S)(1 + k^2 S^2) ... x
 //     = (1 + mass kap^16) y, and y = x + kap / (1 + mass kap^16) S t;
 //   else: z from z_{-1} = 0, and with c_s = mass kap^s / (1 + mass kap^Ls)
@@ -327,9 +343,11 @@ __device__ __forceinline__ void split_inv16(cplx<float> (&x)[3], const InvCoef<f
 // to 16 bits next (2^-8 against a few 2^-24).
 template <int LS, int MLOW, bool LAST, typename R>
 __device__ __forceinline__ void split_m5inv(cplx<R> (&x)[3], const SplitLane& q, int Ls, const InvCoef<R>& k, R ia) {
+  HDCG_PINNED
   if constexpr (!LAST) {
+    const R f = LS == 16 ? k.last : ia;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) x[c] = (LS == 16 ? k.last : ia) * x[c];
+    for (int c = 0; c < 3; ++c) x[c] = cmk(f * x[c].re, f * x[c].im);
   }
   if constexpr (LS == 16 && sizeof(R) == 4) {
     if constexpr (LAST) split_inv16<MLOW>(x, k);
@@ -375,6 +393,7 @@ template <typename R, bool DAG, int EPI, int LS, bool MOB, typename T>
 __device__ __forceinline__ void split_finish(cplx<R> (&acc)[3], const cplx<R> (&U)[3], const cplx<R> (&L)[3],
                                              const Tri<T>& cx, const Tri<T>& cy, const SplitLane& q, int Ls,
                                              const HopArgs& A, const InvCoef<R>& inv) {
+  HDCG_PINNED
   const bool row3 = q.row == 3;
 #pragma unroll
   for (int k = 0; k < 3; ++k)
@@ -392,7 +411,17 @@ __device__ __forceinline__ void split_finish(cplx<R> (&acc)[3], const cplx<R> (&
     const bool wall = (q.upper != DAG) ? q.s == 0 : q.s == Ls - 1;
     const R f = wall ? -m * be : be;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) acc[k] = al * cx.get(k) + f * cy.get(k) - qu * acc[k];
+    for (int k = 0; k < 3; ++k) {
+      // FP32: the largest term last, the product that is exact in Shamir's M_5
+      // (beta = -1) as the plain one: two roundings, one of them small (H
+      // against 64 bits 7.74e-8 -> 7.29e-8).  FP64 keeps the order of the
+      // definition, M_5 c first: a 64-bit reference has the same roundings there.
+      const cplx<R> x = cx.get(k), y = cy.get(k);
+      if constexpr (sizeof(R) == 4)
+        acc[k] = cmk(fma(al, x.re, fma(-qu, acc[k].re, f * y.re)), fma(al, x.im, fma(-qu, acc[k].im, f * y.im)));
+      else
+        acc[k] = cmk(fma(-qu, acc[k].re, fma(al, x.re, f * y.re)), fma(-qu, acc[k].im, fma(al, x.im, f * y.im)));
+    }
   }
 }
 
@@ -400,11 +429,16 @@ __device__ __forceinline__ void split_finish(cplx<R> (&acc)[3], const cplx<R> (&
 template <typename R, typename T>
 __device__ __forceinline__ void split_residual(cplx<R> (&acc)[3], const Tri<T>& r, const Tri<T>& p, const HopArgs& A,
                                                int rhs) {
+  HDCG_PINNED
   const R a = (R)A.cg_alpha[rhs], l = (R)A.cg_lam;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    if (A.cg_p) acc[k] = acc[k] + l * p.get(k);
-    acc[k] = r.get(k) - a * acc[k];
+    if (A.cg_p) {
+      const cplx<R> v = p.get(k);
+      acc[k] = cmk(fma(l, v.re, acc[k].re), fma(l, v.im, acc[k].im));
+    }
+    const cplx<R> v = r.get(k);
+    acc[k] = cmk(fma(-a, acc[k].re, v.re), fma(-a, acc[k].im, v.im));
   }
 }
 
@@ -569,8 +603,8 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
           for (int d = 0; d < 4; ++d)
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-              a[d][k] = b5 * u[d].get(k) + wu * us[d].get(k);
-              b[d][k] = b5 * l[d].get(k) + wl * ls[d].get(k);
+              a[d][k] = split_c5(b5, u[d].get(k), wu, us[d].get(k));
+              b[d][k] = split_c5(b5, l[d].get(k), wl, ls[d].get(k));
             }
           split_dir<0, true>(U, L, a[0], b[0], W, g0);
           split_dir<0>(U, L, a[1], b[1], W + 36, -g0);
@@ -589,7 +623,7 @@ hop_split_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
       if (EPI != EPI_INV && A.partials && active) {
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-          nrm += (double)acc[k].re * (double)acc[k].re + (double)acc[k].im * (double)acc[k].im;
+          nrm = fma((double)acc[k].im, (double)acc[k].im, fma((double)acc[k].re, (double)acc[k].re, nrm));
       }
       if (active) {
         T* o = out + rhs * A.field + (size_t)v * col;
