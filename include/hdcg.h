@@ -107,8 +107,9 @@ int dwf_destroy(dwf_op_t op);
  *           (all 0: consecutive checkerboard sites); a block that does not
  *           divide the lattice falls back to 0; one of more than 256 / Ls sites
  *           is marched along t where the library has that form (Shamir, Ls 8,
- *           12 or 16, by and bz >= 2, at most 16 waves of bx by bz sites, 8 in
- *           complex128), else falls back to 0;
+ *           12 or 16, complex64 with at most 16 waves of bx by bz sites or
+ *           complex128 with 8, by and bz >= 2; lds_kb and rg do not apply),
+ *           else falls back to 0;
  *   remap   1: workgroups reordered so each XCD takes one contiguous range;
  *   lds_kb  minimum LDS per workgroup in KiB (0..150; caps occupancy);
  *   nt      1: non-temporal output stores;

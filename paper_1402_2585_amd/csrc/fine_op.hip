@@ -743,9 +743,10 @@ static void launch_split(bool dagger, int epi, bool mob, int Ls, bool loop, dim3
 
 // Whether the marching form takes this block: bx x by x bz pairs of sites,
 // marched over bt planes (extents that divide the lattice, at least two pairs
-// in y and z, waves and LDS for one workgroup; Shamir, Ls 8, 12 or 16).
+// in y and z, waves and LDS for one workgroup; Shamir, Ls 8, 12 or 16, not 16
+// bits).
 static bool march_fits(const Geom& g, bool mob, int prec, const int* b) {
-  if (mob || (g.Ls != 16 && g.Ls != 12 && g.Ls != 8) || b[0] < 1 || b[1] < 2 || b[2] < 2 || b[3] < 1) return false;
+  if (mob || prec == DWF_BF16 || (g.Ls != 16 && g.Ls != 12 && g.Ls != 8) || b[0] < 1 || b[1] < 2 || b[2] < 2 || b[3] < 1) return false;
   if (g.Xh % b[0] || g.Y % b[1] || g.Z % b[2] || g.T % b[3]) return false;
   const int npair = b[0] * b[1] * b[2], ns = 16 / g.Ls;
   return npair % ns == 0 && npair / ns <= (prec == DWF_C128 ? 8 : 16) &&
@@ -958,17 +959,19 @@ static int hop_launch(dwf_op* op, const HopTune& tune, T* out, const T* in, cons
   const cplx<R>* G = reinterpret_cast<const cplx<R>*>(dbl ? op->gauge128.ptr : op->gauge64.ptr) +
                      (size_t)out_parity * g.Vh * 72;
   const R* pw = reinterpret_cast<const R*>(dbl ? op->pw128.ptr : op->pw64.ptr);
-  if (march) {
-    A.fold = nrhs > 1 && nwg % 8 == 0;
-    const int npair = A.bx * A.by * A.bz;
-    const dim3 mgrid(A.fold ? nwg * nrhs : nwg, A.fold ? 1 : nrhs), mblock(npair / (16 / g.Ls) * 64);
-    const size_t mlds = march_lds(npair, g.Ls, sizeof(T), sizeof(cplx<R>));
-    if (g.Ls == 16) launch_march_ls<R, T, 16>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
-    else if (g.Ls == 12) launch_march_ls<R, T, 12>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
-    else launch_march_ls<R, T, 8>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
-    HDCG_HIP(hipGetLastError());
-    if (norm_result) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride, fin);
-    return DWF_OK;
+  if constexpr (!kSMajor<T>) {
+    if (march) {
+      A.fold = nrhs > 1 && nwg % 8 == 0;
+      const int npair = A.bx * A.by * A.bz;
+      const dim3 mgrid(A.fold ? nwg * nrhs : nwg, A.fold ? 1 : nrhs), mblock(npair / (16 / g.Ls) * 64);
+      const size_t mlds = march_lds(npair, g.Ls, sizeof(T), sizeof(cplx<R>));
+      if (g.Ls == 16) launch_march_ls<R, T, 16>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
+      else if (g.Ls == 12) launch_march_ls<R, T, 12>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
+      else launch_march_ls<R, T, 8>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
+      HDCG_HIP(hipGetLastError());
+      if (norm_result) return launch_finalize(1, A.partials, nwg, nwg, nrhs, norm_result, stream, A.pstride, fin);
+      return DWF_OK;
+    }
   }
   dim3 grid(nwg, (nrhs + A.rg - 1) / A.rg), block(threads);
   const size_t epi_lds =
@@ -1032,11 +1035,8 @@ int launch_mpc(dwf_op* op, T* out, const T* in, bool dagger, int nrhs, hipStream
 // candidates (hop_march.h) win where L2-to-L1 traffic bounds the split form
 // and there are workgroups enough to fill the chip with chunks of t: H in
 // complex64 on 24^3 x 48 x 16 1.69 against 1.87 ms, on 32^3 x 64 x 16 4.65
-// against 5.95 ms, on 16^3 x 32 x 16 0.316 against 0.352 ms; on 16^4 and on
-// 16-bit fields (half the bytes for the same instructions) the split form
-// stays ahead (0.142 against 0.150 ms; 0.95 against 1.05 ms on 24^3 x 48; 8
-// right-hand sides on 16^3 x 32 1.53 against 1.56 ms, though the march wins
-// the tuner's short bursts there at a higher clock: it is not tried).
+// against 5.95 ms, on 16^3 x 32 x 16 0.310 against 0.352 ms; in complex64 on
+// 16^4 the split form stays ahead (0.142 against 0.150 ms).
 struct HopShape {
   int block[4];
   int remap;
@@ -1069,7 +1069,7 @@ static bool hop_candidate(const dwf_op* op, int prec, int c, HopTune* shape) {
   if (!s.march) return true;
   const Geom& g = op->g;
   int best = 0;
-  for (int n = 4; n <= g.T && prec != DWF_BF16; n *= 2) {
+  for (int n = 4; n <= g.T; n *= 2) {
     const int b[4] = {s.block[0], s.block[1], s.block[2], n};
     if (march_fits(g, op->f5.mobius, prec, b) &&
         (best == 0 || (long)g.Vh / (b[0] * b[1] * b[2] * n) >= s.march))

@@ -62,7 +62,6 @@ void launch_march_ls(bool dagger, int epi, dim3 grid, dim3 block, size_t lds, hi
   template void launch_split_mob<float, bf16c, LS>(bool, int, bool, bool, HDCG_HOP_ARGS(float, bf16c));
 #define HDCG_HOP_MARCH(LS)                                                          \
   template void launch_march_ls<double, c128, LS>(bool, int, HDCG_HOP_ARGS(double, c128)); \
-  template void launch_march_ls<float, c64, LS>(bool, int, HDCG_HOP_ARGS(float, c64));     \
-  template void launch_march_ls<float, bf16c, LS>(bool, int, HDCG_HOP_ARGS(float, bf16c));
+  template void launch_march_ls<float, c64, LS>(bool, int, HDCG_HOP_ARGS(float, c64));
 
 }  // namespace hdk

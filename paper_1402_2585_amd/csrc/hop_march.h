@@ -1,5 +1,5 @@
 // The hop stage marched along t with the input columns in LDS (Shamir,
-// Ls = 8, 12 or 16).
+// Ls = 8, 12 or 16, complex64 and complex128).
 //
 // hop_split_kernel reads each input column from the caches by up to eight
 // waves: on 24^3 x 48 x 16 in complex64 H takes 1.87 ms with the real
@@ -22,9 +22,12 @@
 // What bounds it now: in complex64 the vector units (600 instructions a site
 // and plane, 4 waves a SIMD) as much as HBM; a workgroup's 16 waves fill a
 // CU, so a short march pays its three-plane start-up (16^4: slower than the
-// split form).  H in complex64, split against marching: 24^3 x 48 x 16 1.87
-// and 1.69 ms, 32^3 x 64 x 16 5.95 and 4.65 ms (5.0 TB/s of algorithmic
-// bytes).
+// split form).  H, split against marching: complex64 24^3 x 48 x 16 1.87 and
+// 1.66 ms, 32^3 x 64 x 16 5.95 and 4.65 ms (5.0 TB/s of algorithmic bytes);
+// complex128 24^3 x 48 x 16 3.26 and 3.02 ms, 16^4 x 16 282 and 270 us.
+// 16-bit fields, half the bytes for the same instructions, have no marched
+// form: 1.02 and 1.01 ms on 24^3 x 48, 8 right-hand sides on 16^3 x 32 1.53
+// and 1.55 ms.
 #pragma once
 
 #include "hop_split.h"
@@ -130,11 +133,10 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
   constexpr int col = 12 * LS;
   // component offsets of this lane within a column: its upper and lower spin,
   // and the spin it ends with
-  constexpr int cs = kSMajor<T> ? 1 : LS;
-  const int off0 = kSMajor<T> ? q.s * 12 : q.s;
-  const int offu = off0 + sp * 3 * cs, offl = off0 + (6 + lsp * 3) * cs, offo = off0 + q.spin * 3 * cs;
+  constexpr int cs = LS;
+  const int offu = q.s + sp * 3 * cs, offl = q.s + (6 + lsp * 3) * cs, offo = q.s + q.spin * 3 * cs;
   const int sn = (q.upper != DAG) ? (q.s > 0 ? q.s - 1 : Ls - 1) : (q.s + 1 < Ls ? q.s + 1 : 0);
-  const int offn = (kSMajor<T> ? sn * 12 : sn) + q.spin * 3 * cs;
+  const int offn = sn + q.spin * 3 * cs;
 
   // tile, pair and its neighbours
   int gx, gy, gz, gt;
