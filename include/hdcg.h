@@ -112,7 +112,9 @@ int dwf_destroy(dwf_op_t op);
  *           else falls back to 0;
  *   remap   1: workgroups reordered so each XCD takes one contiguous range;
  *   lds_kb  minimum LDS per workgroup in KiB (0..150; caps occupancy);
- *   nt      1: non-temporal output stores;
+ *   nt      1: non-temporal output stores; in complex128 with Ls <= 16 also
+ *           non-temporal loads of the links and the centre values (not in the
+ *           marched form);
  *   morton  block order: 0 lexicographic; 1 Morton (power-of-two block
  *           grids, else lexicographic); 2 the block grid bisected into eight
  *           compact regions, one per XCD, Morton order inside each (any
@@ -134,7 +136,8 @@ int dwf_destroy(dwf_op_t op);
  * milliseconds where H fills the chip (about 0.1 s in all; 10 ms on small
  * lattices; skipped while the stream is being captured), and
  * keeps the fastest for that storage and count; the other entries are
- * {lds_kb 0, nt 0, phases 0}.  This call fixes a shape instead
+ * lds_kb 0, phases 0, and nt 1 in complex128 with Ls <= 16 where the links of a
+ * stage (72 complex numbers a site of one parity) exceed 32 MB, else 0.  This call fixes a shape instead
  * (launch-shape sweeps and their tests); shape[0] = -1 returns to the
  * autotuned shapes.  DWF_ERR_ARG on an invalid entry. */
 int dwf_set_hop_shape(dwf_op_t op, const int shape[10]);

@@ -52,7 +52,7 @@ struct HopTune {
   int block[4] = {2, 2, 1, 1};  // workgroup site block in (x/2, y, z, t), powers of two; 0 = linear
   int remap = 1;                // XCD-contiguous workgroup order
   int lds_kb = 0;               // minimum LDS per workgroup (caps occupancy)
-  int nt = 0;                   // non-temporal output stores
+  int nt = 0;                   // non-temporal output stores (complex128, Ls <= 16: links, centre values too)
   int morton = 1;               // block order: 0 lexicographic, 1 Morton (power-of-two block
                                 // grids), 2-4 per-XCD regions from a table
   int phases = 0;               // neighbour-load phases per stage (2 or 4; 0: 4 for complex128,

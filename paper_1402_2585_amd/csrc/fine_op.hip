@@ -920,13 +920,8 @@ static int hop_launch(dwf_op* op, const HopTune& tune, T* out, const T* in, cons
     }
   }
   A.field = (size_t)g.Vh * 12 * g.Ls;
-  // Streamed operands.  In complex128, once a stage's links alone exceed the
-  // eight 4 MB L2s, links, centre values and output stores pass the caches
-  // as non-temporal: they are used once, and the neighbour columns, used
-  // eight times, stay (H on 16^4 x 16: 290 -> 273 us).  Smaller lattices keep
-  // them cached for the next stage, and the narrower types measured the same
-  // or slower with it (complex64 on 12x10x6x14 x 12: 38 -> 45 us).
-  if (split && sizeof(R) == 8 && (size_t)g.Vh * 72 * sizeof(cplx<R>) > ((size_t)32 << 20)) A.nt = 7;
+  // In complex128 the split form streams links and centre values too
+  if (tune.nt && split && sizeof(R) == 8) A.nt = 7;
   A.alpha = op->f5.alpha;
   A.beta = op->f5.beta;
   A.ia = op->f5.ia;
@@ -1066,6 +1061,13 @@ static bool hop_candidate(const dwf_op* op, int prec, int c, HopTune* shape) {
   shape->remap = s.remap;
   shape->morton = s.order;
   shape->rg = s.rg;
+  // Streamed operands.  In complex128, once a stage's links alone exceed the
+  // eight 4 MB L2s, links, centre values and output stores pass the caches
+  // as non-temporal: they are used once, and the neighbour columns, used
+  // eight times, stay (H on 16^4 x 16: 290 -> 273 us).  Smaller lattices keep
+  // them cached for the next stage, and the narrower types measured the same
+  // or slower with it (complex64 on 12x10x6x14 x 12: 38 -> 45 us).
+  shape->nt = prec == DWF_C128 && op->g.Ls <= 16 && (size_t)op->g.Vh * 72 * sizeof(c128) > ((size_t)32 << 20);
   if (!s.march) return true;
   const Geom& g = op->g;
   int best = 0;

@@ -19,7 +19,7 @@ DEFAULT = (2, 2, 1, 1, 1, 0, 0, 1, 0, 1)
 
 
 def test_a_choice_stays_with_its_storage_and_count():
-    dims, Ls = (16, 16, 16, 16), 16
+    dims, Ls = (16, 16, 16, 8), 16
     banner("launch shape per storage")
     U = synth.gauge_field(dims, 0.7, 171)
     op, fresh = hd.FineOperator(U, dims, Ls, 1.8, 0.02), hd.FineOperator(U, dims, Ls, 1.8, 0.02)
@@ -76,3 +76,26 @@ def test_even_ls_against_oracle(Ls, mobius):
                 exact = ref.H(xin[r].astype(np.complex128))
                 assert np.linalg.norm((got[r] - exact).ravel()) / np.linalg.norm(exact.ravel()) < 4 * 2.0 ** -8, (shape, n, r)
     op.close()
+
+
+def test_streaming_follows_the_shape():
+    """Non-temporal accesses are an entry of the shape: on by default in
+    complex128 where the links exceed 32 MB (16^4: 37.7 MB), off and on as a
+    fixed shape says; the same bits either way."""
+    dims, Ls = (16, 16, 16, 16), 4
+    banner("streaming in the launch shape")
+    U = synth.gauge_field(dims, 0.7, 175)
+    op = hd.FineOperator(U, dims, Ls, 1.8, 0.02)
+    small = hd.FineOperator(synth.gauge_field((8, 8, 8, 8), 0.7, 175), (8, 8, 8, 8), Ls, 1.8, 0.02)
+    assert hd.dwf_get_hop_shape(op.h, hd.DWF_C128, 1)[0][6] == 1
+    assert hd.dwf_get_hop_shape(op.h, hd.DWF_C64, 1)[0][6] == 0
+    assert hd.dwf_get_hop_shape(small.h, hd.DWF_C128, 1)[0][6] == 0
+    x = op.to_native(synth.gaussian_half_field(dims, Ls, 176))
+    out = []
+    for nt in (0, 1):
+        hd.dwf_set_hop_shape(op.h, (2, 2, 1, 1, 1, 0, nt, 1, 0, 1))
+        assert hd.dwf_get_hop_shape(op.h, hd.DWF_C128, 1)[0][6] == nt
+        out.append(op.H(x))
+    assert torch.equal(out[0], out[1])
+    op.close()
+    small.close()
