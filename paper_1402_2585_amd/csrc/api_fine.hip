@@ -135,7 +135,7 @@ static int cg_one(dwf_op* op, c128* x, const c128* b, double tol, int maxiter, i
         double* nxt = rr_slot[(k + 1) & 1];
         // pap = <p, H p> = |M_pc p|^2 in stage 2, r -= alpha H p and |r|^2
         // (to the host too) in the last stage
-        CG_TRY(launch_cg_residual<double>(op, r, p, 1, CgStep{cur, nullptr, 0.0, pap, alpha, nxt, hp + (k % kRing)},
+        CG_TRY(launch_cg_residual<double>(op, r, p, 1, CgStep{cur, nullptr, 0.0, pap, alpha, nxt, hp + (k % kRing), true},
                                           stream));
         CG_TRY(b_cg_xp(red, x, p, r, n, 1, alpha, nxt, cur, false, nullptr, stream));
         CG_HIP(hipEventRecord(ev[k % kRing], stream));
@@ -208,7 +208,7 @@ static int cg_inner64(dwf_op* op, c64* e, const c64* f, double rtol, int maxiter
     if (k < maxiter) {
       double* cur = rr_slot[k & 1];
       double* nxt = rr_slot[(k + 1) & 1];
-      rc = launch_cg_residual<float>(op, r, p, 1, CgStep{cur, nullptr, 0.0, pap, alpha, nxt, hp + (k % kRing)}, stream);
+      rc = launch_cg_residual<float>(op, r, p, 1, CgStep{cur, nullptr, 0.0, pap, alpha, nxt, hp + (k % kRing), true}, stream);
       if (rc == DWF_OK) rc = b_cg_xp(red, e, p, r, n, 1, alpha, nxt, cur, false, nullptr, stream);
       if (rc == DWF_OK && hipEventRecord(ev[k % kRing], stream) != hipSuccess) rc = fail(DWF_ERR_HIP, "event record failed");
       ++k;

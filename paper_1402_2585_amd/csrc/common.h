@@ -290,12 +290,15 @@ __device__ __forceinline__ bool last_ticket(unsigned* counters, int rhs, unsigne
 
 // What a finalize launch (nq = 1) forms beside the sums: also (nullable,
 // pinned host memory) takes them too; alpha (nullable) takes num / (sum + lam
-// den2), or 0 for a zero denominator (den2 only for lam != 0).
+// den2) (den2 only for lam != 0).  A zero denominator gives 0, or with `strict`
+// infinity under a non-zero numerator: a breakdown that the residual's norm
+// then shows.
 struct FinCg {
   double* also = nullptr;
   const double *num = nullptr, *den2 = nullptr;
   double lam = 0.0;
   double* alpha = nullptr;
+  bool strict = false;
 };
 
 // one right-hand side's sum, by one thread
@@ -304,7 +307,8 @@ __device__ __forceinline__ void fin_store(double sum, int rhs, double* res, cons
   if (cg.also) __hip_atomic_store(cg.also + rhs, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (cg.alpha) {
     const double d = cg.lam != 0.0 ? sum + cg.lam * cg.den2[rhs] : sum;
-    cg.alpha[rhs] = d == 0.0 ? 0.0 : cg.num[rhs] / d;
+    const double n = cg.num[rhs];
+    cg.alpha[rhs] = d == 0.0 && (n == 0.0 || !cg.strict) ? 0.0 : n / d;
   }
 }
 

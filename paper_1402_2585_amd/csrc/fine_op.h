@@ -108,7 +108,7 @@ int launch_mpcdagmpc(dwf_op* op, T* out, const T* in, int nrhs, hipStream_t stre
                      double* pap_result /*nullable: <in, H in> = |M_pc in|^2 per rhs*/);
 
 // One CG step on H + lam, but for x and the next p: pap = <p, H p>, alpha =
-// num / (pap + lam den2) (0 for a zero denominator), r -= alpha (H p + lam p),
+// num / (pap + lam den2) (a zero denominator: FinCg, strict), r -= alpha (H p + lam p),
 // rr = |r|^2.  The residual is updated by the last hop stage as it forms H p,
 // which is never stored (Ls <= 16; one update kernel otherwise): of a step's
 // 19 field transfers three less, and four launches less (7 iterations of
@@ -121,6 +121,7 @@ struct CgStep {
   const double* den2;
   double lam;
   double *pap, *alpha, *rr, *rr_host;
+  bool strict = false;
 };
 template <typename R, typename T = cplx<R>>
 int launch_cg_residual(dwf_op* op, T* r, const T* p, int nrhs, const CgStep& cg, hipStream_t stream);

@@ -869,7 +869,7 @@ static int hop_launch(dwf_op* op, const HopTune& tune, T* out, const T* in, cons
   if (epi == EPI_RES)
     fin.also = cg->rr_host;
   else if (cg)
-    fin = {nullptr, cg->num, cg->den2, cg->lam, alpha};
+    fin = {nullptr, cg->num, cg->den2, cg->lam, alpha, cg->strict};
   A.g = g;
   A.out_parity = out_parity;
   // linear order: four waves of the split kernel, or one wave's worth of
