@@ -284,7 +284,8 @@ int blk_project_mfma(hdcg* h, const bf16c* P, const c64* fine, size_t fstride, i
   // left most of the chip idle on small coarse grids: 162 blocks, 24576
   // entries, Nvec 48, 16 RHS 516 us; Nvec 8, 12288 entries, 4 RHS 154 us),
   // each with at least four rounds of its waves.  Where the partial sums have
-  // no room yet and the stream is being captured, one slice.
+  // no room yet and the stream is being captured, or there is none for them,
+  // one slice.
   const int groups = h->Nc * ((nr + 15) / 16);
   int S = std::max(1, std::min(std::min(16, 1024 / groups), (nb + 15) / 16 / (4 * NW * U)));
   if (S > 1 && h->pj_cnt.bytes == 0) {
@@ -292,10 +293,14 @@ int blk_project_mfma(hdcg* h, const bf16c* P, const c64* fine, size_t fstride, i
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
       S = 1;
-    } else {
-      HDCG_TRY(h->pj_part.ensure((size_t)1024 * mt * 256 * sizeof(c64)));
-      HDCG_TRY(h->pj_cnt.ensure(1024 * sizeof(unsigned)));
-      HDCG_HIP(hipMemsetAsync(h->pj_cnt.ptr, 0, h->pj_cnt.bytes, st));
+    } else if (h->pj_part.ensure((size_t)1024 * mt * 256 * sizeof(c64)) < 0 ||
+               h->pj_cnt.ensure(1024 * sizeof(unsigned)) < 0) {
+      (void)hipGetLastError();
+      h->pj_part.release();
+      S = 1;
+    } else if (hipMemsetAsync(h->pj_cnt.ptr, 0, h->pj_cnt.bytes, st) != hipSuccess) {
+      h->pj_cnt.release();
+      return fail(DWF_ERR_HIP, "project: clearing the tickets failed");
     }
   }
   const dim3 grid(h->Nc, (nr + 15) / 16, S);
