@@ -347,7 +347,8 @@ struct hdcg_stats {
   double true_residual;  /* max over RHS of the FP64 relative residual */
   double seconds;        /* solve wall time (setup excluded) */
   double setup_seconds;  /* wall time of hdcg_setup */
-  double matmuls_fp64;   /* applications of H in complex128 (per RHS summed) */
+  double matmuls_fp64;   /* applications of H in complex128 (per RHS summed; here and below
+                            the last step of an M_IRS applies M_pc alone and counts half) */
   double matmuls_fp32;   /* applications of H in complex64 (per RHS summed) */
   double matmuls_bf16;   /* applications of H on 16-bit fields (M_IRS with irs_prec = DWF_BF16) */
   int group_size;        /* right-hand sides solved together (one batch shares every operator pass) */

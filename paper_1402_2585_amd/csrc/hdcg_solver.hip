@@ -545,11 +545,15 @@ static int precondition_body(hdcg* h, c64* y, const c64* r, int nr, InnerStats* 
   return DWF_OK;
 }
 
+// Applications of H in one M_IRS: its last step needs <p, H p> = |M_pc p|^2
+// alone, half of one.
+static double irs_matmuls(const hdcg* h) { return h->prm.n_irs > 0 ? h->prm.n_irs - 0.5 : 0.0; }
+
 static void count_precondition(hdcg* h, int nr, InnerStats* is) {
   if (h->prm.irs_prec == DWF_BF16)
-    is->matmuls16 += (double)h->prm.n_irs * nr;
+    is->matmuls16 += irs_matmuls(h) * nr;
   else
-    is->matmuls32 += (double)h->prm.n_irs * nr;
+    is->matmuls32 += irs_matmuls(h) * nr;
   is->matmuls32 += nr;
   is->coarse_solves += 1;
 }
