@@ -51,7 +51,7 @@ def flops_H(dims, Ls, nrhs):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("fine_op.hip", "fine_op.h", "common.h"):
+    for f in ("fine_op.hip", "fine_op.h", "hop_dev.h", "hop_split.h", "hop_march.h", "hop_ls.h", "common.h"):
         h.update(open(os.path.join(ROOT, "paper_1402_2585_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -554,7 +554,7 @@ def main():
                 "gflops": round(fl / (ms64 * 1e-3) / 1e9, 1), "frac_of_hbm_peak": round(gbs64 / HBM_PEAK_GBS, 3),
                 "traffic": traffic_from_profiles("c64")},
         "roofline": {
-            "kernel": "hop_kernel (4 launches per application; per-launch average)",
+            "kernel": "hop stage (hop_split_kernel or hop_march_kernel; 4 launches per application; per-launch average)",
             "bound": "hbm",
             "achieved": round(gbs128, 1),
             "peak": HBM_PEAK_GBS,

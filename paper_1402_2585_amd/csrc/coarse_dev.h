@@ -185,8 +185,8 @@ __device__ __forceinline__ unsigned short to16(float f) {
 
 // `red` is NW * MT * NT * 64 f32x4 of LDS.  Writes out[r][a][:] for the
 // nrhs right-hand sides of `in` (at most 16 when NT = 2, 8 when NT = 1).
-// With STAGED (one right-hand side) `in` is the site's operand gathered
-// into LDS: in[l * nvec + k] = c[nbr(a,l)][k].  COH: the operand is read
+// With STAGED `in` is the site's operand gathered into LDS:
+// in[(r * NS + l) * nvec + k] = c_r[nbr(a,l)][k].  COH: the operand is read
 // with coherent loads (persistent kernels).  K32: gfx950's 16x16x32 MFMA
 // (8 K values per lane; the A fragment of one 32-wide step is two
 // consecutive 16-wide storage steps, one 16-byte load per lane; needs

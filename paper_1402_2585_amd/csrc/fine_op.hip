@@ -12,10 +12,11 @@
 // Why two: the split form has half the sites in flight for the same bytes in
 // flight (the neighbour columns then stay in the XCD's 4 MB L2), no serial
 // recurrence and one load phase instead of four, so one wave's latency is a
-// third; but its rows hold at most 16 slices.  H, before and after: 4^4 x 8
-// complex128 33.7 -> 17.6 us; 16^4 x 16 complex128 314 -> 283 us; a complex128
-// CG iteration on 8^3 x 16 x 8 68 -> 52 us; 24^3 x 48 x 16 complex64, bound by
-// the bytes between L2 and L1, 1.86 -> 1.82 ms.
+// third; but its rows hold at most 16 slices.  H, with one thread a slice and
+// split: 4^4 x 8 complex128 34.0 and 18.9 us; 16^4 x 16 complex128 314 and 282
+// us; 24^3 x 48 x 16 complex64, bound by the bytes between L2 and L1, 1.86 and
+// 1.87 ms (marched: 1.68); 16 bits, 8 right-hand sides on 16^3 x 32 x 16, 1.544
+// and 1.519 ms.
 //
 // Epilogues (the fifth-dimension factors of M_pc, Sec. IV):
 //   EPI_INV  out = M_5^-1 (Dh in)          or M_5^-+ (Dh^+ in)   [dense in s]

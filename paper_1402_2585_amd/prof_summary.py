@@ -77,7 +77,7 @@ def hop_json(dirs, out_path, root, shapes=None):
     fscale = gib_kib / avg(dirs["copy"][0], "FETCH_SIZE", "copy_kernel")[0]
     wscale = gib_kib / avg(dirs["copy"][1], "WRITE_SIZE", "copy_kernel")[0]
     h = hashlib.sha256()
-    for f in ("fine_op.hip", "fine_op.h", "common.h"):
+    for f in ("fine_op.hip", "fine_op.h", "hop_dev.h", "hop_split.h", "hop_march.h", "hop_ls.h", "common.h"):
         h.update(open(os.path.join(root, "paper_1402_2585_amd", "csrc", f), "rb").read())
     V, Ls = 16 ** 4, 16
     half = V // 2 * Ls * 12
