@@ -886,7 +886,6 @@ static int hop_launch(dwf_op* op, const HopTune& tune, T* out, const T* in, cons
   A.nbt = 1;
   A.order = nullptr;
   A.nrhs = nrhs;
-  A.fold = 0;
   const int prec = std::is_same<T, bf16c>::value ? DWF_BF16 : prec_of<R>();
   // a block of more than 256 / Ls sites is marched along t where that fits
   const int* b = tune.block;
@@ -957,9 +956,8 @@ static int hop_launch(dwf_op* op, const HopTune& tune, T* out, const T* in, cons
   const R* pw = reinterpret_cast<const R*>(dbl ? op->pw128.ptr : op->pw64.ptr);
   if constexpr (!kSMajor<T>) {
     if (march) {
-      A.fold = nrhs > 1 && nwg % 8 == 0;
       const int npair = A.bx * A.by * A.bz;
-      const dim3 mgrid(A.fold ? nwg * nrhs : nwg, A.fold ? 1 : nrhs), mblock(npair / (16 / g.Ls) * 64);
+      const dim3 mgrid(nwg, nrhs), mblock(npair / (16 / g.Ls) * 64);
       const size_t mlds = march_lds(npair, g.Ls, sizeof(T), sizeof(cplx<R>));
       if (g.Ls == 16) launch_march_ls<R, T, 16>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);
       else if (g.Ls == 12) launch_march_ls<R, T, 12>(dagger, epi, mgrid, mblock, mlds, stream, out, in, center, G, pw, A);

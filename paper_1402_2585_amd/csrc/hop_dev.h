@@ -68,7 +68,6 @@ struct HopArgs {
   const int* order;   // nullable: block of workgroup blockIdx.x, packed gx | gy << 8 | gz << 16 | gt << 24
   int rg;             // right-hand sides per workgroup (blockIdx.y takes rg of the nrhs)
   int nrhs;
-  int fold;           // march: blockIdx.x runs over tiles and right-hand sides
   size_t field;       // complex elements per rhs
   // fifth dimension: M_5 = alpha + beta K, recurrence of M_5^-1 y_s = ia x_s + kap y_{s-1},
   // Mobius C_5 = b5 + c5 K (K: P+ from s-1, P- from s+1, -mass at the wrap)

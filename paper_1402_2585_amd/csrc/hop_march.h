@@ -100,9 +100,11 @@ __device__ __forceinline__ void march_step(Tri<T>& r, Tri<T>& p, const T* rf, co
   if (pf) p.ld(pf + (size_t)v * COL + off, cs);
 }
 
-// Grid: tiles x right-hand sides.  A.fold: blockIdx.x runs over both, the
-// right-hand sides of a tile one after another on the same XCD, which then
-// serves the links of all but the first from its L2.  by, bz >= 2.
+// Grid: tiles x right-hand sides, a right-hand side after the other: tiles that
+// share faces are in flight together and meet in L2.  That is worth more than
+// the links of a tile's several right-hand sides in one pass over them (H in
+// complex64 on 24^3 x 48 x 16, 16 right-hand sides: 25.0 against 29.6 ms, with
+// 2, 4 and 8 at a time 25.7, 26.8 and 28.4).  by, bz >= 2.
 template <typename R, bool DAG, int EPI, int LS, typename T>
 __global__ void __launch_bounds__(sizeof(R) == 8 ? 512 : 1024)
 hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restrict__ center,
@@ -110,12 +112,7 @@ hop_march_kernel(T* __restrict__ out, const T* __restrict__ in, const T* __restr
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const Geom& g = A.g;
   constexpr int Ls = LS, NS = 16 / LS;
-  int wg = blockIdx.x, rhs = blockIdx.y;
-  if (A.fold) {  // the k-th workgroup of XCD x takes tile k / nrhs of that XCD's
-    const int k = wg >> 3;
-    rhs = k % A.nrhs;
-    wg = (k / A.nrhs) * 8 + (wg & 7);
-  }
+  const int wg = blockIdx.x, rhs = blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   SplitLane q;
